@@ -128,8 +128,7 @@ def c4_shapes(w):
 
 
 SCHEDULE_NOTE = ("per row-count bin (16 rows each): (XCD chunks, persistent workgroups per XCD or 0 for one per "
-                 "face, split mode: 0 parts at their own narrower widths, 1 whole bin at its width, 2 part 0 "
-                 "narrower, 3 parts 0-1 at width - 4), chosen by timing on the workload")
+                 "face, 0), chosen by timing on the workload")
 
 
 def batched_comparison(steps):
@@ -725,7 +724,7 @@ def main():
         tuning, best = b.autotune(out=st)
         schedule = [(int(tuning.xcd_chunks[i]), int(tuning.blocks_per_xcd[i]), int(tuning.split[i]))
                     for i in range(8)]
-        log(f"autotuned per bin (xcd chunks, blocks per xcd, split mode): {schedule}")
+        log(f"autotuned per bin (xcd chunks, blocks per xcd, 0): {schedule}")
 
     for _ in range(args.warmup):
         b.build(out=st)

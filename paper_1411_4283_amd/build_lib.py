@@ -7,8 +7,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcutcell.so")
-SOURCES = ["api.hip", "enumerate.hip", "stencil.hip", "stencil_d2q2.hip", "stencil_d2q4.hip", "stencil_d3q2.hip",
-           "stencil_d3q4.hip", "stencil_d3q4_mid.hip", "stencil_d3q4_high.hip",
+SOURCES = ["api.hip", "enumerate.hip", "stencil.hip",
+           *[f"stencil_d{d}q{q}_r{r}.hip" for d in (3, 2) for q in (4, 2) for r in (2, 1)],
            "stencil_qr.hip", "apply.hip", "adjoint.hip", "solve.hip", "laplacian.hip", "order.hip", "packed.hip"]
 
 HIPCC_FLAGS = [

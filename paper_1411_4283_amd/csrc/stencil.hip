@@ -134,7 +134,6 @@ static void schedules_from(const cutcell_tuning* t, BinSchedule* sc) {
     if (t) {
       sc[b].xcd = t->xcd_chunks[b] > 1 ? t->xcd_chunks[b] : 1;
       sc[b].per_xcd = t->blocks_per_xcd[b] > 0 ? t->blocks_per_xcd[b] : 0;
-      sc[b].split = (t->split[b] >= 0 && t->split[b] <= 3) ? t->split[b] : 0;
     }
   }
 }
@@ -155,9 +154,8 @@ int backward_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_c
 }
 
 // Times every candidate of every non-empty bin on these faces (HIP events, best of
-// `reps`) and keeps the fastest: the five launch schedules, crossed with the split modes
-// the bin's compiled kernel widths allow; then solves all bins with the choices, so
-// val/status hold the same stencils as an untuned build.
+// `reps`) and keeps the fastest of the five launch schedules; then solves all bins with the
+// choices, so val/status hold the same stencils as an untuned build.
 int tune_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count, const int64_t* row_ptr,
                   const int32_t* col, double* val, int8_t* status, hipStream_t st, cutcell_tuning* out, int reps,
                   double* best_ms) {
@@ -177,17 +175,8 @@ int tune_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count
     best_ms[b] = -1.0;
     if (bin_count[b] == 0) continue;
     double best = 1e300;
-    // split modes that differ for this bin: 1 (whole bin at its width) always; 2 with a
-    // NPAD - 8 instance, 3 with a NPAD - 4 one, 0 with both
-    const int nm = narrow_mask_of(o.dim, o.order, b);
-    int splits[4], nsplit = 0;
-    splits[nsplit++] = 1;
-    if (nm & 1) splits[nsplit++] = 2;
-    if (nm & 2) splits[nsplit++] = 3;
-    if ((nm & 3) == 3) splits[nsplit++] = 0;
-    for (int c = 0; c < nlaunch * nsplit; ++c) {
-      BinSchedule cand = launch[c % nlaunch];
-      cand.split = splits[c / nlaunch];
+    for (int c = 0; c < nlaunch; ++c) {
+      const BinSchedule cand = launch[c];
       BinSchedule trial[kMaxBins];
       for (int i = 0; i < kMaxBins; ++i) trial[i] = cand;
       double tmin = 1e300;
@@ -213,7 +202,7 @@ int tune_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count
   for (int b = 0; b < kMaxBins; ++b) {
     out->xcd_chunks[b] = sc[b].xcd;
     out->blocks_per_xcd[b] = sc[b].per_xcd;
-    out->split[b] = sc[b].split;
+    out->split[b] = 0;
   }
   hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 1LL, 0);
   return run_bins(w, o, bin_count, row_ptr, col, val, status, st, nullptr, sc);

@@ -6,19 +6,26 @@
 // wavefront owns one face:
 //   1. rows: each lane builds its row(s) of B in registers -- the row's moments,
 //      re-centred to x0 by the binomial theorem, divided by the zeroth moment and
-//      scaled by the weight -- and stores them in LDS; a row whose zeroth moment is
-//      below kSmallCell is formed in double-double and rounded (the moments of a small
+//      scaled by the weight -- and puts them in LDS, 64 at a time; a row whose zeroth moment
+//      is below kSmallCell is formed in double-double and rounded (the moments of a small
 //      cut cell about its centre nearly cancel when shifted to x0);
-//   2. G = B^T B on the FP64 matrix cores (v_mfma_f64_16x16x4f64, 16 x 16 tiles, rows
-//      of B as the contraction index); lane i collects row i from the tiles with
-//      ds_bpermute (no shared-memory copy of G);
-//   3. G is equilibrated to unit diagonal and inverted by symmetric Gauss-Jordan sweeps,
-//      lane i holding row i in registers; the sweep pivots are the Cholesky pivots;
-//   4. z from the semi-normal equations z = B G^-1 F~ followed by one step of refinement
+//   2. G = B^T B on the FP64 matrix cores, rows of B as the contraction index; it stays in
+//      their output layout, spread over all 64 lanes (Tile, WaveMatrix);
+//   3. G is equilibrated to unit diagonal and inverted in place by symmetric sweeps over
+//      blocks of four pivots on the matrix cores, with the right-hand side as one more row;
+//      the pivots are the Cholesky pivots;
+//   4. z from the semi-normal equations z = B G^-1 F~, a lane's rows times y, followed by one
+//      step of refinement
 //      with the residual F~ - B^T z computed from B itself in compensated arithmetic
 //      (twice the working precision), which leaves the error of rounding B to FP64, a few
 //      1e-17 cond(B), where the initial error is ~cond(B)^2 eps;
 //   5. val = h^(D-2) W z.
+// What bounds it, 64^3 minus a sphere, 3D order 4 (724k faces, 88 rows x 35 columns for most
+// of them): the FP64 pipe, which vector FMAs and matrix instructions share on MI355X (32
+// flop per cycle and SIMD either way), and the latency between dependent steps that two
+// waves per SIMD leave.  One launch, 12.8 ms; with lane i holding row i of G (29 of 64 lanes
+// idle in the sweep, one exchange through LDS per pivot, a transposition of G by lane
+// permutes) and every row in LDS (three waves on two SIMDs) it was 17.9 ms in six launches.
 // Under Neumann EB conditions (a separate kernel instance) the EB rows are the
 // normal-derivative rows of eq. 'Neu moment eq for cp' and their values carry h^(D-1);
 // the EB faces themselves have a one-entry stencil (their area) and are written by
@@ -164,59 +171,83 @@ __device__ __forceinline__ bool neumann_row(const GeomPtrs& gp, int32_t e, const
   return finite;
 }
 
-// Columns of G beyond the full 16-wide tiles (at most 4, done on the vector ALUs).
+// ---- shape of the Gram matrix in the wave --------------------------------------------------
+// G = B^T B (and its inverse) is spread over the wave in the output layout of the FP64
+// matrix instructions: with r = lane / 16 and c = lane % 16, register q of tile (I, J) holds
+// entry (16 I + r + 4 q, 16 J + c).  The MV (1 to 3) columns past the last full tile are
+// kept as rows: ar[J] holds entry (16 MTF + r, 16 J + c) and t entry (16 MTF + r, 16 MTF +
+// c % 4).  Row and column M hold the right-hand side while the matrix is inverted.
 template <int D, int Q>
-struct GramSplit {
+struct Tile {
   static constexpr int M = Dims<D, Q>::M, MT = Dims<D, Q>::MT;
-  static constexpr int MTF = (MT > 1 && M - 16 * (MT - 1) <= 4) ? MT - 1 : MT;   // tiles per side
+  static constexpr int MTF = (MT > 1 && M - 16 * (MT - 1) <= 3) ? MT - 1 : MT;   // full tiles per side
   static constexpr int MV = M - 16 * MTF > 0 ? M - 16 * MTF : 0;                // trailing columns
+  static constexpr int PI = 4 * MTF;        // rows of the tiles that one lane holds
+  static_assert(MV > 0 || M < 16 * MTF, "the right-hand side needs a free row");
 };
 
-// Shared memory of one face (one wave) in the forward kernel: B, and one buffer that holds
-// in turn the EB normal moments, the trailing Gram columns and z.  Everything else a lane
-// needs (W of its rows, its F~ entry, z of its rows) stays in registers.  On MI355X a
-// wave of this kernel is latency-bound, so the bytes per wave set how many waves share a
-// CU: 39.6 KB with a Gram buffer and W, F~ in shared memory, 27.7 KB like this (3D
-// order 4, 96 rows).
-template <int D, int Q, int NPAD>
-struct LeanSmem {
-  static constexpr bool kFull = false;
-  static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
-  static constexpr int MV = GramSplit<D, Q>::MV;
-  double Bs[NPAD * MS];      // rows of B = W A~
-  union {
-    struct {
-      double zs[NPAD];                 // z = B y (refinement; the pivot row of the sweep)
-      double zl[NPAD];                 // its low part where z is a double-double
-    };
-    double nus[D][M1];                 // EB normal moments about x0 (flux vector)
-    double tt[M * (MV > 0 ? MV : 1)];  // trailing Gram columns (transposition)
-  };
-};
-
-// Shared memory of one face in the adjoint kernel, which reads W, z, y and the normal
-// moments again after the forward solve.
-template <int D, int Q, int NPAD>
-struct FaceSmem {
-  static constexpr bool kFull = true;
-  static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
-  static constexpr int MV = GramSplit<D, Q>::MV;
-  double Bs[NPAD * MS];      // rows of B = W A~
-  double tt[M * (MV > 0 ? MV : 1)];
-  double gsum[M + 1];        // per-component sums of the adjoint
-  double ys[M + 1];          // y = G^-1 F~
-  double zs[NPAD];           // z = B y
-  double zl[NPAD];           // its low part where z is a double-double
-  double wls[NPAD];          // W
-  double nus[D][M1];         // EB normal moments about x0
-};
-
-// 64-bit ds_bpermute: the value of v in lane src_lane
-__device__ __forceinline__ double bpermute_f64(double v, int src_lane) {
-  const int lo = __builtin_amdgcn_ds_bpermute(src_lane * 4, __double2loint(v));
-  const int hi = __builtin_amdgcn_ds_bpermute(src_lane * 4, __double2hiint(v));
-  return __hiloint2double(hi, lo);
+// Slot of component i of a vector in shared memory: the PI components of the tile rows of
+// one lane (16 I + r + 4 q over I and q) are consecutive, so that a lane reads them with
+// 16-byte loads; the trailing components follow.
+template <int D, int Q>
+__host__ __device__ constexpr int vec_slot(int i) {
+  using TL = Tile<D, Q>;
+  return i < 16 * TL::MTF ? TL::PI * (i % 4) + i / 4 : i;
 }
+
+// The matrix in registers, and the column scales of its rows and columns.
+template <int D, int Q>
+struct WaveMatrix {
+  using TL = Tile<D, Q>;
+  double a[TL::MTF][TL::MTF][4];
+  double ar[TL::MTF];
+  double t;
+  double sj[TL::MTF];   // scale of column 16 J + c
+  double st, sr;        // of columns 16 MTF + c % 4 and 16 MTF + r
+  double sd;            // of component `lane`
+};
+
+// Shared memory of one face (one wave): 64 rows of B and one buffer used in turn for the EB
+// normal moments, the tile transposition, the pivot rows and z.  The rows stay in registers
+// too (a lane holds rows lane and lane + 64), so rows past 64 need no space of their own:
+// they take the first slots in turn with the rows that belong there.  20.3 KB in 3D order
+// 4, so that eight waves share the 160 KB of a CU, two on each SIMD, which is also what 256
+// registers a lane allow; with every row in shared memory it was 26 KB at 88 rows and six
+// waves.
+template <int D, int Q>
+struct FaceSmem {
+  static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
+  static constexpr int S = 64;
+  double Bs[S * MS];
+  union {
+    double nus[D][M1];                              // EB normal moments about x0 (flux vector)
+    double tr[256];                                 // one tile, for its transpose
+    double vec[40];                                 // a vector that every lane reads
+    struct {
+      double buf[64];                               // the pivot block
+      double pv[64];                                // the trailing rows' entries in its columns
+    };
+    struct {
+      double zs[kMaxRows];                          // z = B y
+      double zl[kMaxRows];                          // its low part where z is a double-double
+    };
+    struct {
+      double ys[40];                                // y and w of the adjoint
+      double wv[40];
+      double gx[64];                                // its sums over the rows
+      double g0[12];
+    };
+  };
+  double dy[40];                                    // the vector y that multiplies B
+};
+
+// c ? x : y by value: between two lvalues ?: selects an address, which would keep a register
+// array in memory.
+__device__ __forceinline__ double pick(bool c, double x, double y) { return c ? x : y; }
+
+// Orders shared-memory accesses of the wave's lanes with each other (one wave per
+// workgroup, whose shared-memory instructions complete in order): for the compiler only.
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Everything about the face that the row and flux computations need.
 struct FaceInfo {
@@ -270,33 +301,11 @@ __device__ __forceinline__ void face_x0_dd(const GridDims& g, const GeomPtrs& gp
   for (int ax = 0; ax < D; ++ax) x0[ax] = dd_add(dd_from(cown[ax] + 0.5), dd_div(dd_from(vm[1 + ax]), k0));
 }
 
-// Entry `lane` of the flux vector F~ (0 for lanes >= M) and, for EB faces, the normal
-// moments re-centred to x0 (sm.nus, lanes 0..D-1 one component each).  Ends with a barrier.
+// Re-centred normal moments of an EB face about x0, component d in lane d, into sm.nus.
 template <int D, int Q, class SM>
-__device__ __forceinline__ double face_flux(const GridDims& g, const GeomPtrs& gp, const FaceInfo& fi, SM& sm,
-                                            int lane, const dd* x0dd) {
-  constexpr int M = Dims<D, Q>::M, Mf = Dims<D, Q>::Mf, M1 = Dims<D, Q>::M1;
-  const int dn = fi.dn;
-  double fv = 0.0;
-  if (fi.kind == 0) {
-    // F~_p = face moment of p - e_d when p_d = 1 (reference normal +e_d)
-    const double* fm = gp.face_mom[dn] + (fi.ref - g.foff[dn]) * Mf;
-    if (lane < M) {
-      constexpr auto& T = kMono<D, Q>;
-      const int e0 = T.e[lane][0], e1 = T.e[lane][1], e2 = T.e[lane][2];
-      const int pd = (dn == 0) ? e0 : (dn == 1 ? e1 : e2);
-      if (pd == 1) {
-        int s;
-        if (D == 2) s = mono_index<1>(dn == 0 ? e1 : e0, 0, 0);
-        else if (dn == 0) s = mono_index<2>(e1, e2, 0);
-        else if (dn == 1) s = mono_index<2>(e0, e2, 0);
-        else s = mono_index<2>(e0, e1, 0);
-        fv = fm[s];
-      }
-    }
-    __syncthreads();
-    return fv;
-  }
+__device__ __forceinline__ void eb_normal_moments(const GridDims& g, const GeomPtrs& gp, const FaceInfo& fi, SM& sm,
+                                                  int lane, const dd* x0dd) {
+  constexpr int M = Dims<D, Q>::M, M1 = Dims<D, Q>::M1;
   const bool small = gp.vol_mom[(long long)fi.owner_cell * M] < kSmallCell;
   if (lane < D && !small) {
     double nu[M1];
@@ -316,7 +325,35 @@ __device__ __forceinline__ double face_flux(const GridDims& g, const GeomPtrs& g
     recentre_dd<D, Q - 1>(nu, dl);
     static_for<0, M1>([&](auto I) { sm.nus[lane][I] = nu[I].hi + nu[I].lo; });
   }
-  __syncthreads();
+  lds_order();
+}
+
+// Entry `lane` of the flux vector F~ (0 for lanes >= M).
+template <int D, int Q, class SM>
+__device__ __forceinline__ double face_flux(const GridDims& g, const GeomPtrs& gp, const FaceInfo& fi, SM& sm,
+                                            int lane, const dd* x0dd) {
+  constexpr int M = Dims<D, Q>::M, Mf = Dims<D, Q>::Mf;
+  const int dn = fi.dn;
+  double fv = 0.0;
+  if (fi.kind == 0) {
+    // F~_p = face moment of p - e_d when p_d = 1 (reference normal +e_d)
+    const double* fm = gp.face_mom[dn] + (fi.ref - g.foff[dn]) * Mf;
+    if (lane < M) {
+      constexpr auto& T = kMono<D, Q>;
+      const int e0 = T.e[lane][0], e1 = T.e[lane][1], e2 = T.e[lane][2];
+      const int pd = (dn == 0) ? e0 : (dn == 1 ? e1 : e2);
+      if (pd == 1) {
+        int s;
+        if (D == 2) s = mono_index<1>(dn == 0 ? e1 : e0, 0, 0);
+        else if (dn == 0) s = mono_index<2>(e1, e2, 0);
+        else if (dn == 1) s = mono_index<2>(e0, e2, 0);
+        else s = mono_index<2>(e0, e1, 0);
+        fv = fm[s];
+      }
+    }
+    return fv;
+  }
+  eb_normal_moments<D, Q>(g, gp, fi, sm, lane, x0dd);
   if (lane < M) {
     constexpr auto& T = kMono<D, Q>;
     for (int ax = 0; ax < D; ++ax) {
@@ -328,30 +365,280 @@ __device__ __forceinline__ double face_flux(const GridDims& g, const GeomPtrs& g
       }
     }
   }
-  __syncthreads();
+  lds_order();
   return fv;
 }
 
-// Rows, Gram matrix, inverse and the refined semi-normal solve of one face.  Leaves B in
-// shared memory, -G^^-1 (row `lane`) in a[], the column equilibration in sdiag, and W and
-// z of rows lane, lane + 64, ... in wreg[], zreg[]; the adjoint's layout (SM::kFull) also
-// keeps W, z and y in shared memory.  Returns the face status, or kStatusRoute.
-template <int D, int Q, int NPAD, bool NEU, class SM>
+// The wave's row `lane` of m into slot `lane` of Bs, for the lanes below n.
+template <int D, int Q, class SM>
+__device__ __forceinline__ void stage_rows(SM& sm, const double* m, int lane, int n) {
+  constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS;
+  lds_order();
+  if (lane < n) static_for<0, M>([&](auto I) { sm.Bs[lane * MS + I] = m[I]; });
+  lds_order();
+}
+
+// G += the n (a multiple of 8) rows in Bs: tiles on and above the diagonal with
+// v_mfma_f64_16x16x4f64, the trailing rows with v_mfma_f64_4x4x4f64 (four 4 x 4 blocks: the
+// trailing columns against four columns of a tile each, which comes out in the tiles' own
+// layout).
+template <int D, int Q, class SM>
+__device__ __forceinline__ void gram_rows(const SM& sm, int lane, int n, dbl4 (*acc)[Tile<D, Q>::MTF],
+                                          WaveMatrix<D, Q>& W) {
+  constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, MTF = Tile<D, Q>::MTF, MV = Tile<D, Q>::MV;
+  const int r = lane >> 4, c = lane & 15;
+  const double* p = sm.Bs + r * MS;
+  for (int k0 = 0; k0 < n; k0 += 8, p += 8 * MS) {
+    double x[2][MTF], y[2] = {0.0, 0.0};   // two steps of four rows, loaded together
+    static_for<0, 2>([&](auto U) {
+      const double* pu = p + 4 * MS * U;
+      static_for<0, MTF>([&](auto I) {
+        if constexpr (16 * I + 15 < M) x[U][I] = pu[16 * I + c];
+        else x[U][I] = pick(16 * I + c < M, pu[(16 * I + c < M) ? 16 * I + c : 0], 0.0);
+      });
+      if constexpr (MV > 0) y[U] = pick(c % 4 < MV, pu[(c % 4 < MV) ? 16 * MTF + c % 4 : 0], 0.0);
+    });
+    static_for<0, 2>([&](auto U) {
+      static_for<0, MTF>([&](auto I) {
+        static_for<I, MTF>([&](auto J) {
+          acc[I][J] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[U][I], x[U][J], acc[I][J], 0, 0, 0);
+        });
+      });
+      if constexpr (MV > 0) {
+        static_for<0, MTF>([&](auto J) {
+          W.ar[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(y[U], x[U][J], W.ar[J], 0, 0, 0);
+        });
+        W.t = __builtin_amdgcn_mfma_f64_4x4x4f64(y[U], y[U], W.t, 0, 0, 0);
+      }
+    });
+  }
+}
+
+// L D L^T of the leading NP x NP block (2 <= NP <= 4) of a symmetric 4 x 4 matrix (d: the
+// upper triangle, row by row), alike in every lane: the pivots, their reciprocals and the
+// inverse of L below its unit diagonal (m: 10, 20, 21, 30, 31, 32).
+template <int NP>
+__device__ __forceinline__ void block_factor(const double* d, double* pv, double* rd, double* m) {
+  const double a01 = d[1], a02 = d[2], a03 = d[3];
+  pv[0] = d[0];
+  rd[0] = recip_f64(pv[0]);
+  const double l10 = a01 * rd[0], l20 = a02 * rd[0], l30 = a03 * rd[0];
+  pv[1] = fma(-l10, a01, d[4]);
+  rd[1] = recip_f64(pv[1]);
+  m[0] = -l10;
+  if constexpr (NP > 2) {
+    const double a12 = fma(-l10, a02, d[5]), a13 = fma(-l10, a03, d[6]);
+    const double l21 = a12 * rd[1], l31 = a13 * rd[1];
+    pv[2] = fma(-l21, a12, fma(-l20, a02, d[7]));
+    rd[2] = recip_f64(pv[2]);
+    m[1] = fma(l21, l10, -l20);
+    m[2] = -l21;
+    if constexpr (NP > 3) {
+      const double a23 = fma(-l21, a13, fma(-l20, a03, d[8]));
+      const double l32 = a23 * rd[2];
+      pv[3] = fma(-l32, a23, fma(-l31, a13, fma(-l30, a03, d[9])));
+      rd[3] = recip_f64(pv[3]);
+      m[3] = fma(-l32, m[1], fma(l31, l10, -l30));
+      m[4] = fma(l32, l21, -l31);
+      m[5] = -l32;
+    }
+  }
+}
+
+// In-place inverse of the scaled Gram matrix A by symmetric sweeps over blocks of four
+// pivots K (A ends as -A^-1; a row that is no pivot ends as itself times A^-1, so row M, the
+// right-hand side f, ends as A^-1 f).  With A_KK = L D L^T, R = the block's rows, Y = L^-1 R,
+// Z = D^-1 Y and X = L^-T Z:
+//   A_ij -= Y_i^T Z_j  (i, j not in K);  A_Kj = X_j;  A_iK = X_i^T;  A_KK = -A_KK^-1.
+// (Y^T Z is the update of a Cholesky step, as accurate as one pivot at a time; with A_iK and
+// A_KK^-1 A_Kj in its place the error grows by cond(A_KK).)  The rows of a block are one
+// register of their tiles, and that register is, lane for lane, the operand that the matrix
+// instructions want both for rows of B and, the matrix being symmetric, for columns of A:
+// the update is one v_mfma_f64_16x16x4f64 per tile, and Y and X one v_mfma_f64_4x4x4f64 per
+// tile column each, with no exchange between lanes.  Only the 4 x 4 block (which every lane
+// factors) and the trailing rows' entries in columns K go through shared memory: 9 round
+// trips in 3D order 4, where one pivot at a time takes 35, each with loads of the pivot row.
+// Columns K come out of the same update with D^-1 L^-1 taken from Z there, and X then holds
+// I - A_KK^-1 in them.  Returns in `piv` the pivot of component `lane`.
+template <int D, int Q, class SM>
+__device__ __forceinline__ void sweep(SM& sm, int lane, WaveMatrix<D, Q>& W, double& piv) {
+  using TL = Tile<D, Q>;
+  constexpr int M = TL::M, MTF = TL::MTF, MV = TL::MV;
+  const int r = lane >> 4, c = lane & 15, s = c & 3;
+  static_for<0, (M + 3) / 4>([&](auto KB) {
+    constexpr int kb = KB, NP = M - 4 * kb < 4 ? M - 4 * kb : 4;
+    constexpr bool TR = 4 * kb >= 16 * MTF;                   // the trailing block
+    constexpr int Ip = TR ? 0 : kb / 4, q = kb % 4;
+    double R[MTF];
+    static_for<0, MTF>([&](auto J) {
+      if constexpr (TR) R[J] = W.ar[J];
+      else R[J] = W.a[Ip][J][q];
+    });
+    lds_order();
+    if constexpr (TR) sm.buf[lane] = W.t;
+    else sm.buf[lane] = R[Ip];
+    if constexpr (MV > 0 && !TR) sm.pv[4 * c + r] = W.ar[Ip];
+    lds_order();
+    constexpr int off = TR ? 0 : 4 * q;
+    double d[10];
+    static_for<0, 4>([&](auto I) {
+      static_for<I, 4>([&](auto J) { d[4 * I - I * (I - 1) / 2 + (J - I)] = sm.buf[16 * I + off + J]; });
+    });
+    double T = 0.0;                                           // columns of the trailing rows: entry (K_r, s)
+    if constexpr (TR) T = W.t;
+    else if constexpr (MV > 0) T = sm.pv[4 * (4 * q + r) + s];
+    double pv[4], rd[4], m[6];
+    block_factor<NP>(d, pv, rd, m);
+    static_for<0, NP>([&](auto I) { piv = pick(lane == 4 * kb + I, pv[I], piv); });
+    // L^-1 as the two operands: V entry (r, s), U entry (s, r); 1/d_r
+    double V = (r == s && r < NP) ? 1.0 : 0.0, U = V;
+    double rr = pick(r == 1, rd[1], rd[0]);
+    V = pick(r == 1 && s == 0, m[0], V);
+    U = pick(s == 1 && r == 0, m[0], U);
+    if constexpr (NP > 2) {
+      rr = pick(r == 2, rd[2], rr);
+      static_for<0, 2>([&](auto I) {
+        V = pick(r == 2 && s == I, m[1 + I], V);
+        U = pick(s == 2 && r == I, m[1 + I], U);
+      });
+    }
+    if constexpr (NP > 3) {
+      rr = pick(r == 3, rd[3], rr);
+      static_for<0, 3>([&](auto I) {
+        V = pick(r == 3 && s == I, m[3 + I], V);
+        U = pick(s == 3 && r == I, m[3 + I], U);
+      });
+    }
+    // Y, -Z (with columns K put in place) and -X
+    const bool inK = (TR || c / 4 == q) && (NP == 4 || s < NP);
+    const double zK = inK ? V * rr : 0.0, xK = (inK && r == s) ? 1.0 : 0.0;
+    double Y[MTF], Z[MTF], X[MTF], YT = 0.0, ZT = 0.0, XT = 0.0;
+    static_for<0, MTF>([&](auto J) {
+      Y[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(U, R[J], 0.0, 0, 0, 0);
+      Z[J] = -Y[J] * rr;
+      if constexpr (!TR && J == Ip) Z[J] += zK;
+      X[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(V, Z[J], 0.0, 0, 0, 0);
+      if constexpr (!TR && J == Ip) X[J] += xK;
+    });
+    if constexpr (MV > 0) {
+      YT = __builtin_amdgcn_mfma_f64_4x4x4f64(U, T, 0.0, 0, 0, 0);
+      ZT = -YT * rr;
+      if constexpr (TR) {
+        ZT += zK;
+        XT = __builtin_amdgcn_mfma_f64_4x4x4f64(V, ZT, 0.0, 0, 0, 0) + xK;
+      }
+    }
+    static_for<0, MTF>([&](auto I) {
+      static_for<0, MTF>([&](auto J) {
+        dbl4 t = {W.a[I][J][0], W.a[I][J][1], W.a[I][J][2], W.a[I][J][3]};
+        t = __builtin_amdgcn_mfma_f64_16x16x4f64(Y[I], Z[J], t, 0, 0, 0);
+        static_for<0, 4>([&](auto QQ) { W.a[I][J][QQ] = t[(int)QQ]; });
+      });
+    });
+    if constexpr (MV > 0) {
+      static_for<0, MTF>([&](auto J) {
+        W.ar[J] = __builtin_amdgcn_mfma_f64_4x4x4f64(YT, Z[J], W.ar[J], 0, 0, 0);
+      });
+      W.t = __builtin_amdgcn_mfma_f64_4x4x4f64(YT, ZT, W.t, 0, 0, 0);
+    }
+    // rows K
+    const bool rowK = NP == 4 || r < NP;
+    static_for<0, MTF>([&](auto J) {
+      if constexpr (TR) W.ar[J] = pick(rowK, -X[J], W.ar[J]);
+      else W.a[Ip][J][q] = pick(rowK, -X[J], W.a[Ip][J][q]);
+    });
+    if constexpr (TR) W.t = pick(rowK, -XT, W.t);
+  });
+}
+
+// dy = E (-W) x, the scaled inverse times x (component `lane` in lane `lane`, 0 from M on; x
+// already carries its factor E), into sm.dy.
+template <int D, int Q, class SM>
+__device__ __forceinline__ void apply_inverse(SM& sm, int lane, const WaveMatrix<D, Q>& W, double x) {
+  using TL = Tile<D, Q>;
+  constexpr int M = TL::M, MTF = TL::MTF, MV = TL::MV, PI = TL::PI;
+  const int r = lane >> 4, c = lane & 15;
+  lds_order();
+  if (lane < 16 * MTF + (MV > 0 ? 4 : 0)) sm.vec[vec_slot<D, Q>(lane)] = x;
+  lds_order();
+  double xr = 0.0;
+  if constexpr (MV > 0) xr = sm.vec[16 * MTF + r];
+  double xi[MTF][4];
+  static_for<0, MTF>([&](auto I) { static_for<0, 4>([&](auto QQ) { xi[I][QQ] = sm.vec[PI * r + 4 * I + QQ]; }); });
+  double y[MTF];
+  static_for<0, MTF>([&](auto J) {
+    double s0 = W.ar[J] * xr, s1 = 0.0;
+    if constexpr (MV == 0) s0 = 0.0;
+    static_for<0, MTF>([&](auto I) {
+      static_for<0, 4>([&](auto QQ) {
+        if constexpr (QQ % 2 == 0) s0 = fma(W.a[I][J][QQ], xi[I][QQ], s0);
+        else s1 = fma(W.a[I][J][QQ], xi[I][QQ], s1);
+      });
+    });
+    y[J] = sum_lane_rows(s0 + s1);
+  });
+  double yt = 0.0;
+  if constexpr (MV > 0) {
+    yt = (c < MV) ? W.t * sm.vec[16 * MTF + c % 4] : 0.0;
+    static_for<0, MTF>([&](auto J) { yt = fma(W.ar[J], sm.vec[PI * (c % 4) + c / 4 + 4 * J], yt); });
+    yt = sum_in_lane_row(yt);
+  }
+  lds_order();
+  if (r == 0) static_for<0, MTF>([&](auto J) { if (16 * J + c < M) sm.dy[16 * J + c] = -(y[J] * W.sj[J]); });
+  if constexpr (MV > 0)
+    if (c == 0 && r < MV) sm.dy[16 * MTF + r] = -(yt * W.sr);
+  lds_order();
+}
+
+// sum of Bs[i][lane] z[i] over rows [i0, i1) of Bs (multiples of 8), z at zs[i + zoff]: two
+// sums in turn
+template <int D, int Q, class SM>
+__device__ __forceinline__ void column_sum(const SM& sm, int lane, int i0, int i1, int zoff, double& p0, double& p1) {
+  constexpr int MS = Dims<D, Q>::MS;
+  for (int i = i0; i < i1; i += 8) {
+    static_for<0, 8>([&](auto U) {
+      const double b = sm.Bs[(i + U) * MS + lane], z = sm.zs[i + zoff + U];
+      if constexpr (U % 2 == 0) p0 = fma(-b, z, p0);
+      else p1 = fma(-b, z, p1);
+    });
+  }
+}
+
+// the same compensated, the low part of z in the compensation
+template <int D, int Q, class SM>
+__device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int i0, int i1, int zoff, Dot2& d0, Dot2& d1,
+                                                double& lo) {
+  constexpr int MS = Dims<D, Q>::MS;
+  for (int i = i0; i < i1; i += 2) {
+    const double b0 = -sm.Bs[i * MS + lane], b1 = -sm.Bs[(i + 1) * MS + lane];
+    dot2_add(d0, b0, sm.zs[i + zoff]);
+    dot2_add(d1, b1, sm.zs[i + zoff + 1]);
+    lo = fma(b0, sm.zl[i + zoff], lo);
+    lo = fma(b1, sm.zl[i + zoff + 1], lo);
+  }
+}
+
+// Rows, Gram matrix, inverse and the refined semi-normal solve of one face with at most
+// 64 NR rows.  Leaves the rows lane, lane + 64 of B in b[][] (and the first 64 in Bs), the
+// inverse in W, weights and z of the lane's rows in wreg[], zreg[], and component `lane` of
+// y in y.  Returns the face status, or kStatusRoute.
+template <int D, int Q, int NR, bool NEU, class SM>
 __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& gp, const FaceInfo& fi,
                                             const int32_t* __restrict__ vol_cell, const int32_t* __restrict__ box_lf,
-                                            const int32_t* __restrict__ col, SM& sm, int lane, double* a,
-                                            double& sdiag, double* wreg, double* zreg, double wpow,
-                                            bool* rank_low = nullptr) {
+                                            const int32_t* __restrict__ col, SM& sm, int lane, WaveMatrix<D, Q>& W,
+                                            double (*b)[Dims<D, Q>::M], double* wreg, double* zreg, double& y,
+                                            double wpow, bool* rank_low = nullptr) {
   using DM = Dims<D, Q>;
-  constexpr int M = DM::M, MS = DM::MS;
-  static_assert(M < NPAD, "the sweep's pivot buffer (zs) needs a slot past M");
-  double* Bs = sm.Bs;
+  using TL = Tile<D, Q>;
+  constexpr int M = DM::M, MTF = TL::MTF, MV = TL::MV, PI = TL::PI;
   const int N = fi.N;
+  // rows in Bs (n0) and past 64 (n1), in eights (the rows past N are zero)
+  const int n0 = (NR > 1 && N > 64) ? 64 : ((N + 7) & ~7);
+  const int n1 = (NR > 1 && N > 64) ? ((N - 64 + 7) & ~7) : 0;
 
   // ---- rows of B ----------------------------------------------------------------------
-  // Lane r builds rows r, r + 64, ...: every row's index chain (col -> cell -> moments) is
+  // Lane r builds rows r and r + 64: every row's index chain (col -> cell -> moments) is
   // issued before the first row is finished, so the dependent loads of all rows overlap.
-  constexpr int NR = (NPAD + 63) / 64;
   bool finite = true;
   dd x0dd[3];
   face_x0_dd<D, Q>(g, gp, fi, x0dd);
@@ -363,171 +650,163 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
   });
   static_for<0, NR>([&](auto R) {
     const int r = lane + 64 * R;
-    wreg[R] = 0.0;
-    if (r < NPAD) {
-      double m[M];
-      double wr = 0.0;
-      if (r < N) {
-        const bool neu_row = NEU && rsrc[R].eb >= 0;
-        const double m0 = neu_row ? gp.eb_mom[(long long)rsrc[R].eb * M] : rsrc[R].src[0];
-        if (!(m0 >= kSmallCell)) {   // a small cell (or a non-finite moment): double-double
-          dd md[M];
-          finite = dd_row<D, Q, NEU>(gp, rsrc[R], x0dd, wpow, md, wr) && finite;
-          static_for<0, M>([&](auto I) { m[I] = md[I].hi; });
-        } else if (neu_row) {
-          finite = neumann_row<D, Q>(gp, rsrc[R].eb, rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
-        } else {
-          load_row_moments<D, Q>(rsrc[R], m);
-          finite = finish_row<D, Q>(rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
-        }
+    double wr = 0.0;
+    double* m = b[R];
+    if (r < N) {
+      const bool neu_row = NEU && rsrc[R].eb >= 0;
+      const double m0 = neu_row ? gp.eb_mom[(long long)rsrc[R].eb * M] : rsrc[R].src[0];
+      if (!(m0 >= kSmallCell)) {   // a small cell (or a non-finite moment): double-double
+        dd md[M];
+        finite = dd_row<D, Q, NEU>(gp, rsrc[R], x0dd, wpow, md, wr) && finite;
+        static_for<0, M>([&](auto I) { m[I] = md[I].hi; });
+      } else if (neu_row) {
+        finite = neumann_row<D, Q>(gp, rsrc[R].eb, rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
       } else {
-        static_for<0, M>([&](auto I) { m[I] = 0.0; });
+        load_row_moments<D, Q>(rsrc[R], m);
+        finite = finish_row<D, Q>(rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
       }
-      static_for<0, M>([&](auto I) { Bs[r * MS + I] = m[I]; });
-      wreg[R] = wr;
-      if constexpr (SM::kFull) sm.wls[r] = wr;
+    } else {
+      static_for<0, M>([&](auto I) { m[I] = 0.0; });
     }
+    wreg[R] = wr;
+    if constexpr (R == 0) stage_rows<D, Q>(sm, b[0], lane, FaceSmem<D, Q>::S);
   });
-  const double fv = face_flux<D, Q>(g, gp, fi, sm, lane, x0dd);   // barrier: B complete
+  const double fv = face_flux<D, Q>(g, gp, fi, sm, lane, x0dd);
   const bool allfinite = __all(finite) && __all(isfinite(fv));
 
-  // ---- G = B^T B: full 16-column tiles on the matrix cores --------------------------------
-  // (v_mfma_f64_16x16x4f64, rows of B as the contraction index; every tile, the lower
-  // ones too, so each lane can fetch its row below).  A narrow trailing block (at most 4
-  // columns, e.g. 3 of M = 35) is done on the vector ALUs instead: as a 16-wide tile it
-  // would be mostly padding, and FP64 MFMA has no more throughput than FP64 FMA on this
-  // chip.
-  constexpr int MTF = GramSplit<D, Q>::MTF, MV = GramSplit<D, Q>::MV;
-  dbl4 acc[MTF][MTF];
-#pragma unroll
-  for (int i = 0; i < MTF; ++i)
-#pragma unroll
-    for (int j = 0; j < MTF; ++j) acc[i][j] = dbl4{0, 0, 0, 0};
-  const int lr = lane >> 4, lc = lane & 15;
-#pragma unroll
-  for (int k0 = 0; k0 < NPAD; k0 += 4) {
-    double x[MTF];
-#pragma unroll
-    for (int i = 0; i < MTF; ++i) {
-      const int cidx = 16 * i + lc;
-      x[i] = (cidx < M) ? Bs[(k0 + lr) * MS + cidx] : 0.0;
-    }
-#pragma unroll
-    for (int i = 0; i < MTF; ++i)
-#pragma unroll
-      for (int j = 0; j < MTF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], x[j], acc[i][j], 0, 0, 0);
-  }
-  double gt[MV > 0 ? MV : 1];   // lane l: G[l][16 MTF + c] for the trailing columns c
-  if constexpr (MV > 0) {
-    static_for<0, MV>([&](auto C) { gt[C] = 0.0; });
-    if (lane < M) {
-      double g0[MV], g1[MV];
-      static_for<0, MV>([&](auto C) { g0[C] = 0.0; g1[C] = 0.0; });
-      for (int k = 0; k < NPAD; k += 2) {
-        const double b0 = Bs[k * MS + lane], b1 = Bs[(k + 1) * MS + lane];
-        static_for<0, MV>([&](auto C) {
-          g0[C] = fma(b0, Bs[k * MS + 16 * MTF + C], g0[C]);
-          g1[C] = fma(b1, Bs[(k + 1) * MS + 16 * MTF + C], g1[C]);
-        });
-      }
-      static_for<0, MV>([&](auto C) { gt[C] = g0[C] + g1[C]; });
-    }
-  }
-  // Row `lane` of G into a[].  Tile (i, j) register q of lane 16 r' + c' holds
-  // G[16i + r' + 4q][16j + c'] (the output layout of v_mfma_f64_16x16x4f64), so lane l
-  // reading lane 16 r' + l % 16 gets G[16i + r' + 4q][l] = G[l][16i + r' + 4q] from tile
-  // (i, l / 16): a fixed register for every lane, as ds_bpermute needs.
-  const int band = lane >> 4;
-  static_for<0, MTF>([&](auto I) {
-    static_for<0, 4>([&](auto RR) {
-      static_for<0, 4>([&](auto QQ) {
-        constexpr int c = 16 * I + RR + 4 * QQ;
-        if constexpr (c < M) {
-          const int src = 16 * RR + lc;
-          double v = bpermute_f64(acc[I][0][(int)QQ], src);
-          static_for<1, MTF>([&](auto J) {
-            const double vj = bpermute_f64(acc[I][J][(int)QQ], src);
-            v = (band == J) ? vj : v;
-          });
-          a[c] = v;
-        }
-      });
+  // ---- G = B^T B --------------------------------------------------------------------------
+  const int r = lane >> 4, c = lane & 15;
+  {
+    dbl4 acc[MTF][MTF];
+    static_for<0, MTF>([&](auto I) {
+      static_for<0, MTF>([&](auto J) { acc[I][J] = dbl4{0, 0, 0, 0}; });
+      W.ar[I] = 0.0;
     });
-  });
-  if constexpr (MV > 0) {
-    static_for<0, MV>([&](auto C) { a[16 * MTF + C] = gt[C]; });
-    // rows beyond the tiles: G[l][c] = G[c][l], entry l - 16 MTF of gt in lane c
-    if (lane < M) static_for<0, MV>([&](auto C) { sm.tt[lane * MV + C] = gt[C]; });
-    __syncthreads();
-    if (lane >= 16 * MTF && lane < M) {
-      const int cc = lane - 16 * MTF;
-      static_for<0, 16 * MTF>([&](auto C) { a[C] = sm.tt[C * MV + cc]; });
+    W.t = 0.0;
+    gram_rows<D, Q>(sm, lane, n0, acc, W);
+    if constexpr (NR > 1) {
+      // the first row comes back from shared memory, so that it takes no registers while
+      // the second one is built (which needs all of them in double-double)
+      static_for<0, M>([&](auto I) { b[0][I] = sm.Bs[lane * DM::MS + I]; });
+      if (n1 > 0) {
+        stage_rows<D, Q>(sm, b[1], lane, n1);
+        gram_rows<D, Q>(sm, lane, n1, acc, W);
+      }
     }
-    __syncthreads();
+    static_for<0, MTF>([&](auto I) {
+      static_for<I, MTF>([&](auto J) { static_for<0, 4>([&](auto QQ) { W.a[I][J][QQ] = acc[I][J][(int)QQ]; }); });
+    });
+    // the tile below the diagonal is the transpose of the one above (skewed slots: no bank
+    // conflicts); as another tile of the matrix instructions it would cost ten times as much
+    if constexpr (MTF == 2) {
+      lds_order();
+      static_for<0, 4>([&](auto QQ) { sm.tr[16 * (r + 4 * QQ) + ((c + r + 4 * QQ) & 15)] = W.a[0][1][QQ]; });
+      lds_order();
+      static_for<0, 4>([&](auto QQ) { W.a[1][0][QQ] = sm.tr[16 * c + ((r + 4 * QQ + c) & 15)]; });
+      lds_order();
+    }
   }
 
-  // ---- equilibrate to unit diagonal and invert: lane i holds row i ----------------------------
-  // Symmetric Gauss-Jordan sweeps over the pivots k = 0..M-1 turn G^ into -G^-1 in place;
-  // the pivot of step k is the k-th Schur complement pivot (L_kk^2 of the Cholesky factor),
-  // which gives the rank and routing tests.  Values that every lane needs from one lane
-  // (the pivot rows, E, the right-hand sides) go through a shared-memory slot per lane and
-  // come back as broadcast loads, in place of v_readlane through scalar registers.
+  // ---- equilibrate to unit diagonal ---------------------------------------------------------
+  // E = 1/sqrt(diag G); the diagonal goes through shared memory to component order and E
+  // back to the rows and columns
   const bool act = lane < M;
-  double* piv = sm.zs;   // free between the flux vector and the refinement
-  const int pslot = lane < M ? lane : M;   // lanes past M write an unused slot (M < NPAD)
-  double gdiag = 1.0;
-  static_for<0, M>([&](auto C) { gdiag = (lane == C) ? a[C] : gdiag; });
-  sdiag = act ? 1.0 / sqrt(gdiag) : 1.0;
-  piv[pslot] = sdiag;
-  static_for<0, M>([&](auto J) { a[J] = act ? a[J] * sdiag * piv[J] : 0.0; });
-  double gnorm = 0.0;   // ||G^||_inf: largest absolute row sum of the equilibrated Gram matrix
-  static_for<0, M>([&](auto J) { gnorm += fabs(a[J]); });
-  double pmax = 0.0, pmin = 1e300;   // extreme pivots L_kk^2 (the tests square their bounds)
-  // Step k:  a_ij -= (a_ik / d) a_kj  (i, j != k);  a_ik /= d;  a_kj /= d;  a_kk = -1/d.
-  // Each lane scales its multiplier once (u = a_ik / d; on lane k, 1 - 1/d turns the
-  // pivot row into a_kj / d), so every entry is one FMA.  The sweep keeps the matrix
-  // symmetric (up to rounding), so the pivot row is the pivot column: every lane stores
-  // its entry of column k in shared memory (one store) and all lanes read the row back
-  // with broadcast loads, eight entries at a time before their FMAs.
-  static_for<0, M>([&](auto K) {
-    constexpr int k = K;
-    piv[pslot] = a[k];
-    const double d = piv[k];
-    const double dp = d > 0.0 ? d : 0.0;
-    pmax = fmax(pmax, dp);
-    pmin = fmin(pmin, dp);
-    const double rd = recip_f64(d);
-    const double u = (lane == k) ? 1.0 - rd : a[k] * rd;
-    static_for<0, (M + 7) / 8>([&](auto G) {
-      double pr[8];
-      static_for<0, 8>([&](auto I) {
-        constexpr int j = 8 * G + I;
-        if constexpr (j < M && j != k) pr[I] = piv[j];
+  {
+    static_for<0, MTF>([&](auto J) {
+      double dg = W.a[J][J][0];
+      static_for<1, 4>([&](auto QQ) { dg = pick(c / 4 == QQ, W.a[J][J][QQ], dg); });
+      if (r == c % 4) sm.dy[16 * J + c] = dg;
+    });
+    if constexpr (MV > 0)
+      if (r == c) sm.dy[16 * MTF + c] = W.t;
+    lds_order();
+    W.sd = act ? 1.0 / sqrt(sm.dy[lane < 40 ? lane : 0]) : 1.0;
+    lds_order();
+    if (lane < 16 * MTF + (MV > 0 ? 4 : 0)) sm.vec[vec_slot<D, Q>(lane)] = W.sd;
+    if (lane < 40) sm.dy[lane] = act ? fv * W.sd : 0.0;      // the scaled right-hand side
+    lds_order();
+    double si[MTF][4];
+    static_for<0, MTF>([&](auto I) {
+      static_for<0, 4>([&](auto QQ) { si[I][QQ] = sm.vec[PI * r + 4 * I + QQ]; });
+      W.sj[I] = sm.vec[PI * (c % 4) + c / 4 + 4 * I];
+    });
+    W.st = W.sr = 0.0;
+    if constexpr (MV > 0) {
+      W.sr = sm.vec[16 * MTF + r];
+      W.st = sm.vec[16 * MTF + c % 4];
+    }
+    static_for<0, MTF>([&](auto J) {
+      static_for<0, MTF>([&](auto I) {
+        static_for<0, 4>([&](auto QQ) { W.a[I][J][QQ] *= si[I][QQ] * W.sj[J]; });
       });
-      static_for<0, 8>([&](auto I) {
-        constexpr int j = 8 * G + I;
-        if constexpr (j < M && j != k) a[j] = fma(-u, pr[I], a[j]);
+      W.ar[J] *= W.sr * W.sj[J];
+    });
+    W.t *= W.sr * W.st;
+  }
+  // ||G^||_inf: the largest absolute column sum of the equilibrated Gram matrix
+  double gnorm = 0.0;
+  static_for<0, MTF>([&](auto J) {
+    double s = (MV > 0) ? fabs(W.ar[J]) : 0.0;
+    static_for<0, MTF>([&](auto I) { static_for<0, 4>([&](auto QQ) { s += fabs(W.a[I][J][QQ]); }); });
+    gnorm = fmax(gnorm, sum_lane_rows(s));
+  });
+  if constexpr (MV > 0) {
+    double s = (c < MV) ? fabs(W.t) : 0.0;
+    static_for<0, MTF>([&](auto J) { s += fabs(W.ar[J]); });
+    gnorm = fmax(gnorm, sum_in_lane_row(s));
+  }
+  // the right-hand side E F~ as row and column M
+  if constexpr (MV > 0) {
+    static_for<0, MTF>([&](auto J) { W.ar[J] = pick(r == MV, sm.dy[16 * J + c], W.ar[J]); });
+    W.t = pick(r == MV, sm.dy[16 * MTF + c % 4], pick(c % 4 == MV, sm.dy[16 * MTF + r], W.t));
+  } else {
+    constexpr int rM = M % 4, qM = M / 4;
+    W.a[0][0][qM] = pick(r == rM, sm.dy[c], W.a[0][0][qM]);
+    static_for<0, 4>([&](auto QQ) { W.a[0][0][QQ] = pick(c == M, sm.dy[r + 4 * QQ], W.a[0][0][QQ]); });
+  }
+
+  // ---- invert; the pivots are the Cholesky pivots L_kk^2 -----------------------------------
+  double piv = 0.0;
+  sweep<D, Q>(sm, lane, W, piv);
+  const double pd = piv > 0.0 ? piv : 0.0;       // (the tests square their bounds)
+  const double pmax = wave_max_f64(act ? pd : 0.0);
+  const double pmin = -wave_max_f64(act ? -pd : -1e300);
+  const bool pivots_ok = (pmin > kRouteTol * kRouteTol * pmax) && (pmax > 0.0);
+  double inv2 = 0.0;    // ||G^^-1||_F^2, from the entries of the inverse
+  static_for<0, MTF>([&](auto J) {
+    static_for<0, MTF>([&](auto I) {
+      static_for<0, 4>([&](auto QQ) {
+        const double v = pick(MV > 0 || (c < M && r + 4 * QQ < M), W.a[I][J][QQ], 0.0);
+        inv2 = fma(v, v, inv2);
       });
     });
-    a[k] = (lane == k) ? -rd : u;
   });
-  const bool pivots_ok = (pmin > kRouteTol * kRouteTol * pmax) && (pmax > 0.0);
-  double inv2 = 0.0;    // ||G^^-1||_F^2, from the rows of the inverse
-  static_for<0, M>([&](auto J) { inv2 = fma(a[J], a[J], inv2); });
-  for (int o = 32; o > 0; o >>= 1) {
-    gnorm = fmax(gnorm, __shfl_xor(gnorm, o));
-    inv2 += __shfl_xor(inv2, o);
+  if constexpr (MV > 0) {
+    double s = 0.0;   // the trailing rows, and the columns they stand for
+    static_for<0, MTF>([&](auto J) { s = fma(W.ar[J], W.ar[J], s); });
+    if (r < MV) inv2 = fma(2.0, s, inv2);
+    if (r < MV && c < MV) inv2 = fma(W.t, W.t, inv2);
   }
+  gnorm = wave_max_f64(gnorm);
+  inv2 = sum_lane_rows(sum_in_lane_row(inv2));
   const double cbound = gnorm * sqrt(inv2);   // wave-uniform
   const bool cond_ok = cbound <= kCondRoute * kCondRoute;
   const bool dot2 = !(cbound <= kDot2Cond);
 
   // ---- semi-normal solve with one refinement step (compensated past kDot2Cond) ---------
-  // y = G^-1 rhs with G^ = E G E (E = diag(sdiag)):  y = E (-a) (E rhs).  Lane p holds
-  // component p of F~, rhs and y; lane r holds z of its rows r, r + 64 (past kDot2Cond
-  // as zreg + zlo).
-  double rhs = fv * sdiag;
-  double ysum = 0.0;
+  // y = G^-1 F~, with G^ = E G E: the first y is row M times E.  Lane r holds z of its rows
+  // r, r + 64 (past kDot2Cond as zreg + zlo).
+  lds_order();
+  if constexpr (MV > 0) {
+    if (r == MV) {
+      static_for<0, MTF>([&](auto J) { sm.dy[16 * J + c] = W.ar[J] * W.sj[J]; });
+      if (c < MV) sm.dy[16 * MTF + c] = W.t * W.st;
+    }
+  } else {
+    if (r == M % 4 && c < M) sm.dy[c] = W.a[0][0][M / 4] * W.sj[0];
+  }
+  lds_order();
+  y = 0.0;
   double dlast = 0.0;   // largest change of W z in the refinement step
   double zlo[NR];
   static_for<0, NR>([&](auto R) {
@@ -535,90 +814,80 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
     zlo[R] = 0.0;
   });
   for (int it = 0; it <= kRefine; ++it) {
-    double tq[4] = {0.0, 0.0, 0.0, 0.0};
-    piv[pslot] = rhs;
-    static_for<0, M>([&](auto J) { tq[J % 4] = fma(-a[J], piv[J], tq[J % 4]); });
-    const double t = (tq[0] + tq[1]) + (tq[2] + tq[3]);
-    const double dy = act ? t * sdiag : 0.0;
-    ysum += dy;
-    piv[pslot] = dy;
+    if (act) y += sm.dy[lane];
     // z += B dy
-    static_for<0, NR>([&](auto R) {
-      const int r = lane + 64 * R;
-      if (r < NPAD) {
-        double inc;
-        if (dot2) {
-          Dot2 d0{0.0, 0.0}, d1{0.0, 0.0};
-          static_for<0, M>([&](auto J) {
-            if constexpr (J % 2 == 0) dot2_add(d0, Bs[r * MS + J], piv[J]);
-            else dot2_add(d1, Bs[r * MS + J], piv[J]);
-          });
-          const Dot2 d = dot2_join(d0, d1);
-          dd zs2 = dd_add(dd{zreg[R], zlo[R]}, dd{d.s, d.c});
-          zreg[R] = zs2.hi;
-          zlo[R] = zs2.lo;
-          inc = d.s + d.c;
-        } else {
-          double sq4[4] = {0.0, 0.0, 0.0, 0.0};
-          static_for<0, M>([&](auto J) { sq4[J % 4] = fma(Bs[r * MS + J], piv[J], sq4[J % 4]); });
-          inc = (sq4[0] + sq4[1]) + (sq4[2] + sq4[3]);
-          zreg[R] += inc;
-        }
-        if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * inc));
-      }
-    });
+    if (dot2) {
+      static_for<0, NR>([&](auto R) {
+        Dot2 d0{0.0, 0.0}, d1{0.0, 0.0};
+        static_for<0, M>([&](auto J) {
+          if constexpr (J % 2 == 0) dot2_add(d0, b[R][J], sm.dy[J]);
+          else dot2_add(d1, b[R][J], sm.dy[J]);
+        });
+        const Dot2 d = dot2_join(d0, d1);
+        const dd zs2 = dd_add(dd{zreg[R], zlo[R]}, dd{d.s, d.c});
+        zreg[R] = zs2.hi;
+        zlo[R] = zs2.lo;
+        if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * (d.s + d.c)));
+      });
+    } else {
+      double inc[NR][2];
+      static_for<0, NR>([&](auto R) { inc[R][0] = inc[R][1] = 0.0; });
+      static_for<0, M>([&](auto J) {
+        const double v = sm.dy[J];
+        static_for<0, NR>([&](auto R) { inc[R][J % 2] = fma(b[R][J], v, inc[R][J % 2]); });
+      });
+      static_for<0, NR>([&](auto R) {
+        const double s = inc[R][0] + inc[R][1];
+        zreg[R] += s;
+        if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * s));
+      });
+    }
     if (it == kRefine) break;
     // residual of B^T z = F~ (two interleaved sums, compensated past kDot2Cond, where the
-    // low part of z enters the compensation); z goes through LDS, B^T is read by columns
+    // low part of z enters the compensation); z goes through shared memory, B^T is read by
+    // columns: first the rows in place, then, if rows past 64 stand in the first slots, the
+    // rows that belong there
+    lds_order();
     static_for<0, NR>([&](auto R) {
-      const int r = lane + 64 * R;
-      if (r < NPAD) {
-        sm.zs[r] = zreg[R];
-        sm.zl[r] = zlo[R];
-      }
+      sm.zs[lane + 64 * R] = zreg[R];
+      if (dot2) sm.zl[lane + 64 * R] = zlo[R];
     });
-    __syncthreads();
+    lds_order();
     double res = 0.0;
-    if (act && dot2) {
+    const int cl = act ? lane : 0;
+    if (dot2) {
       Dot2 d0{fv, 0.0}, d1{0.0, 0.0};
       double lo = 0.0;
-#pragma unroll 4
-      for (int r = 0; r < NPAD; r += 2) {
-        dot2_add(d0, -Bs[(r + 0) * MS + lane], sm.zs[r + 0]);
-        dot2_add(d1, -Bs[(r + 1) * MS + lane], sm.zs[r + 1]);
-        lo = fma(-Bs[(r + 0) * MS + lane], sm.zl[r + 0], lo);
-        lo = fma(-Bs[(r + 1) * MS + lane], sm.zl[r + 1], lo);
+      column_sum_dot2<D, Q>(sm, cl, n1, n0, 0, d0, d1, lo);
+      if constexpr (NR > 1) {
+        if (n1 > 0) {
+          column_sum_dot2<D, Q>(sm, cl, 0, n1, 64, d0, d1, lo);
+          stage_rows<D, Q>(sm, b[0], lane, n1);
+          column_sum_dot2<D, Q>(sm, cl, 0, n1, 0, d0, d1, lo);
+        }
       }
       d1.c += lo;
       res = dot2_merge(d0, d1);
-    } else if (act) {
+    } else {
       double p0 = fv, p1 = 0.0;
-#pragma unroll 4
-      for (int r = 0; r < NPAD; r += 2) {
-        p0 = fma(-Bs[(r + 0) * MS + lane], sm.zs[r + 0], p0);
-        p1 = fma(-Bs[(r + 1) * MS + lane], sm.zs[r + 1], p1);
+      column_sum<D, Q>(sm, cl, n1, n0, 0, p0, p1);
+      if constexpr (NR > 1) {
+        if (n1 > 0) {
+          column_sum<D, Q>(sm, cl, 0, n1, 64, p0, p1);
+          stage_rows<D, Q>(sm, b[0], lane, n1);
+          column_sum<D, Q>(sm, cl, 0, n1, 0, p0, p1);
+        }
       }
       res = p0 + p1;
     }
-    rhs = res * sdiag;
-    __syncthreads();
+    apply_inverse<D, Q>(sm, lane, W, act ? res * W.sd : 0.0);
   }
   if (dot2) static_for<0, NR>([&](auto R) { zreg[R] += zlo[R]; });
-  if constexpr (SM::kFull) {
-    static_for<0, NR>([&](auto R) {
-      const int r = lane + 64 * R;
-      if (r < NPAD) sm.zs[r] = zreg[R];
-    });
-    if (act) sm.ys[lane] = ysum;
-    __syncthreads();
-  }
   // has the refinement settled?  The step's change of the stencil W z against its size
   double smax = 0.0;
   static_for<0, NR>([&](auto R) { smax = fmax(smax, fabs(wreg[R] * zreg[R])); });
-  for (int o = 32; o > 0; o >>= 1) {
-    dlast = fmax(dlast, __shfl_xor(dlast, o));
-    smax = fmax(smax, __shfl_xor(smax, o));
-  }
+  dlast = wave_max_f64(dlast);
+  smax = wave_max_f64(smax);
   const bool settled = dlast <= kSettleTol * smax;
   if (rank_low) *rank_low = !((pmin > kRankTol * kRankTol * pmax) && (pmax > 0.0));
   if (!allfinite) return CUTCELL_STATUS_NONFINITE;
@@ -674,36 +943,36 @@ struct FaceWalk {
 
 __device__ __forceinline__ FaceInfo face_info(const StencilArgs& A, long long t) {
   FaceInfo fi;
-  fi.F = A.perm[t];
-  const int32_t code = A.fcode[fi.F];
+  fi.F = __builtin_amdgcn_readfirstlane(A.perm[t]);
+  const int32_t code = __builtin_amdgcn_readfirstlane(A.fcode[fi.F]);
   fi.gi = code >> 4;
   fi.kind = (code >> 2) & 3;
   fi.dn = code & 3;
-  fi.ref = A.fref[fi.F];
+  fi.ref = __builtin_amdgcn_readfirstlane(A.fref[fi.F]);
   fi.n_vol = A.counts[4 * fi.gi + 0];
   fi.n_eb = A.counts[4 * fi.gi + 1];
   fi.phi0 = A.offs[fi.gi];
   fi.rp = A.row_ptr[fi.F];
-  fi.N = (int)(A.row_ptr[fi.F + 1] - fi.rp);
+  fi.N = __builtin_amdgcn_readfirstlane((int)(A.row_ptr[fi.F + 1] - fi.rp));
   return fi;
 }
 
 // One face per workgroup (WALK = false: face t of the bin, t from the XCD mapping), or a
 // persistent workgroup that walks its chunk (WALK = true).  Two instances because the
 // loop costs the single-face kernel registers.
-template <int D, int Q, int NPAD, bool NEU>
-__device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, LeanSmem<D, Q, NPAD>& sm, int lane,
+template <int D, int Q, int NR, bool NEU>
+__device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, FaceSmem<D, Q>& sm, int lane,
                                              double* __restrict__ val, int8_t* __restrict__ status, int32_t* flagged) {
-  constexpr int M = Dims<D, Q>::M, NR = (NPAD + 63) / 64;
+  constexpr int M = Dims<D, Q>::M;
   FaceInfo fi = face_info(A, t);
   const GeomPtrs gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
-  double a[M], wreg[NR], zreg[NR];
-  double sdiag;
+  WaveMatrix<D, Q> W;
+  double b[NR][M], wreg[NR], zreg[NR], y;
   bool rank_low = false;
-  int st = face_forward<D, Q, NPAD, NEU>(A.g, gp, fi, A.vol_cell_ws + (long long)fi.gi * A.g.ncell,
-                                         A.box_lf_ws + (long long)fi.gi * A.g.nboxslot, A.col, sm, lane, a, sdiag,
-                                         wreg, zreg, A.wpow, &rank_low);
+  int st = face_forward<D, Q, NR, NEU>(A.g, gp, fi, A.vol_cell_ws + (long long)fi.gi * A.g.ncell,
+                                       A.box_lf_ws + (long long)fi.gi * A.g.nboxslot, A.col, sm, lane, W, b, wreg,
+                                       zreg, y, A.wpow, &rank_low);
   if (st == kStatusRoute) {
     if (A.route) {   // the QR path writes this face's values and status
       if (lane == 0) A.qr_list[atomicAdd(A.qr_count, 1)] = fi.F;
@@ -728,19 +997,23 @@ __device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, 
   }
 }
 
-// (two waves per SIMD: the register budget of 256 includes the matrix-core accumulators)
-template <int D, int Q, int NPAD, bool WALK, bool NEU = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_stencil(StencilArgs A, double* __restrict__ val, int8_t* __restrict__ status,
-                                               int32_t* flagged) {
-  __shared__ LeanSmem<D, Q, NPAD> sm;
+// Waves per SIMD that the kernels are built for: two where the rows of B fill the
+// registers (3D order 4), four otherwise (shared memory allows no more).
+template <int D, int Q>
+constexpr int kWaves = Dims<D, Q>::M > 16 ? 2 : 4;
+
+template <int D, int Q, int NR, bool WALK, bool NEU = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>))) void k_stencil(
+    StencilArgs A, double* __restrict__ val, int8_t* __restrict__ status, int32_t* flagged) {
+  __shared__ __align__(16) FaceSmem<D, Q> sm;
   const int lane = threadIdx.x;
   FaceWalk walk(A);
   if constexpr (!WALK) {
     const long long t = walk.next();
-    if (t >= 0 && t < A.nbin) stencil_face<D, Q, NPAD, NEU>(A, t, sm, lane, val, status, flagged);
+    if (t >= 0 && t < A.nbin) stencil_face<D, Q, NR, NEU>(A, t, sm, lane, val, status, flagged);
   } else {
     for (long long t = walk.next(); t >= 0 && t < A.nbin; t = walk.next()) {
-      stencil_face<D, Q, NPAD, NEU>(A, t, sm, lane, val, status, flagged);
+      stencil_face<D, Q, NR, NEU>(A, t, sm, lane, val, status, flagged);
       __syncthreads();   // the next face reuses the shared memory
     }
   }
@@ -759,23 +1032,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // the cut volume, so every row's delta and weight and the re-centred normal moments also
 // depend on that volume's moments 0..D; their gradient goes to owner_grad.
 
-template <int D, int Q, int NPAD>
-__global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, BackwardArgs B) {
+template <int D, int Q, int NR>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>))) void k_stencil_backward(
+    StencilArgs A, BackwardArgs B) {
   using DM = Dims<D, Q>;
-  constexpr int M = DM::M, MS = DM::MS, Mf = DM::Mf, M1 = DM::M1;
-  __shared__ FaceSmem<D, Q, NPAD> sm;
-  __shared__ double zbar[NPAD];   // W s~bar, then the residual r = zbar - B w
-  __shared__ double bw[NPAD];     // B w
-  __shared__ double wv[M + 1];    // w
-  __shared__ double gdx[64][3];   // per-lane sums of dl/dx0 over the rows
+  constexpr int M = DM::M, Mf = DM::Mf, M1 = DM::M1;
+  __shared__ __align__(16) FaceSmem<D, Q> sm;
   const long long t = blockIdx.x;
   if (t >= A.nbin) return;
   const int lane = threadIdx.x;
   FaceInfo fi = face_info(A, t);
   const GeomPtrs gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
-  double a[M];
-  double sdiag;
   const int32_t* vol_cell = A.vol_cell_ws + (long long)fi.gi * A.g.ncell;
   const int32_t* box_lf = A.box_lf_ws + (long long)fi.gi * A.g.nboxslot;
   const bool act = lane < M;
@@ -796,10 +1064,10 @@ __global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, Backward
     if (lane < 4) og[lane] = 0.0;
     return;
   }
-  double wreg[(NPAD + 63) / 64], zreg[(NPAD + 63) / 64];
-  const int st = face_forward<D, Q, NPAD, false>(A.g, gp, fi, vol_cell, box_lf, A.col, sm, lane, a, sdiag, wreg, zreg,
-                                                 A.wpow);
-  const double* Bs = sm.Bs;
+  WaveMatrix<D, Q> G;
+  double b[NR][M], wreg[NR], zreg[NR], yl;
+  const int st = face_forward<D, Q, NR, false>(A.g, gp, fi, vol_cell, box_lf, A.col, sm, lane, G, b, wreg, zreg, yl,
+                                               A.wpow);
   // a flagged face has s = 0 whatever its inputs: no gradient (the forward status decides
   // for the faces the forward build solved by Householder QR)
   if (st == CUTCELL_STATUS_NONFINITE || B.fwd_status[fi.F] != CUTCELL_STATUS_OK) {
@@ -812,90 +1080,95 @@ __global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, Backward
     if (lane < 4) og[lane] = 0.0;
     return;
   }
-  // s~bar = h^(D-2) val_bar;  zbar = W s~bar;  the direct part of Wbar in gdx-free regs
-  for (int r = lane; r < NPAD; r += 64) {
-    const double sb = (r < N) ? A.hscale * B.val_bar[fi.rp + r] : 0.0;
-    zbar[r] = sm.wls[r] * sb;
-  }
-  __syncthreads();
-  // w = G^-1 B^T zbar, refined:  w += G^-1 B^T (zbar - B w); lane p holds w_p
-  constexpr int NR = (NPAD + 63) / 64;
+  // s~bar = h^(D-2) val_bar;  zbar = W s~bar
+  double sb[NR], zbar[NR], bw[NR];
+  static_for<0, NR>([&](auto R) {
+    const int r = lane + 64 * R;
+    sb[R] = (r < N) ? A.hscale * B.val_bar[fi.rp + r] : 0.0;
+    zbar[R] = wreg[R] * sb[R];
+    bw[R] = 0.0;
+  });
+  // w = G^-1 B^T zbar, refined:  w += G^-1 B^T (zbar - B w); lane p holds w_p, and dy ends
+  // as w.  The column sums read the rows past 64 from the first slots, in turn with the
+  // rows that belong there (face_forward leaves those in place).
+  const int n0 = (NR > 1 && N > 64) ? 64 : ((N + 7) & ~7);
+  const int n1 = (NR > 1 && N > 64) ? ((N - 64 + 7) & ~7) : 0;
+  const int cl = act ? lane : 0;
   double wl = 0.0;
   for (int it = 0; it <= kRefineBackward; ++it) {
-    double res = 0.0;
-    if (act) {
-      double r0 = 0.0, r1 = 0.0, r2 = 0.0, r3 = 0.0;
-      for (int r = 0; r < NPAD; r += 4) {
-        double e0 = zbar[r + 0], e1 = zbar[r + 1], e2 = zbar[r + 2], e3 = zbar[r + 3];
-        if (it > 0) { e0 -= bw[r + 0]; e1 -= bw[r + 1]; e2 -= bw[r + 2]; e3 -= bw[r + 3]; }
-        r0 = fma(Bs[(r + 0) * MS + lane], e0, r0);
-        r1 = fma(Bs[(r + 1) * MS + lane], e1, r1);
-        r2 = fma(Bs[(r + 2) * MS + lane], e2, r2);
-        r3 = fma(Bs[(r + 3) * MS + lane], e3, r3);
+    lds_order();
+    static_for<0, NR>([&](auto R) { sm.zs[lane + 64 * R] = bw[R] - zbar[R]; });
+    lds_order();
+    double p0 = 0.0, p1 = 0.0;
+    column_sum<D, Q>(sm, cl, 0, n0, 0, p0, p1);
+    if constexpr (NR > 1) {
+      if (n1 > 0) {
+        stage_rows<D, Q>(sm, b[1], lane, n1);
+        column_sum<D, Q>(sm, cl, 0, n1, 64, p0, p1);
+        stage_rows<D, Q>(sm, b[0], lane, n1);
       }
-      res = (r0 + r1) + (r2 + r3);
     }
-    const double rhs = res * sdiag;
-    double tq[4] = {0.0, 0.0, 0.0, 0.0};
-    static_for<0, M>([&](auto J) { tq[J % 4] = fma(-a[J], readlane_f64(rhs, J), tq[J % 4]); });
-    if (act) wl += ((tq[0] + tq[1]) + (tq[2] + tq[3])) * sdiag;
-    __syncthreads();
-    static_for<0, NR>([&](auto R) {
-      const int r = lane + 64 * R;
-      if (r < NPAD) {
-        double s = 0.0;
-        static_for<0, M>([&](auto J) { s = fma(Bs[r * MS + J], readlane_f64(wl, J), s); });
-        bw[r] = s;
-      }
+    apply_inverse<D, Q>(sm, lane, G, act ? (p0 + p1) * G.sd : 0.0);
+    if (act) wl += sm.dy[lane];
+    lds_order();
+    if (act) sm.dy[lane] = wl;
+    lds_order();
+    double s[NR][2];
+    static_for<0, NR>([&](auto R) { s[R][0] = s[R][1] = 0.0; });
+    static_for<0, M>([&](auto J) {
+      const double v = sm.dy[J];
+      static_for<0, NR>([&](auto R) { s[R][J % 2] = fma(b[R][J], v, s[R][J % 2]); });
     });
-    __syncthreads();
+    static_for<0, NR>([&](auto R) { bw[R] = s[R][0] + s[R][1]; });
   }
-  if (act) wv[lane] = wl;
-  __syncthreads();
   if (act) {
-    yw[lane] = sm.ys[lane];
+    yw[lane] = yl;
     yw[M + lane] = wl;
+    sm.ys[lane] = yl;
   }
+  lds_order();
   // per row: r = zbar - B w;  Wbar;  (W r, W z) for the moment reduction;  EB x0 terms
   double gx[3] = {0, 0, 0};
-  for (int r = lane; r < N; r += 64) {
-    const double W = sm.wls[r], zz = sm.zs[r];
-    const double rr = zbar[r] - bw[r];
-    const double sb = A.hscale * B.val_bar[fi.rp + r];
-    const double bdot = zz * (rr - bw[r]);            // Bbar_i . B_i
-    const double wtot = sb * zz + bdot / W;           // dl/dW_i
-    if (B.weight_bar) B.weight_bar[fi.rp + r] = wtot;
-    B.nz_rz[2 * (fi.rp + r)] = W * rr;
-    B.nz_rz[2 * (fi.rp + r) + 1] = W * zz;
-    if (fi.kind == 1) {
-      // delta_i = x_i/h - x0h: d B_ip / d delta_d = p_d B_i,p-e_d (weight fixed), and
-      // dW/d delta_d = -p W delta_d / |delta|^2 outside half a cell (W = (2|delta|)^-p)
-      const RowSource rs = row_source<D, Q>(A.g, gp, (int64_t)A.col[fi.rp + r] - fi.phi0, fi.n_vol, fi.n_eb,
-                                            vol_cell, box_lf);
-      double dl[3] = {0, 0, 0}, d2 = 0.0;
-      for (int ax = 0; ax < D; ++ax) {
-        dl[ax] = rs.ctr[ax] - fi.x0h[ax];
-        d2 += dl[ax] * dl[ax];
-      }
-      double gd[3] = {0, 0, 0};
-      static_for<0, M>([&](auto P) {
-        constexpr int p = P;
-        const double bb = rr * sm.ys[p] - zz * wv[p];   // Bbar_ip
-        static_for<0, D>([&](auto AX) {
-          constexpr int ax = AX;
-          constexpr int pd = kMono<D, Q>.e[p][ax];
-          if constexpr (pd > 0) {
-            constexpr int q = mono_index<D>(kMono<D, Q>.e[p][0] - (ax == 0), kMono<D, Q>.e[p][1] - (ax == 1),
-                                            kMono<D, Q>.e[p][2] - (ax == 2));
-            gd[ax] = fma(bb * pd, Bs[r * MS + q], gd[ax]);
-          }
+  static_for<0, NR>([&](auto R) {
+    const int r = lane + 64 * R;
+    if (r < N) {
+      const double Wt = wreg[R], zz = zreg[R];
+      const double rr = zbar[R] - bw[R];
+      const double bdot = zz * (rr - bw[R]);               // Bbar_i . B_i
+      const double wtot = sb[R] * zz + bdot / Wt;          // dl/dW_i
+      if (B.weight_bar) B.weight_bar[fi.rp + r] = wtot;
+      B.nz_rz[2 * (fi.rp + r)] = Wt * rr;
+      B.nz_rz[2 * (fi.rp + r) + 1] = Wt * zz;
+      if (fi.kind == 1) {
+        // delta_i = x_i/h - x0h: d B_ip / d delta_d = p_d B_i,p-e_d (weight fixed), and
+        // dW/d delta_d = -p W delta_d / |delta|^2 outside half a cell (W = (2|delta|)^-p)
+        const RowSource rs = row_source<D, Q>(A.g, gp, (int64_t)A.col[fi.rp + r] - fi.phi0, fi.n_vol, fi.n_eb,
+                                              vol_cell, box_lf);
+        double dl[3] = {0, 0, 0}, d2 = 0.0;
+        for (int ax = 0; ax < D; ++ax) {
+          dl[ax] = rs.ctr[ax] - fi.x0h[ax];
+          d2 += dl[ax] * dl[ax];
+        }
+        double gd[3] = {0, 0, 0};
+        static_for<0, M>([&](auto P) {
+          constexpr int p = P;
+          const double bb = rr * sm.ys[p] - zz * sm.dy[p];   // Bbar_ip
+          static_for<0, D>([&](auto AX) {
+            constexpr int ax = AX;
+            constexpr int pd = kMono<D, Q>.e[p][ax];
+            if constexpr (pd > 0) {
+              constexpr int q = mono_index<D>(kMono<D, Q>.e[p][0] - (ax == 0), kMono<D, Q>.e[p][1] - (ax == 1),
+                                              kMono<D, Q>.e[p][2] - (ax == 2));
+              gd[ax] = fma(bb * pd, b[R][q], gd[ax]);
+            }
+          });
         });
-      });
-      if (sqrt(d2) >= 0.5)
-        for (int ax = 0; ax < D; ++ax) gd[ax] += wtot * (-A.wpow * W * dl[ax] / d2);
-      for (int ax = 0; ax < D; ++ax) gx[ax] -= gd[ax];   // d delta / d x0h = -1
+        if (sqrt(d2) >= 0.5)
+          for (int ax = 0; ax < D; ++ax) gd[ax] += wtot * (-A.wpow * Wt * dl[ax] / d2);
+        for (int ax = 0; ax < D; ++ax) gx[ax] -= gd[ax];   // d delta / d x0h = -1
+      }
     }
-  }
+  });
   // flux-vector gradient Fbar = w
   if (fi.kind == 0) {
     if (lane < 4) og[lane] = 0.0;
@@ -910,7 +1183,7 @@ __global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, Backward
         else if (dn == 0) s = mono_index<2>(e1, e2, 0);
         else if (dn == 1) s = mono_index<2>(e0, e2, 0);
         else s = mono_index<2>(e0, e1, 0);
-        B.grads[fi.gi].face_mom[dn][(fi.ref - A.g.foff[dn]) * Mf + s] = wv[lane];
+        B.grads[fi.gi].face_mom[dn][(fi.ref - A.g.foff[dn]) * Mf + s] = wl;
       }
     }
     return;
@@ -918,17 +1191,23 @@ __global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, Backward
   // EB face: F~_p = sum_d p_d nu'_{d, p - e_d} with nu' the normal moments re-centred by
   // delta0 = (c - x0)/h:  nu'bar_{d,q} = (q_d + 1) w_{q + e_d},  nubar = S(delta0)^T nu'bar,
   // and d nu'_{d,q} / d delta0_k = q_k nu'_{d, q - e_k}
-  for (int ax = 0; ax < 3; ++ax) gdx[lane][ax] = gx[ax];
-  __syncthreads();
+  double gxh[3] = {0, 0, 0};
+  for (int ax = 0; ax < D; ++ax) gxh[ax] = wave_sum_f64(gx[ax]);
+  lds_order();
+  {
+    dd x0dd[3];
+    face_x0_dd<D, Q>(A.g, gp, fi, x0dd);
+    eb_normal_moments<D, Q>(A.g, gp, fi, sm, lane, x0dd);
+  }
+  double g0[3] = {0, 0, 0};
   if (lane < D) {
     double nb[M1];
-    double g0[3] = {0, 0, 0};
     static_for<0, M1>([&](auto I) {
       constexpr int i = I;
       constexpr int q0 = kMono<D, Q - 1>.e[i][0], q1 = kMono<D, Q - 1>.e[i][1], q2 = kMono<D, Q - 1>.e[i][2];
       const int qd = (lane == 0) ? q0 : (lane == 1 ? q1 : q2);
       const int up = mono_index<D>(q0 + (lane == 0), q1 + (lane == 1), q2 + (lane == 2));
-      nb[i] = (qd + 1) * wv[up];
+      nb[i] = (qd + 1) * sm.dy[up];
     });
     static_for<0, M1>([&](auto I) {
       constexpr int i = I;
@@ -946,24 +1225,19 @@ __global__ __launch_bounds__(64) void k_stencil_backward(StencilArgs A, Backward
     recentre_T<D, Q - 1>(nb, d0);
     double* dst = B.grads[fi.gi].eb_nmom + ((long long)fi.ref * D + lane) * M1;
     static_for<0, M1>([&](auto I) { dst[I] = nb[I]; });
-    for (int k = 0; k < 3; ++k) sm.gsum[lane * 3 + k] = g0[k];   // dl/d delta0 from component `lane`
   }
-  __syncthreads();
+  // dl/dx0h = sum over rows - dl/d delta0 (component c in lane c);  x0h_d = centre_d + m^{e_d} / m^0
+  for (int k = 0; k < D; ++k)
+    for (int q = 0; q < D; ++q) gxh[k] -= readlane_f64(g0[k], q);
   if (lane == 0) {
-    // dl/dx0h = sum over rows (gdx) - dl/d delta0;  x0h_d = centre_d + m^{e_d} / m^0
-    double gxh[3] = {0, 0, 0};
-    for (int l = 0; l < 64; ++l)
-      for (int ax = 0; ax < D; ++ax) gxh[ax] += gdx[l][ax];
-    for (int c = 0; c < D; ++c)
-      for (int k = 0; k < D; ++k) gxh[k] -= sm.gsum[c * 3 + k];
     const double* vm = gp.vol_mom + (long long)fi.owner_cell * M;
     const double m0 = vm[0];
-    double g0 = 0.0;
+    double gm = 0.0;
     for (int ax = 0; ax < D; ++ax) {
       og[1 + ax] = gxh[ax] / m0;
-      g0 -= gxh[ax] * vm[1 + ax] / (m0 * m0);
+      gm -= gxh[ax] * vm[1 + ax] / (m0 * m0);
     }
-    og[0] = g0;
+    og[0] = gm;
     for (int ax = D; ax < 3; ++ax) og[1 + ax] = 0.0;
   }
 }
@@ -999,30 +1273,25 @@ inline StencilArgs stencil_args(const Work& w, double hscale, const int32_t* per
 }
 
 // Launch shape of one bin: xcd = 1 or the number of XCDs whose chunks the bin is split
-// into; per_xcd = 0 for one workgroup per face, else the persistent workgroups per chunk;
-// split: which kernel widths take the bin's parts 0 and 1 (its faces with at most
-// NPAD - 8 and NPAD - 4 rows) where narrower instances are compiled -- 0: part 0 at
-// NPAD - 8 and part 1 at NPAD - 4; 1: none, the whole bin at NPAD rows; 2: part 0 at
-// NPAD - 8 only; 3: parts 0 and 1 at NPAD - 4.
+// into; per_xcd = 0 for one workgroup per face, else the persistent workgroups per chunk.
 struct BinSchedule {
   int xcd = 1;
   int per_xcd = 0;
-  int split = 0;
   bool route = true;   // faces the Gram path cannot resolve go to the QR path
+  bool same(const BinSchedule& o) const { return xcd == o.xcd && per_xcd == o.per_xcd && route == o.route; }
 };
 
-template <int D, int Q, int NPAD, bool FWD_ONLY = false>
-static void launch_bin(const Work& w, double hscale, const int32_t* perm, long long nbin, const int64_t* row_ptr,
-                       const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
-                       BinSchedule sc, bool neu, double h, double wpow) {
+// Faces [perm, perm + nbin) of bins whose rows fit 64 NR.
+template <int D, int Q, int NR>
+void launch_rows(const Work& w, double hscale, const int32_t* perm, long long nbin, const int64_t* row_ptr,
+                 const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
+                 BinSchedule sc, bool neu, double h, double wpow) {
   if (nbin <= 0) return;
   StencilArgs A = stencil_args(w, hscale, perm, nbin, row_ptr, col);
   A.wpow = wpow;
-  if constexpr (!FWD_ONLY) {
-    if (bw) {
-      hipLaunchKernelGGL((k_stencil_backward<D, Q, NPAD>), dim3((unsigned)nbin), dim3(64), 0, st, A, *bw);
-      return;
-    }
+  if (bw) {
+    hipLaunchKernelGGL((k_stencil_backward<D, Q, NR>), dim3((unsigned)nbin), dim3(64), 0, st, A, *bw);
+    return;
   }
   const int X = sc.xcd > 1 ? sc.xcd : 1;
   const long long chunk = (nbin + X - 1) / X;
@@ -1033,130 +1302,55 @@ static void launch_bin(const Work& w, double hscale, const int32_t* perm, long l
   if (neu) {   // one workgroup per face (no persistent instance of the Neumann kernel)
     A.per_xcd = (int)chunk;
     A.h = h;
-    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, false, true>), dim3((unsigned)(X * chunk)), dim3(64), 0, st, A, val,
+    hipLaunchKernelGGL((k_stencil<D, Q, NR, false, true>), dim3((unsigned)(X * chunk)), dim3(64), 0, st, A, val,
                        status, w.flagged);
     return;
   }
   if (per < chunk)
-    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, true>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
+    hipLaunchKernelGGL((k_stencil<D, Q, NR, true>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
                        w.flagged);
   else
-    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, false>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
+    hipLaunchKernelGGL((k_stencil<D, Q, NR, false>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
                        w.flagged);
 }
 
-// Waves of the forward kernel that one 80 KB shared-memory pool (two SIMDs) holds: measured
-// on MI355X, residency follows two such pools per CU rather than the 160 KB total.  At most
-// 4 (2 per SIMD at the kernel's register count).
-template <int D, int Q, int NPAD>
-constexpr int pool_waves() {
-  constexpr int n = 81920 / (int)sizeof(LeanSmem<D, Q, NPAD>);
-  return n < 4 ? n : 4;
-}
+// Explicit instantiations: each (dimension, order, rows per lane) lives in one
+// stencil_d*q*.hip file, so the library's kernels compile in parallel.
+#define CC_ROWS(DD, QQ, NR, EXT) \
+  EXT template void launch_rows<DD, QQ, NR>(const Work&, double, const int32_t*, long long, const int64_t*, \
+                                            const int32_t*, double*, int8_t*, hipStream_t, const BackwardArgs*, \
+                                            BinSchedule, bool, double, double);
+CC_ROWS(2, 2, 1, extern) CC_ROWS(2, 2, 2, extern) CC_ROWS(2, 4, 1, extern) CC_ROWS(2, 4, 2, extern)
+CC_ROWS(3, 2, 1, extern) CC_ROWS(3, 2, 2, extern) CC_ROWS(3, 4, 1, extern) CC_ROWS(3, 4, 2, extern)
 
-// A narrower kernel instance of P rows pays for a part of a bin of NPAD rows when it fits
-// more waves per pool (3D order 4: 88 and 92 rows for the 96-row bin, whose regular faces
-// have 88 rows; no other bin of the orders and dimensions built).
-template <int D, int Q, int P, int NPAD>
-constexpr bool narrower_pays() {
-  if constexpr (P < Dims<D, Q>::M) return false;
-  else return pool_waves<D, Q, P>() > pool_waves<D, Q, NPAD>();
-}
-
-// One row bin: its part 0 (n0 faces, at most NPAD - 8 rows) and part 1 (n1 faces, at most
-// NPAD - 4 rows) come first in its order; each runs on the narrowest instance that pays,
-// the rest on the NPAD-row instance.  The adjoint runs the whole bin at NPAD rows.
-template <int D, int Q, int NPAD>
-void launch_row_bin(const Work& w, double hscale, const int32_t* perm, long long nbin, long long n0, long long n1,
-                    const int64_t* row_ptr, const int32_t* col, double* val, int8_t* status, hipStream_t st,
-                    const BackwardArgs* bw, BinSchedule sc, bool neu, double h, double wpow) {
-  constexpr int P0 = NPAD - kBinRows / 2, P1 = NPAD - kBinRows / 4;
-  long long done = 0;
-  if (!bw) {
-    if constexpr (narrower_pays<D, Q, P0, NPAD>()) {
-      if (sc.split == 0 || sc.split == 2) {
-        launch_bin<D, Q, P0, true>(w, hscale, perm, n0, row_ptr, col, val, status, st, bw, sc, neu, h, wpow);
-        done = n0;
-      }
-    }
-    if constexpr (narrower_pays<D, Q, P1, NPAD>()) {
-      if (sc.split == 0 || sc.split == 3) {
-        launch_bin<D, Q, P1, true>(w, hscale, perm + done, n0 + n1 - done, row_ptr, col, val, status, st, bw, sc,
-                                   neu, h, wpow);
-        done = n0 + n1;
-      }
-    }
-  }
-  launch_bin<D, Q, NPAD>(w, hscale, perm + done, nbin - done, row_ptr, col, val, status, st, bw, sc, neu, h, wpow);
-}
-
-// Narrower instances compiled for the bin of NPAD rows: bit 0 for NPAD - 8, bit 1 for NPAD - 4.
-template <int D, int Q, int NPAD>
-constexpr int narrow_mask() {
-  return (narrower_pays<D, Q, NPAD - kBinRows / 2, NPAD>() ? 1 : 0) |
-         (narrower_pays<D, Q, NPAD - kBinRows / 4, NPAD>() ? 2 : 0);
-}
-
-// the same for dimension, order and bin b known at run time (the split modes to tune)
-inline int narrow_mask_of(int D, int Q, int b) {
-  auto pick = [&](auto DD, auto QQ) {
-    constexpr int Dc = decltype(DD)::value, Qc = decltype(QQ)::value;
-    switch (b) {
-      case 1: return narrow_mask<Dc, Qc, 32>();
-      case 2: return narrow_mask<Dc, Qc, 48>();
-      case 3: return narrow_mask<Dc, Qc, 64>();
-      case 4: return narrow_mask<Dc, Qc, 80>();
-      case 5: return narrow_mask<Dc, Qc, 96>();
-      case 6: return narrow_mask<Dc, Qc, 112>();
-      case 7: return narrow_mask<Dc, Qc, 128>();
-      default: return 0;
-    }
-  };
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
-  using I4 = std::integral_constant<int, 4>;
-  if (D == 2) return Q == 2 ? pick(I2{}, I2{}) : pick(I2{}, I4{});
-  return Q == 2 ? pick(I3{}, I2{}) : pick(I3{}, I4{});
-}
-
-// Explicit instantiations: each (dimension, order, bin) lives in one stencil_d*q*.hip file,
-// so the library's kernels compile in parallel (the 3D order-4 bins over three files).
-#define CC_ROW_BIN(DD, QQ, P, EXT) \
-  EXT template void launch_row_bin<DD, QQ, P>(const Work&, double, const int32_t*, long long, long long, long long, \
-                                              const int64_t*, const int32_t*, double*, int8_t*, hipStream_t, \
-                                              const BackwardArgs*, BinSchedule, bool, double, double);
-#define CC_ROW_BINS_ALL(DD, QQ, EXT) \
-  CC_ROW_BIN(DD, QQ, 16, EXT) CC_ROW_BIN(DD, QQ, 32, EXT) CC_ROW_BIN(DD, QQ, 48, EXT) CC_ROW_BIN(DD, QQ, 64, EXT) \
-  CC_ROW_BIN(DD, QQ, 80, EXT) CC_ROW_BIN(DD, QQ, 96, EXT) CC_ROW_BIN(DD, QQ, 112, EXT) CC_ROW_BIN(DD, QQ, 128, EXT)
-CC_ROW_BINS_ALL(2, 2, extern) CC_ROW_BINS_ALL(2, 4, extern) CC_ROW_BINS_ALL(3, 2, extern)
-CC_ROW_BIN(3, 4, 48, extern) CC_ROW_BIN(3, 4, 64, extern) CC_ROW_BIN(3, 4, 80, extern)
-CC_ROW_BIN(3, 4, 96, extern) CC_ROW_BIN(3, 4, 112, extern) CC_ROW_BIN(3, 4, 128, extern)
-
-// The row bins of one (dimension, order): one launch per bin (two for a split bin).
+// The row bins of one (dimension, order): bins that run on the same kernel with the same
+// schedule share a launch (their faces follow each other in the order), so that a small
+// build pays for two launches and no bin ends with a nearly empty chip.
 template <int D, int Q>
 int dispatch_row_bins(const Work& w, double hscale, const int32_t* bin_count, const int64_t* row_ptr,
                       const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
                       const BinSchedule* sched, int only_bin, bool neu, double h, double wpow) {
   constexpr int M = binom(Q + D, D);
+  constexpr int kNarrow = 64 / kBinRows;   // bins of at most 64 rows: one row per lane
   long long start = 0;
-  for (int b = 0; b < kMaxBins; ++b) {
-    const long long nb = bin_count[b];
-    const int32_t* p = w.perm + start;
-    start += nb;
-    if (nb == 0 || (only_bin >= 0 && b != only_bin)) continue;
-    const int npad = kBinRows * (b + 1);
-    if (npad < M) return fail(CUTCELL_E_INVALID_ARG, "internal: face with N >= M in a bin narrower than M");
-    const long long n0 = bin_count[kPartWords + b], n1 = bin_count[kPartWords + kMaxBins + b];
-    switch (npad) {
-#define CC_BIN(P) \
-  case P: \
-    if constexpr (M <= P) \
-      launch_row_bin<D, Q, P>(w, hscale, p, nb, n0, n1, row_ptr, col, val, status, st, bw, sched[b], neu, h, \
-                              wpow); \
-    break;
-      CC_BIN(16) CC_BIN(32) CC_BIN(48) CC_BIN(64) CC_BIN(80) CC_BIN(96) CC_BIN(112) CC_BIN(128)
-#undef CC_BIN
+  for (int b = 0; b < kMaxBins;) {
+    const bool narrow = b < kNarrow;
+    const int last = narrow ? kNarrow : kMaxBins;
+    long long nb = bin_count[b];
+    const bool skip = only_bin >= 0 && b != only_bin;
+    if (nb > 0 && kBinRows * (b + 1) < M && !skip)
+      return fail(CUTCELL_E_INVALID_ARG, "internal: face with N >= M in a bin narrower than M");
+    int e = b + 1;
+    if (only_bin < 0)
+      for (; e < last && (bw || sched[e].same(sched[b])); ++e) nb += bin_count[e];
+    if (!skip) {
+      if (narrow)
+        launch_rows<D, Q, 1>(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
+      else
+        launch_rows<D, Q, 2>(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
     }
+    start += nb;
+    b = e;
   }
   CC_HIP(hipGetLastError());
   return CUTCELL_OK;
