@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcutcell.so")
 SOURCES = ["api.hip", "enumerate.hip", "stencil.hip",
-           *[f"stencil_d{d}q{q}_r{r}.hip" for d in (3, 2) for q in (4, 2) for r in (2, 1)],
+           *[f"stencil_d{d}q{q}_r{r}.hip" for d in (3, 2) for q in (4, 2) for r in (96, 128, 64)],
            "stencil_qr.hip", "apply.hip", "adjoint.hip", "solve.hip", "laplacian.hip", "order.hip", "packed.hip"]
 
 HIPCC_FLAGS = [

@@ -1,0 +1,8 @@
+// Stencil kernels of dimension 2, order 2, up to 64 rows (one file per kernel, so that they
+// compile in parallel).
+#include "stencil_impl.hpp"
+
+namespace cutcell {
+CC_DISPATCH(2, 2, )
+CC_ROWS(2, 2, 64, )
+}  // namespace cutcell

@@ -1,0 +1,8 @@
+// Stencil kernels of dimension 3, order 4, up to 64 rows (one file per kernel, so that they
+// compile in parallel).
+#include "stencil_impl.hpp"
+
+namespace cutcell {
+CC_DISPATCH(3, 4, )
+CC_ROWS(3, 4, 64, )
+}  // namespace cutcell

@@ -208,12 +208,13 @@ struct WaveMatrix {
 };
 
 // Shared memory of one face (one wave): 64 rows of B and one buffer used in turn for the EB
-// normal moments, the tile transposition, the pivot rows and z.  The rows stay in registers
-// too (a lane holds rows lane and lane + 64), so rows past 64 need no space of their own:
-// they take the first slots in turn with the rows that belong there.  20.3 KB in 3D order
-// 4, so that eight waves share the 160 KB of a CU, two on each SIMD, which is also what 256
-// registers a lane allow; with every row in shared memory it was 26 KB at 88 rows and six
-// waves.
+// normal moments, the tile transposition, the pivot blocks and z.  20.3 KB in 3D order 4, so
+// that eight waves share the 160 KB of a CU, two on each SIMD; with every row in shared
+// memory it was 26 KB at 88 rows and six waves.  The slots hold rows 0..63 (state 0), or
+// rows 64 and up in the first slots instead of the ones that belong there (state 1); the
+// contents of the slots concerned that are not in place are kept in registers, flat (18 per
+// lane for 32 slots), and exchanged (RowSwap).  Rows held in registers row by row (140 a
+// lane) left too few for the rest of the solve: 104 spilled, 3 of 13 ms.
 template <int D, int Q>
 struct FaceSmem {
   static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
@@ -376,6 +377,50 @@ __device__ __forceinline__ void stage_rows(SM& sm, const double* m, int lane, in
   lds_order();
   if (lane < n) static_for<0, M>([&](auto I) { sm.Bs[lane * MS + I] = m[I]; });
   lds_order();
+}
+
+// The slots of Bs that rows past 64 take in turn with rows 0, 1, ...: NX of them, flat.
+template <int D, int Q, int NX>
+struct RowSwap {
+  static constexpr int MS = Dims<D, Q>::MS, FL = (NX * MS + 63) / 64;
+  double f[FL > 0 ? FL : 1];
+  template <class SM>
+  __device__ __forceinline__ void save(const SM& sm, int lane) {
+    lds_order();
+    static_for<0, FL>([&](auto I) { f[I] = sm.Bs[lane + 64 * I]; });
+    lds_order();
+  }
+  template <class SM>
+  __device__ __forceinline__ void exchange(SM& sm, int lane) {
+    lds_order();
+    double t[FL > 0 ? FL : 1];
+    static_for<0, FL>([&](auto I) { t[I] = sm.Bs[lane + 64 * I]; });
+    lds_order();
+    static_for<0, FL>([&](auto I) { sm.Bs[lane + 64 * I] = f[I]; });
+    static_for<0, FL>([&](auto I) { f[I] = t[I]; });
+    lds_order();
+  }
+};
+
+// slot `lane` of Bs times the vector dy
+template <int D, int Q, class SM>
+__device__ __forceinline__ double row_product(const SM& sm, int lane) {
+  constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS;
+  double p[2] = {0.0, 0.0};
+  static_for<0, M>([&](auto J) { p[J % 2] = fma(sm.Bs[lane * MS + J], sm.dy[J], p[J % 2]); });
+  return p[0] + p[1];
+}
+template <int D, int Q, class SM>
+__device__ __forceinline__ Dot2 row_product_dot2(const SM& sm, int lane) {
+  constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS;
+  Dot2 d0{0.0, 0.0}, d1{0.0, 0.0};
+#pragma unroll 1
+  for (int j = 0; j + 1 < M; j += 2) {
+    dot2_add(d0, sm.Bs[lane * MS + j], sm.dy[j]);
+    dot2_add(d1, sm.Bs[lane * MS + j + 1], sm.dy[j + 1]);
+  }
+  if constexpr (M % 2) dot2_add(d0, sm.Bs[lane * MS + M - 1], sm.dy[M - 1]);
+  return dot2_join(d0, d1);
 }
 
 // G += the n (a multiple of 8) rows in Bs: tiles on and above the diagonal with
@@ -590,12 +635,12 @@ __device__ __forceinline__ void apply_inverse(SM& sm, int lane, const WaveMatrix
   lds_order();
 }
 
-// sum of Bs[i][lane] z[i] over rows [i0, i1) of Bs (multiples of 8), z at zs[i + zoff]: two
-// sums in turn
+// sum of -Bs[i][lane] z[i] over the first n (a multiple of 8) slots of Bs, z at zs[i + zoff]:
+// two sums in turn
 template <int D, int Q, class SM>
-__device__ __forceinline__ void column_sum(const SM& sm, int lane, int i0, int i1, int zoff, double& p0, double& p1) {
+__device__ __forceinline__ void column_sum(const SM& sm, int lane, int n, int zoff, double& p0, double& p1) {
   constexpr int MS = Dims<D, Q>::MS;
-  for (int i = i0; i < i1; i += 8) {
+  for (int i = 0; i < n; i += 8) {
     static_for<0, 8>([&](auto U) {
       const double b = sm.Bs[(i + U) * MS + lane], z = sm.zs[i + zoff + U];
       if constexpr (U % 2 == 0) p0 = fma(-b, z, p0);
@@ -606,10 +651,10 @@ __device__ __forceinline__ void column_sum(const SM& sm, int lane, int i0, int i
 
 // the same compensated, the low part of z in the compensation
 template <int D, int Q, class SM>
-__device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int i0, int i1, int zoff, Dot2& d0, Dot2& d1,
+__device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int n, int zoff, Dot2& d0, Dot2& d1,
                                                 double& lo) {
   constexpr int MS = Dims<D, Q>::MS;
-  for (int i = i0; i < i1; i += 2) {
+  for (int i = 0; i < n; i += 2) {
     const double b0 = -sm.Bs[i * MS + lane], b1 = -sm.Bs[(i + 1) * MS + lane];
     dot2_add(d0, b0, sm.zs[i + zoff]);
     dot2_add(d1, b1, sm.zs[i + zoff + 1]);
@@ -619,18 +664,18 @@ __device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int i0, 
 }
 
 // Rows, Gram matrix, inverse and the refined semi-normal solve of one face with at most
-// 64 NR rows.  Leaves the rows lane, lane + 64 of B in b[][] (and the first 64 in Bs), the
-// inverse in W, weights and z of the lane's rows in wreg[], zreg[], and component `lane` of
-// y in y.  Returns the face status, or kStatusRoute.
-template <int D, int Q, int NR, bool NEU, class SM>
+// NPAD (64, 96 or 128) rows.  Leaves rows 0..63 of B in Bs and the ones past 64 in sw, the
+// inverse in W, weights and z of rows lane and lane + 64 in wreg[], zreg[], and component
+// `lane` of y in y.  Returns the face status, or kStatusRoute.
+template <int D, int Q, int NPAD, bool NEU, class SM>
 __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& gp, const FaceInfo& fi,
                                             const int32_t* __restrict__ vol_cell, const int32_t* __restrict__ box_lf,
                                             const int32_t* __restrict__ col, SM& sm, int lane, WaveMatrix<D, Q>& W,
-                                            double (*b)[Dims<D, Q>::M], double* wreg, double* zreg, double& y,
+                                            RowSwap<D, Q, NPAD - 64>& sw, double* wreg, double* zreg, double& y,
                                             double wpow, bool* rank_low = nullptr) {
   using DM = Dims<D, Q>;
   using TL = Tile<D, Q>;
-  constexpr int M = DM::M, MTF = TL::MTF, MV = TL::MV, PI = TL::PI;
+  constexpr int M = DM::M, MS = DM::MS, MTF = TL::MTF, MV = TL::MV, PI = TL::PI, NR = (NPAD + 63) / 64;
   const int N = fi.N;
   // rows in Bs (n0) and past 64 (n1), in eights (the rows past N are zero)
   const int n0 = (NR > 1 && N > 64) ? 64 : ((N + 7) & ~7);
@@ -639,6 +684,8 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
   // ---- rows of B ----------------------------------------------------------------------
   // Lane r builds rows r and r + 64: every row's index chain (col -> cell -> moments) is
   // issued before the first row is finished, so the dependent loads of all rows overlap.
+  // The rows of small cells come from a second pass, which only the faces that have some
+  // take.
   bool finite = true;
   dd x0dd[3];
   face_x0_dd<D, Q>(g, gp, fi, x0dd);
@@ -648,31 +695,42 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
     if (r < N) rsrc[R] = row_source<D, Q>(g, gp, (int64_t)col[fi.rp + r] - fi.phi0, fi.n_vol, fi.n_eb, vol_cell,
                                           box_lf);
   });
+  double b1[M];       // row lane + 64
+  bool small[NR];
   static_for<0, NR>([&](auto R) {
     const int r = lane + 64 * R;
+    double m[M];
     double wr = 0.0;
-    double* m = b[R];
+    small[R] = false;
+    static_for<0, M>([&](auto I) { m[I] = 0.0; });
     if (r < N) {
       const bool neu_row = NEU && rsrc[R].eb >= 0;
-      const double m0 = neu_row ? gp.eb_mom[(long long)rsrc[R].eb * M] : rsrc[R].src[0];
-      if (!(m0 >= kSmallCell)) {   // a small cell (or a non-finite moment): double-double
-        dd md[M];
-        finite = dd_row<D, Q, NEU>(gp, rsrc[R], x0dd, wpow, md, wr) && finite;
-        static_for<0, M>([&](auto I) { m[I] = md[I].hi; });
-      } else if (neu_row) {
-        finite = neumann_row<D, Q>(gp, rsrc[R].eb, rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
+      bool fin;
+      if (neu_row) {
+        small[R] = !(gp.eb_mom[(long long)rsrc[R].eb * M] >= kSmallCell);
+        fin = neumann_row<D, Q>(gp, rsrc[R].eb, rsrc[R].ctr, fi.x0h, m, wr, wpow);
       } else {
         load_row_moments<D, Q>(rsrc[R], m);
-        finite = finish_row<D, Q>(rsrc[R].ctr, fi.x0h, m, wr, wpow) && finite;
+        small[R] = !(m[0] >= kSmallCell);   // (or a non-finite moment)
+        fin = finish_row<D, Q>(rsrc[R].ctr, fi.x0h, m, wr, wpow);
       }
-    } else {
-      static_for<0, M>([&](auto I) { m[I] = 0.0; });
+      finite = finite && (fin || small[R]);
     }
     wreg[R] = wr;
-    if constexpr (R == 0) stage_rows<D, Q>(sm, b[0], lane, FaceSmem<D, Q>::S);
+    if constexpr (R == 0) stage_rows<D, Q>(sm, m, lane, FaceSmem<D, Q>::S);
+    else static_for<0, M>([&](auto I) { b1[I] = m[I]; });
   });
+  // row lane + 64 R of a small cell in double-double, into the lane's slot
+  auto small_row = [&](auto R) {
+    if (small[R]) {
+      dd md[M];
+      finite = dd_row<D, Q, NEU>(gp, rsrc[R], x0dd, wpow, md, wreg[R]) && finite;
+      static_for<0, M>([&](auto I) { sm.Bs[lane * MS + I] = md[I].hi; });
+    }
+    lds_order();
+  };
+  small_row(std::integral_constant<int, 0>{});
   const double fv = face_flux<D, Q>(g, gp, fi, sm, lane, x0dd);
-  const bool allfinite = __all(finite) && __all(isfinite(fv));
 
   // ---- G = B^T B --------------------------------------------------------------------------
   const int r = lane >> 4, c = lane & 15;
@@ -683,15 +741,13 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
       W.ar[I] = 0.0;
     });
     W.t = 0.0;
+    lds_order();
     gram_rows<D, Q>(sm, lane, n0, acc, W);
     if constexpr (NR > 1) {
-      // the first row comes back from shared memory, so that it takes no registers while
-      // the second one is built (which needs all of them in double-double)
-      static_for<0, M>([&](auto I) { b[0][I] = sm.Bs[lane * DM::MS + I]; });
-      if (n1 > 0) {
-        stage_rows<D, Q>(sm, b[1], lane, n1);
-        gram_rows<D, Q>(sm, lane, n1, acc, W);
-      }
+      sw.save(sm, lane);
+      stage_rows<D, Q>(sm, b1, lane, n1);
+      small_row(std::integral_constant<int, 1>{});
+      gram_rows<D, Q>(sm, lane, n1, acc, W);   // the slots are left in state 1
     }
     static_for<0, MTF>([&](auto I) {
       static_for<I, MTF>([&](auto J) { static_for<0, 4>([&](auto QQ) { W.a[I][J][QQ] = acc[I][J][(int)QQ]; }); });
@@ -706,6 +762,8 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
       lds_order();
     }
   }
+
+  const bool allfinite = __all(finite) && __all(isfinite(fv));
 
   // ---- equilibrate to unit diagonal ---------------------------------------------------------
   // E = 1/sqrt(diag G); the diagonal goes through shared memory to component order and E
@@ -815,38 +873,26 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
   });
   for (int it = 0; it <= kRefine; ++it) {
     if (act) y += sm.dy[lane];
-    // z += B dy
-    if (dot2) {
-      static_for<0, NR>([&](auto R) {
-        Dot2 d0{0.0, 0.0}, d1{0.0, 0.0};
-        static_for<0, M>([&](auto J) {
-          if constexpr (J % 2 == 0) dot2_add(d0, b[R][J], sm.dy[J]);
-          else dot2_add(d1, b[R][J], sm.dy[J]);
-        });
-        const Dot2 d = dot2_join(d0, d1);
+    // z += B dy: the rows past 64 in state 1, then the others in state 0
+    static_for_down<0, NR>([&](auto R) {
+      double inc;
+      if (dot2) {
+        const Dot2 d = row_product_dot2<D, Q>(sm, lane);
         const dd zs2 = dd_add(dd{zreg[R], zlo[R]}, dd{d.s, d.c});
-        zreg[R] = zs2.hi;
-        zlo[R] = zs2.lo;
-        if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * (d.s + d.c)));
-      });
-    } else {
-      double inc[NR][2];
-      static_for<0, NR>([&](auto R) { inc[R][0] = inc[R][1] = 0.0; });
-      static_for<0, M>([&](auto J) {
-        const double v = sm.dy[J];
-        static_for<0, NR>([&](auto R) { inc[R][J % 2] = fma(b[R][J], v, inc[R][J % 2]); });
-      });
-      static_for<0, NR>([&](auto R) {
-        const double s = inc[R][0] + inc[R][1];
-        zreg[R] += s;
-        if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * s));
-      });
-    }
+        zreg[R] = (R == 0 || lane < n1) ? zs2.hi : 0.0;
+        zlo[R] = (R == 0 || lane < n1) ? zs2.lo : 0.0;
+        inc = d.s + d.c;
+      } else {
+        inc = row_product<D, Q>(sm, lane);
+        zreg[R] = (R == 0 || lane < n1) ? zreg[R] + inc : 0.0;
+      }
+      if (it == kRefine) dlast = fmax(dlast, fabs(wreg[R] * inc));
+      if constexpr (R > 0) sw.exchange(sm, lane);
+    });
     if (it == kRefine) break;
     // residual of B^T z = F~ (two interleaved sums, compensated past kDot2Cond, where the
     // low part of z enters the compensation); z goes through shared memory, B^T is read by
-    // columns: first the rows in place, then, if rows past 64 stand in the first slots, the
-    // rows that belong there
+    // columns: rows 0..63, then the ones past 64
     lds_order();
     static_for<0, NR>([&](auto R) {
       sm.zs[lane + 64 * R] = zreg[R];
@@ -858,25 +904,19 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
     if (dot2) {
       Dot2 d0{fv, 0.0}, d1{0.0, 0.0};
       double lo = 0.0;
-      column_sum_dot2<D, Q>(sm, cl, n1, n0, 0, d0, d1, lo);
+      column_sum_dot2<D, Q>(sm, cl, n0, 0, d0, d1, lo);
       if constexpr (NR > 1) {
-        if (n1 > 0) {
-          column_sum_dot2<D, Q>(sm, cl, 0, n1, 64, d0, d1, lo);
-          stage_rows<D, Q>(sm, b[0], lane, n1);
-          column_sum_dot2<D, Q>(sm, cl, 0, n1, 0, d0, d1, lo);
-        }
+        sw.exchange(sm, lane);
+        column_sum_dot2<D, Q>(sm, cl, n1, 64, d0, d1, lo);
       }
       d1.c += lo;
       res = dot2_merge(d0, d1);
     } else {
       double p0 = fv, p1 = 0.0;
-      column_sum<D, Q>(sm, cl, n1, n0, 0, p0, p1);
+      column_sum<D, Q>(sm, cl, n0, 0, p0, p1);
       if constexpr (NR > 1) {
-        if (n1 > 0) {
-          column_sum<D, Q>(sm, cl, 0, n1, 64, p0, p1);
-          stage_rows<D, Q>(sm, b[0], lane, n1);
-          column_sum<D, Q>(sm, cl, 0, n1, 0, p0, p1);
-        }
+        sw.exchange(sm, lane);
+        column_sum<D, Q>(sm, cl, n1, 64, p0, p1);
       }
       res = p0 + p1;
     }
@@ -960,19 +1000,20 @@ __device__ __forceinline__ FaceInfo face_info(const StencilArgs& A, long long t)
 // One face per workgroup (WALK = false: face t of the bin, t from the XCD mapping), or a
 // persistent workgroup that walks its chunk (WALK = true).  Two instances because the
 // loop costs the single-face kernel registers.
-template <int D, int Q, int NR, bool NEU>
+template <int D, int Q, int NPAD, bool NEU>
 __device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, FaceSmem<D, Q>& sm, int lane,
                                              double* __restrict__ val, int8_t* __restrict__ status, int32_t* flagged) {
-  constexpr int M = Dims<D, Q>::M;
+  constexpr int NR = (NPAD + 63) / 64;
   FaceInfo fi = face_info(A, t);
   const GeomPtrs gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
   WaveMatrix<D, Q> W;
-  double b[NR][M], wreg[NR], zreg[NR], y;
+  RowSwap<D, Q, NPAD - 64> sw;
+  double wreg[NR], zreg[NR], y;
   bool rank_low = false;
-  int st = face_forward<D, Q, NR, NEU>(A.g, gp, fi, A.vol_cell_ws + (long long)fi.gi * A.g.ncell,
-                                       A.box_lf_ws + (long long)fi.gi * A.g.nboxslot, A.col, sm, lane, W, b, wreg,
-                                       zreg, y, A.wpow, &rank_low);
+  int st = face_forward<D, Q, NPAD, NEU>(A.g, gp, fi, A.vol_cell_ws + (long long)fi.gi * A.g.ncell,
+                                         A.box_lf_ws + (long long)fi.gi * A.g.nboxslot, A.col, sm, lane, W, sw, wreg,
+                                         zreg, y, A.wpow, &rank_low);
   if (st == kStatusRoute) {
     if (A.route) {   // the QR path writes this face's values and status
       if (lane == 0) A.qr_list[atomicAdd(A.qr_count, 1)] = fi.F;
@@ -1002,7 +1043,7 @@ __device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, 
 template <int D, int Q>
 constexpr int kWaves = Dims<D, Q>::M > 16 ? 2 : 4;
 
-template <int D, int Q, int NR, bool WALK, bool NEU = false>
+template <int D, int Q, int NPAD, bool WALK, bool NEU = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>))) void k_stencil(
     StencilArgs A, double* __restrict__ val, int8_t* __restrict__ status, int32_t* flagged) {
   __shared__ __align__(16) FaceSmem<D, Q> sm;
@@ -1010,10 +1051,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
   FaceWalk walk(A);
   if constexpr (!WALK) {
     const long long t = walk.next();
-    if (t >= 0 && t < A.nbin) stencil_face<D, Q, NR, NEU>(A, t, sm, lane, val, status, flagged);
+    if (t >= 0 && t < A.nbin) stencil_face<D, Q, NPAD, NEU>(A, t, sm, lane, val, status, flagged);
   } else {
     for (long long t = walk.next(); t >= 0 && t < A.nbin; t = walk.next()) {
-      stencil_face<D, Q, NR, NEU>(A, t, sm, lane, val, status, flagged);
+      stencil_face<D, Q, NPAD, NEU>(A, t, sm, lane, val, status, flagged);
       __syncthreads();   // the next face reuses the shared memory
     }
   }
@@ -1032,11 +1073,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
 // the cut volume, so every row's delta and weight and the re-centred normal moments also
 // depend on that volume's moments 0..D; their gradient goes to owner_grad.
 
-template <int D, int Q, int NR>
+template <int D, int Q, int NPAD>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>))) void k_stencil_backward(
     StencilArgs A, BackwardArgs B) {
   using DM = Dims<D, Q>;
-  constexpr int M = DM::M, Mf = DM::Mf, M1 = DM::M1;
+  constexpr int M = DM::M, MS = DM::MS, Mf = DM::Mf, M1 = DM::M1, NR = (NPAD + 63) / 64;
   __shared__ __align__(16) FaceSmem<D, Q> sm;
   const long long t = blockIdx.x;
   if (t >= A.nbin) return;
@@ -1065,9 +1106,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
     return;
   }
   WaveMatrix<D, Q> G;
-  double b[NR][M], wreg[NR], zreg[NR], yl;
-  const int st = face_forward<D, Q, NR, false>(A.g, gp, fi, vol_cell, box_lf, A.col, sm, lane, G, b, wreg, zreg, yl,
-                                               A.wpow);
+  RowSwap<D, Q, NPAD - 64> sw;
+  double wreg[NR], zreg[NR], yl;
+  const int st = face_forward<D, Q, NPAD, false>(A.g, gp, fi, vol_cell, box_lf, A.col, sm, lane, G, sw, wreg, zreg, yl,
+                                                 A.wpow);
   // a flagged face has s = 0 whatever its inputs: no gradient (the forward status decides
   // for the faces the forward build solved by Householder QR)
   if (st == CUTCELL_STATUS_NONFINITE || B.fwd_status[fi.F] != CUTCELL_STATUS_OK) {
@@ -1089,8 +1131,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
     bw[R] = 0.0;
   });
   // w = G^-1 B^T zbar, refined:  w += G^-1 B^T (zbar - B w); lane p holds w_p, and dy ends
-  // as w.  The column sums read the rows past 64 from the first slots, in turn with the
-  // rows that belong there (face_forward leaves those in place).
+  // as w.  Rows 0..63 are in their slots (state 0), the ones past 64 change places with them.
   const int n0 = (NR > 1 && N > 64) ? 64 : ((N + 7) & ~7);
   const int n1 = (NR > 1 && N > 64) ? ((N - 64 + 7) & ~7) : 0;
   const int cl = act ? lane : 0;
@@ -1100,26 +1141,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
     static_for<0, NR>([&](auto R) { sm.zs[lane + 64 * R] = bw[R] - zbar[R]; });
     lds_order();
     double p0 = 0.0, p1 = 0.0;
-    column_sum<D, Q>(sm, cl, 0, n0, 0, p0, p1);
+    column_sum<D, Q>(sm, cl, n0, 0, p0, p1);
     if constexpr (NR > 1) {
-      if (n1 > 0) {
-        stage_rows<D, Q>(sm, b[1], lane, n1);
-        column_sum<D, Q>(sm, cl, 0, n1, 64, p0, p1);
-        stage_rows<D, Q>(sm, b[0], lane, n1);
-      }
+      sw.exchange(sm, lane);
+      column_sum<D, Q>(sm, cl, n1, 64, p0, p1);
     }
     apply_inverse<D, Q>(sm, lane, G, act ? (p0 + p1) * G.sd : 0.0);
     if (act) wl += sm.dy[lane];
     lds_order();
     if (act) sm.dy[lane] = wl;
     lds_order();
-    double s[NR][2];
-    static_for<0, NR>([&](auto R) { s[R][0] = s[R][1] = 0.0; });
-    static_for<0, M>([&](auto J) {
-      const double v = sm.dy[J];
-      static_for<0, NR>([&](auto R) { s[R][J % 2] = fma(b[R][J], v, s[R][J % 2]); });
+    static_for_down<0, NR>([&](auto R) {
+      const double s = row_product<D, Q>(sm, lane);
+      bw[R] = (R == 0 || lane < n1) ? s : 0.0;
+      if constexpr (R > 0) sw.exchange(sm, lane);
     });
-    static_for<0, NR>([&](auto R) { bw[R] = s[R][0] + s[R][1]; });
   }
   if (act) {
     yw[lane] = yl;
@@ -1159,7 +1195,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
             if constexpr (pd > 0) {
               constexpr int q = mono_index<D>(kMono<D, Q>.e[p][0] - (ax == 0), kMono<D, Q>.e[p][1] - (ax == 1),
                                               kMono<D, Q>.e[p][2] - (ax == 2));
-              gd[ax] = fma(bb * pd, b[R][q], gd[ax]);
+              gd[ax] = fma(bb * pd, sm.Bs[lane * MS + q], gd[ax]);
             }
           });
         });
@@ -1168,6 +1204,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
         for (int ax = 0; ax < D; ++ax) gx[ax] -= gd[ax];   // d delta / d x0h = -1
       }
     }
+    if constexpr (R + 1 < NR) sw.exchange(sm, lane);
   });
   // flux-vector gradient Fbar = w
   if (fi.kind == 0) {
@@ -1281,8 +1318,8 @@ struct BinSchedule {
   bool same(const BinSchedule& o) const { return xcd == o.xcd && per_xcd == o.per_xcd && route == o.route; }
 };
 
-// Faces [perm, perm + nbin) of bins whose rows fit 64 NR.
-template <int D, int Q, int NR>
+// Faces [perm, perm + nbin) of bins of at most NPAD rows.
+template <int D, int Q, int NPAD>
 void launch_rows(const Work& w, double hscale, const int32_t* perm, long long nbin, const int64_t* row_ptr,
                  const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
                  BinSchedule sc, bool neu, double h, double wpow) {
@@ -1290,7 +1327,7 @@ void launch_rows(const Work& w, double hscale, const int32_t* perm, long long nb
   StencilArgs A = stencil_args(w, hscale, perm, nbin, row_ptr, col);
   A.wpow = wpow;
   if (bw) {
-    hipLaunchKernelGGL((k_stencil_backward<D, Q, NR>), dim3((unsigned)nbin), dim3(64), 0, st, A, *bw);
+    hipLaunchKernelGGL((k_stencil_backward<D, Q, NPAD>), dim3((unsigned)nbin), dim3(64), 0, st, A, *bw);
     return;
   }
   const int X = sc.xcd > 1 ? sc.xcd : 1;
@@ -1302,26 +1339,26 @@ void launch_rows(const Work& w, double hscale, const int32_t* perm, long long nb
   if (neu) {   // one workgroup per face (no persistent instance of the Neumann kernel)
     A.per_xcd = (int)chunk;
     A.h = h;
-    hipLaunchKernelGGL((k_stencil<D, Q, NR, false, true>), dim3((unsigned)(X * chunk)), dim3(64), 0, st, A, val,
+    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, false, true>), dim3((unsigned)(X * chunk)), dim3(64), 0, st, A, val,
                        status, w.flagged);
     return;
   }
   if (per < chunk)
-    hipLaunchKernelGGL((k_stencil<D, Q, NR, true>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
+    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, true>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
                        w.flagged);
   else
-    hipLaunchKernelGGL((k_stencil<D, Q, NR, false>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
+    hipLaunchKernelGGL((k_stencil<D, Q, NPAD, false>), dim3((unsigned)(X * per)), dim3(64), 0, st, A, val, status,
                        w.flagged);
 }
 
-// Explicit instantiations: each (dimension, order, rows per lane) lives in one
+// Explicit instantiations: each (dimension, order, most rows) lives in one
 // stencil_d*q*.hip file, so the library's kernels compile in parallel.
-#define CC_ROWS(DD, QQ, NR, EXT) \
-  EXT template void launch_rows<DD, QQ, NR>(const Work&, double, const int32_t*, long long, const int64_t*, \
-                                            const int32_t*, double*, int8_t*, hipStream_t, const BackwardArgs*, \
-                                            BinSchedule, bool, double, double);
-CC_ROWS(2, 2, 1, extern) CC_ROWS(2, 2, 2, extern) CC_ROWS(2, 4, 1, extern) CC_ROWS(2, 4, 2, extern)
-CC_ROWS(3, 2, 1, extern) CC_ROWS(3, 2, 2, extern) CC_ROWS(3, 4, 1, extern) CC_ROWS(3, 4, 2, extern)
+#define CC_ROWS(DD, QQ, NPAD, EXT) \
+  EXT template void launch_rows<DD, QQ, NPAD>(const Work&, double, const int32_t*, long long, const int64_t*, \
+                                              const int32_t*, double*, int8_t*, hipStream_t, const BackwardArgs*, \
+                                              BinSchedule, bool, double, double);
+#define CC_ROWS_ALL(DD, QQ) CC_ROWS(DD, QQ, 64, extern) CC_ROWS(DD, QQ, 96, extern) CC_ROWS(DD, QQ, 128, extern)
+CC_ROWS_ALL(2, 2) CC_ROWS_ALL(2, 4) CC_ROWS_ALL(3, 2) CC_ROWS_ALL(3, 4)
 
 // The row bins of one (dimension, order): bins that run on the same kernel with the same
 // schedule share a launch (their faces follow each other in the order), so that a small
@@ -1331,23 +1368,20 @@ int dispatch_row_bins(const Work& w, double hscale, const int32_t* bin_count, co
                       const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
                       const BinSchedule* sched, int only_bin, bool neu, double h, double wpow) {
   constexpr int M = binom(Q + D, D);
-  constexpr int kNarrow = 64 / kBinRows;   // bins of at most 64 rows: one row per lane
+  auto width = [](int b) { return kBinRows * (b + 1) <= 64 ? 64 : (kBinRows * (b + 1) <= 96 ? 96 : 128); };
   long long start = 0;
   for (int b = 0; b < kMaxBins;) {
-    const bool narrow = b < kNarrow;
-    const int last = narrow ? kNarrow : kMaxBins;
     long long nb = bin_count[b];
     const bool skip = only_bin >= 0 && b != only_bin;
     if (nb > 0 && kBinRows * (b + 1) < M && !skip)
       return fail(CUTCELL_E_INVALID_ARG, "internal: face with N >= M in a bin narrower than M");
     int e = b + 1;
     if (only_bin < 0)
-      for (; e < last && (bw || sched[e].same(sched[b])); ++e) nb += bin_count[e];
+      for (; e < kMaxBins && width(e) == width(b) && (bw || sched[e].same(sched[b])); ++e) nb += bin_count[e];
     if (!skip) {
-      if (narrow)
-        launch_rows<D, Q, 1>(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
-      else
-        launch_rows<D, Q, 2>(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
+      const auto launch = width(b) == 64 ? launch_rows<D, Q, 64> : (width(b) == 96 ? launch_rows<D, Q, 96>
+                                                                                   : launch_rows<D, Q, 128>);
+      launch(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
     }
     start += nb;
     b = e;
