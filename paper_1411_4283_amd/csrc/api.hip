@@ -107,7 +107,8 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.box_id = (int32_t*)take(sizeof(int32_t) * G * g.NF);
   t.box_lf = (int32_t*)take(sizeof(int32_t) * G * std::max<long long>(g.nboxslot, 1));
   t.vol_cell = (int32_t*)take(sizeof(int32_t) * G * g.ncell);
-  t.cellinfo = (uint8_t*)take(sizeof(uint8_t) * G * g.ncell);
+  t.cellinfo = (uint8_t*)take(sizeof(uint8_t) * G * g.ncell + 2 * kInfoPad);
+  if (base) t.cellinfo += kInfoPad;
   t.ballreg = (uint8_t*)take(sizeof(uint8_t) * G * g.ncell);
   t.ballreg_tmp = (uint8_t*)take(sizeof(uint8_t) * G * g.ncell);
   t.canon = (uint8_t*)take(sizeof(uint8_t) * G * g.ncell);
@@ -135,10 +136,6 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
     const int M = binom(o.order + o.dim, o.dim);
     t.qr_slots = (int)std::min<long long>(kQrSlots, std::max<long long>(totface, 1));
     t.qr_b = (double*)take(sizeof(double) * t.qr_slots * 2 * kMaxRows * (M | 1));
-    // ballot masks of the neighbour window, (2R + 2)(2R + 1)^(D-1) cells, per face
-    long long nw = 2 * o.path_radius + 2;
-    for (int d = 1; d < o.dim; ++d) nw *= 2 * o.path_radius + 1;
-    t.nbmask = (unsigned long long*)take(sizeof(unsigned long long) * totface * ((nw + 63) / 64));
   }
   t.geoms = (GeomPtrs*)take(sizeof(GeomPtrs) * G);
   t.bytes = off;

@@ -252,6 +252,12 @@ __device__ __forceinline__ double wave_max_f64(double v) {
   return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
 }
 
+__device__ __forceinline__ long long readlane_i64(long long v, int lane) {
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
 __device__ __forceinline__ unsigned long long lanes_below(int lane) {
   return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 }

@@ -243,13 +243,26 @@ int enumerate_batch(const Work& w, const cutcell_opts& o, hipStream_t st) {
 
 // ---------------------------------------------------------------------------------------
 // neighbours: breadth-first search by path distance inside a window around the face
+//
+// A lane holds lines of window cells along x as bit masks (volumes, open faces per side, EB
+// faces), read as the line's bytes of cellinfo in one or two loads.  A step of the search is
+// then a handful of bit operations on the lane's mask and its four neighbours' masks (y and
+// z, through shared memory).  A window has (2R + 2)(2R + 1) lines in 3D and 2R + 2 in 2D, so
+// 16, 32 or 64 lanes take a face; a wave takes a chunk of consecutive faces, answers the
+// ones between ball-regular cells from the fixed offsets, and searches the others in turn.
+// The fill pass searches again: that is cheaper than keeping the masks.  It is bound by the
+// latency of the search's dependent steps.  64^3, path radius 3 (724k faces, half of them
+// searched): count and fill 0.7 ms; with one cell per lane and step, a wave per face and the
+// masks kept for the fill, 1.69 and 0.96 ms.
 
 template <int D, int R>
 struct Win {
   static constexpr int EN = 2 * R + 2;                       // extent along the face normal
   static constexpr int ET = 2 * R + 1;                       // transverse extent
-  static constexpr int NW = EN * (D >= 2 ? ET : 1) * (D >= 3 ? ET : 1);
-  static constexpr int K = (NW + 63) / 64;                   // window cells per lane
+  static constexpr int L = D == 3 ? EN * ET : EN;            // lines along x, at most
+  static constexpr int LPF = L <= 16 ? 16 : (L <= 32 ? 32 : 64);   // lanes per face
+  static constexpr int KL = (L + LPF - 1) / LPF;             // lines per lane
+  static constexpr int FPW = 64 / LPF;                       // faces of a wave at a time
 };
 
 // Rows of a face between two ball-regular cells a (low) and a + e_d: the union of the L1
@@ -288,259 +301,307 @@ struct RegularRows {
 template <int D, int R>
 inline constexpr RegularRows<D, R> kRegularRows{};
 
+// bit i of the result: bit `b` of byte i of v
+__device__ __forceinline__ unsigned byte_plane(uint2 v, int b) {
+  const unsigned lo = (v.x >> b) & 0x01010101u, hi = (v.y >> b) & 0x01010101u;
+  return __builtin_amdgcn_udot4(hi, 0x80402010u, __builtin_amdgcn_udot4(lo, 0x08040201u, 0u, false), false);
+}
+
+// sum of v over the lane's group of W lanes, and over the lanes of it before this one
+template <int W>
+__device__ __forceinline__ int group_sum(int v) {
+#pragma unroll
+  for (int o = W / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, W);
+  return v;
+}
+template <int W>
+__device__ __forceinline__ int group_before(int v) {
+  const int l = threadIdx.x & (W - 1);
+  int s = v;
+#pragma unroll
+  for (int o = 1; o < W; o <<= 1) {
+    const int t = __shfl_up(s, o, W);
+    if (l >= o) s += t;
+  }
+  return s - v;
+}
+
+struct NeighbourArgs {
+  GridDims g;
+  long long n_face;
+  int chunk;                     // faces per wave, at most 64
+  const int32_t* fcode;
+  const int32_t* fref;
+  const GeomPtrs* geoms;
+  const int32_t* vol_id;
+  const int32_t* eb_id;
+  const int32_t* box_id;
+  const int64_t* counts;
+  const int64_t* offs;
+  const uint8_t* cellinfo;       // readable kInfoPad bytes before and after
+  const uint8_t* ballreg;
+  int32_t* nrows;
+  const int64_t* row_ptr;
+  int32_t* col;
+  int neumann;
+};
+
 template <int D, int R, bool FILL>
-__global__ __launch_bounds__(64) void k_neighbours(GridDims g, int G, long long n_face,
-                                                   const int32_t* __restrict__ fcode, const int32_t* __restrict__ fref,
-                                                   const GeomPtrs* __restrict__ geoms, const int32_t* __restrict__ vol_id,
-                                                   const int32_t* __restrict__ eb_id, const int32_t* __restrict__ face_id,
-                                                   const int32_t* __restrict__ box_id, const int64_t* __restrict__ counts,
-                                                   const int64_t* __restrict__ offs, const uint8_t* __restrict__ cellinfo,
-                                                   const uint8_t* __restrict__ ballreg, int32_t* nrows,
-                                                   const int64_t* __restrict__ row_ptr, int32_t* col, int neumann,
-                                                   unsigned long long* __restrict__ nbmask) {
+__global__ __launch_bounds__(64) void k_neighbours(NeighbourArgs A) {
   using W = Win<D, R>;
-  __shared__ int8_t dist[W::NW];
-  const long long F = blockIdx.x;
-  if (F >= n_face) return;
+  constexpr int LPF = W::LPF, KL = W::KL, FPW = W::FPW;
+  static_assert(W::EN <= 16 && W::EN <= kInfoPad, "a line's mask and its loads");
+  __shared__ unsigned cur[FPW][KL * LPF];
+  __shared__ int32_t stage[FILL ? FPW : 1][FILL ? kMaxRows : 1];
+  __shared__ int8_t list[64];
+  const GridDims& g = A.g;
   const int lane = threadIdx.x;
-  const int32_t code = fcode[F];
-  const int gi = code >> 4, kind = (code >> 2) & 3, dn = code & 3;
-  const int32_t ref = fref[F];
-  // a Neumann EB face's flux is its data: one row, its own Phi entry
-  if (kind == 1 && neumann) {
-    if (lane == 0) {
-      if (!FILL) nrows[F] = 1;
-      else col[row_ptr[F]] = (int32_t)(offs[gi] + counts[4 * gi + 0] + ref);
-    }
-    return;
-  }
+  const long long F0 = (long long)blockIdx.x * A.chunk;
+  const long long st1 = g.n[0], st2 = (long long)g.n[0] * g.n[1];
 
-  const int32_t* vid = vol_id + gi * g.ncell;
-  // fast path: a grid face between two ball-regular cells has the fixed L1-ball rows
-  if (kind == 0) {
-    int j[3];
-    lattice_coords(g, dn, ref, j);
-    if (j[dn] >= 1 && j[dn] <= g.n[dn] - 1) {
-      const long long b = cell_index(g, j);
-      const long long st[3] = {1, g.n[0], (long long)g.n[0] * g.n[1]};
-      const long long a = b - st[dn];
-      const uint8_t* reg = ballreg + (long long)gi * g.ncell;
-      if (reg[a] && reg[b]) {
-        constexpr auto& P = kRegularRows<D, R>;
-        if (!FILL) {
-          if (lane == 0) nrows[F] = P.n;
-          return;
-        }
-        const long long pos = row_ptr[F];
-        const int64_t phi0 = offs[gi];
-        for (int i = lane; i < P.n; i += 64) {
-          const long long c = a + P.off[dn][i][0] + st[1] * P.off[dn][i][1] + st[2] * P.off[dn][i][2];
-          col[pos + i] = (int32_t)(phi0 + vid[c]);
-        }
-        return;
+  // ---- the chunk's faces, one per lane ------------------------------------------------------
+  const bool have = lane < A.chunk && F0 + lane < A.n_face;
+  int32_t code = 0, ref = 0;
+  long long low = 0;               // regular faces: the low cell
+  bool regular = false, search = false;
+  int64_t pos0 = 0;
+  if (have) {
+    code = A.fcode[F0 + lane];
+    ref = A.fref[F0 + lane];
+    if (FILL) pos0 = A.row_ptr[F0 + lane];
+    const int gi = code >> 4, kind = (code >> 2) & 3, dn = code & 3;
+    search = true;
+    if (kind == 1 && A.neumann) {
+      // a Neumann EB face's flux is its data: one row, its own Phi entry
+      if (!FILL) A.nrows[F0 + lane] = 1;
+      else A.col[pos0] = (int32_t)(A.offs[gi] + A.counts[4 * gi + 0] + ref);
+      search = false;
+    } else if (kind == 0) {
+      // a grid face between two ball-regular cells has the fixed L1-ball rows
+      int j[3];
+      lattice_coords(g, dn, ref, j);
+      if (j[dn] >= 1 && j[dn] <= g.n[dn] - 1) {
+        const long long b = cell_index(g, j);
+        const uint8_t* reg = A.ballreg + (long long)gi * g.ncell;
+        low = b - (dn == 0 ? 1 : (dn == 1 ? st1 : st2));
+        regular = reg[low] && reg[b];
+        search = !regular;
       }
     }
   }
-  const int32_t* eid = eb_id + gi * g.ncell;
-  const int32_t* bid = box_id + gi * g.NF;
-
-  // window origin and extents; the adjacent cells sit at normal index R (and R + 1)
-  int org[3] = {0, 0, 0}, ext[3] = {1, 1, 1};
-  int nrm = dn;
-  if (kind == 0) {
-    int j[3];
-    lattice_coords(g, dn, ref, j);
-    for (int ax = 0; ax < D; ++ax) {
-      ext[ax] = (ax == dn) ? W::EN : W::ET;
-      org[ax] = (ax == dn) ? j[ax] - R - 1 : j[ax] - R;
-    }
+  constexpr auto& P = kRegularRows<D, R>;
+  if (!FILL) {
+    if (regular) A.nrows[F0 + lane] = P.n;
   } else {
-    const int32_t c = geoms[gi].eb_cell[ref];
-    int ci[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
-    nrm = 0;
-    for (int ax = 0; ax < D; ++ax) {
-      ext[ax] = (ax == 0) ? W::EN : W::ET;
-      org[ax] = ci[ax] - R;
-    }
-  }
-  const int NW = ext[0] * ext[1] * ext[2];
-
-  // the fill pass takes the rows the count pass found (its ballot masks, one word per 64
-  // window cells, at the face's own slot) instead of searching again
-  const bool reuse = FILL && nbmask;
-
-  // per-lane window cells: global cell, info byte (volume, open faces, EB); open bits
-  // are kept only toward neighbours inside the window and the box
-  const uint8_t* inf = cellinfo + (long long)gi * g.ncell;
-  long long cell[W::K];
-  bool isvol[W::K];
-  unsigned open[W::K];
-  unsigned info[W::K];
-  int wpos[W::K][3];
-  int xk[W::K][3];      // grid coordinates of the window cells
+    // the wave writes one regular face at a time, an entry (or more) per lane
+    constexpr int E = (P.n + 63) / 64;
+    int off[D][E];
 #pragma unroll
-  for (int k = 0; k < W::K; ++k) {
-    const int w = lane + 64 * k;
-    isvol[k] = false;
-    open[k] = 0;
-    info[k] = 0;
-    cell[k] = -1;
-    xk[k][0] = xk[k][1] = xk[k][2] = -1;
-    if (w >= NW) continue;
-    // window coordinates with compile-time divisors (the long extent is along nrm)
-    int wc[3];
-    if (nrm == 0) {
-      wc[0] = w % W::EN; wc[1] = (w / W::EN) % W::ET; wc[2] = w / (W::EN * W::ET);
-    } else if (nrm == 1) {
-      wc[0] = w % W::ET; wc[1] = (w / W::ET) % W::EN; wc[2] = w / (W::ET * W::EN);
-    } else {
-      wc[0] = w % W::ET; wc[1] = (w / W::ET) % W::ET; wc[2] = w / (W::ET * W::ET);
-    }
-    if (D == 2) wc[2] = 0;
-    int x[3];
-    bool inbox = true;
-    for (int ax = 0; ax < 3; ++ax) {
-      wpos[k][ax] = wc[ax];
-      x[ax] = org[ax] + wc[ax];
-      xk[k][ax] = x[ax];
-      if (ax < D && (x[ax] < 0 || x[ax] >= g.n[ax])) inbox = false;
-    }
-    if (!inbox) continue;
-    cell[k] = cell_index(g, x);
-    if (reuse) continue;   // rows from the count pass: no search
-    info[k] = inf[cell[k]];
-    isvol[k] = info[k] & 1u;
-    for (int ax = 0; ax < D; ++ax)
-      for (int s = 0; s < 2; ++s) {
-        const int wn = wc[ax] + (s ? 1 : -1);
-        const int xn = x[ax] + (s ? 1 : -1);
-        if (wn >= 0 && wn < ext[ax] && xn >= 0 && xn < g.n[ax] && ((info[k] >> (1 + 2 * ax + s)) & 1u))
-          open[k] |= 1u << (2 * ax + s);
+    for (int dn = 0; dn < D; ++dn)
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const int k = lane + 64 * i < P.n ? lane + 64 * i : 0;
+        off[dn][i] = (int)(P.off[dn][k][0] + st1 * P.off[dn][k][1] + st2 * P.off[dn][k][2]);
       }
-  }
-  bool inS[W::K];
-  if (reuse) {
-    const unsigned long long* mk = nbmask + F * W::K;
+    for (unsigned long long m = __ballot(regular); m != 0; m &= m - 1) {
+      const int l = __ffsll((long long)m) - 1;
+      const int cd = __builtin_amdgcn_readlane(code, l), dn = cd & 3, gi = cd >> 4;
+      const long long a = __builtin_amdgcn_readlane((int)low, l);   // fewer than 2^31 cells
+      const long long at = readlane_i64(pos0, l);
+      const int32_t* vid = A.vol_id + (long long)gi * g.ncell + a;
+      const int32_t phi0 = (int32_t)A.offs[gi];
 #pragma unroll
-    for (int k = 0; k < W::K; ++k) inS[k] = (mk[k] >> lane) & 1ull;
-  } else {
-  // distances: 0 at the adjacent volumes, R + 1 ("far") elsewhere
-#pragma unroll
-  for (int k = 0; k < W::K; ++k) {
-    const int w = lane + 64 * k;
-    if (w >= NW) continue;
-    bool adj = isvol[k];
-    for (int ax = 0; ax < D; ++ax) {
-      if (ax == nrm)
-        adj = adj && ((wpos[k][ax] == R) || (kind == 0 && wpos[k][ax] == R + 1));
-      else
-        adj = adj && (wpos[k][ax] == R);
+      for (int i = 0; i < E; ++i) {
+        int o = off[0][i];
+        if (dn == 1) o = off[1][i];
+        if (D == 3 && dn == 2) o = off[D - 1][i];
+        if (lane + 64 * i < P.n) A.col[at + lane + 64 * i] = phi0 + vid[o];
+      }
     }
-    dist[w] = adj ? 0 : (R + 1);
   }
+
+  // ---- the others, FPW at a time ---------------------------------------------------------------
+  const unsigned long long todo = __ballot(search);
+  const int ntodo = __popcll(todo);
+  if (search) list[__popcll(todo & lanes_below(lane))] = (int8_t)lane;
   __syncthreads();
-  for (int r = 1; r <= R; ++r) {
-    int8_t nd[W::K];
+  const int grp = lane / LPF, gl = lane & (LPF - 1);
+  for (int t0 = 0; t0 < ntodo; t0 += FPW) {
+    const bool on = t0 + grp < ntodo;
+    const int src = list[on ? t0 + grp : 0];
+    const int cd = __shfl(code, src), rf = __shfl(ref, src);
+    const int gi = cd >> 4, kind = (cd >> 2) & 3, dn = cd & 3;
+    const int nrm = kind == 0 ? dn : 0;
+    // window origin and extents; the adjacent cells sit at normal index R (and R + 1)
+    int org[3] = {0, 0, 0}, ext[3] = {1, 1, 1};
+    if (kind == 0) {
+      int j[3];
+      lattice_coords(g, dn, rf, j);
 #pragma unroll
-    for (int k = 0; k < W::K; ++k) {
-      const int w = lane + 64 * k;
-      nd[k] = -1;
-      if (w >= NW || !isvol[k] || dist[w] <= R) continue;
-      const int st[3] = {1, ext[0], ext[0] * ext[1]};
-      for (int ax = 0; ax < D; ++ax)
-        for (int s = 0; s < 2; ++s)
-          if ((open[k] >> (2 * ax + s)) & 1u) {
-            int wn = w + (s ? st[ax] : -st[ax]);
-            if (dist[wn] == r - 1) nd[k] = (int8_t)r;
-          }
+      for (int ax = 0; ax < D; ++ax) org[ax] = j[ax] - R - (ax == dn);
+    } else {
+      const int c = A.geoms[gi].eb_cell[rf];
+      org[0] = c % g.n[0] - R;
+      org[1] = (c / g.n[0]) % g.n[1] - R;
+      if (D == 3) org[2] = c / (g.n[0] * g.n[1]) - R;
     }
 #pragma unroll
-    for (int k = 0; k < W::K; ++k)
-      if (nd[k] > 0) dist[lane + 64 * k] = nd[k];
+    for (int ax = 0; ax < D; ++ax) ext[ax] = ax == nrm ? W::EN : W::ET;
+    const int nl = ext[1] * ext[2];
+    const uint8_t* inf = A.cellinfo + (long long)gi * g.ncell;
+    // bits of the line inside the box
+    const int xlo = org[0] < 0 ? -org[0] : 0, xhi = min(ext[0], g.n[0] - org[0]);
+    const unsigned xin = ((1u << xhi) - 1u) & ~((1u << xlo) - 1u);
+    unsigned vol[KL], ol[KL][D], oh[KL][D], eb[KL], S[KL];
+    int wy[KL], wz[KL];
+    long long line[KL];
+#pragma unroll
+    for (int k = 0; k < KL; ++k) {
+      const int li = gl + LPF * k;
+      wy[k] = li;
+      wz[k] = 0;
+      if (D == 3) {   // compile-time divisors: the long extent is along nrm
+        wy[k] = nrm == 1 ? li % W::EN : li % W::ET;
+        wz[k] = nrm == 1 ? li / W::EN : li / W::ET;
+      }
+      const int y = org[1] + wy[k], z = org[2] + wz[k];
+      const bool in = on && li < nl && y >= 0 && y < g.n[1] && z >= 0 && z < g.n[2];
+      line[k] = st2 * z + st1 * y + org[0];
+      vol[k] = eb[k] = S[k] = 0;
+#pragma unroll
+      for (int ax = 0; ax < D; ++ax) ol[k][ax] = oh[k][ax] = 0;
+      if (in) {
+        uint2 v, w;
+        __builtin_memcpy(&v, inf + line[k], 8);
+        if (W::EN > 8) __builtin_memcpy(&w, inf + line[k] + 8, 8);
+        auto plane = [&](int b) {
+          unsigned m = byte_plane(v, b);
+          if (W::EN > 8) m |= byte_plane(w, b) << 8;
+          return m & xin;
+        };
+        vol[k] = plane(0);
+        eb[k] = plane(7);
+#pragma unroll
+        for (int ax = 0; ax < D; ++ax) {
+          ol[k][ax] = plane(1 + 2 * ax);
+          oh[k][ax] = plane(2 + 2 * ax);
+        }
+        // the face's adjacent cells
+        unsigned m = 0;
+        if (nrm == 0) {
+          if (wy[k] == R && (D == 2 || wz[k] == R)) m = kind == 0 ? 3u << R : 1u << R;
+        } else if (nrm == 1) {
+          if ((wy[k] == R || wy[k] == R + 1) && (D == 2 || wz[k] == R)) m = 1u << R;
+        } else {
+          if (wy[k] == R && (wz[k] == R || wz[k] == R + 1)) m = 1u << R;
+        }
+        S[k] = m & vol[k];
+      }
+    }
+#pragma unroll 1
+    for (int r = 0; r < R; ++r) {
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < KL; ++k) cur[grp][gl + LPF * k] = S[k];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < KL; ++k) {
+        // a cell is reached through its own open face from a reached neighbour in the window
+        const int li = gl + LPF * k;
+        unsigned m = ((S[k] << 1) & ol[k][0]) | ((S[k] >> 1) & oh[k][0]);
+        if (wy[k] > 0 && li < nl) m |= cur[grp][li - 1] & ol[k][1];
+        if (wy[k] + 1 < ext[1] && li < nl) m |= cur[grp][li + 1] & oh[k][1];
+        if (D == 3) {
+          if (wz[k] > 0 && li < nl) m |= cur[grp][li - ext[1]] & ol[k][D - 1];
+          if (wz[k] + 1 < ext[2] && li < nl) m |= cur[grp][li + ext[1]] & oh[k][D - 1];
+        }
+        S[k] |= m;
+      }
+    }
+    // box faces of the reached cells, by direction and side
+    auto box_mask = [&](int k, int ax, int s) -> unsigned {
+      const unsigned m = S[k] & (s ? oh[k][ax] : ol[k][ax]);
+      const int at = s ? g.n[ax] - 1 : 0;
+      if (ax == 0) {
+        const int b = at - org[0];
+        return (b >= 0 && b < ext[0]) ? m & (1u << b) : 0u;
+      }
+      return (ax == 1 ? org[1] + wy[k] : org[2] + wz[k]) == at ? m : 0u;
+    };
+    if (!FILL) {
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < KL; ++k) {
+        c += __popc(S[k]) + __popc(S[k] & eb[k]);
+#pragma unroll
+        for (int ax = 0; ax < D; ++ax) c += __popc(box_mask(k, ax, 0)) + __popc(box_mask(k, ax, 1));
+      }
+      c = group_sum<LPF>(c);
+      if (on && gl == 0) A.nrows[F0 + src] = c;
+      continue;
+    }
+    // rows in ascending Phi order: volumes, EB faces, box faces by (d, side).  The ids of a
+    // line's volumes (and of its EB faces) are consecutive, so one load gives them all.
+    const int64_t* cnt = A.counts + 4 * gi;
+    const int32_t phi0 = (int32_t)A.offs[gi];
+    const int32_t* vid = A.vol_id + (long long)gi * g.ncell;
+    const int32_t* eid = A.eb_id + (long long)gi * g.ncell;
+    const int32_t* bid = A.box_id + (long long)gi * g.NF;
+    int n = 0;
+    auto put = [&](int k, unsigned m, auto&& entry) {
+      int p = n + group_before<LPF>(__popc(m));
+      n += group_sum<LPF>(__popc(m));
+      for (; m != 0; m &= m - 1) {
+        if (p < kMaxRows) stage[FILL ? grp : 0][FILL ? p : 0] = entry(__ffs(m) - 1);
+        ++p;
+      }
+    };
+#pragma unroll
+    for (int k = 0; k < KL; ++k) {
+      const int32_t v0 = vol[k] ? phi0 + vid[line[k] + __ffs(vol[k]) - 1] : 0;
+      put(k, S[k], [&](int b) { return v0 + __popc(vol[k] & ((1u << b) - 1u)); });
+    }
+#pragma unroll
+    for (int k = 0; k < KL; ++k) {
+      const unsigned m = S[k] & eb[k];
+      if (!__any(m != 0)) continue;
+      const int32_t e0 = m ? phi0 + (int32_t)cnt[0] + eid[line[k] + __ffs(eb[k]) - 1] : 0;
+      put(k, m, [&](int b) { return e0 + __popc(eb[k] & ((1u << b) - 1u)); });
+    }
+#pragma unroll
+    for (int ax = 0; ax < D; ++ax)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int k = 0; k < KL; ++k) {
+          const unsigned m = box_mask(k, ax, s);
+          if (!__any(m != 0)) continue;
+          put(k, m, [&](int b) {
+            int j[3] = {org[0] + b, org[1] + wy[k], org[2] + wz[k]};
+            j[ax] += s;
+            return phi0 + (int32_t)(cnt[0] + cnt[1]) + bid[lattice_index(g, ax, j)];
+          });
+        }
+    __syncthreads();
+    if (on) {
+      const long long at = __shfl(pos0, src);
+      for (int i = gl; i < n; i += LPF) A.col[at + i] = stage[FILL ? grp : 0][FILL ? i : 0];
+    }
     __syncthreads();
   }
-#pragma unroll
-  for (int k = 0; k < W::K; ++k) {
-    const int w = lane + 64 * k;
-    inS[k] = (w < NW) && isvol[k] && dist[w] <= R;
-  }
-  }
-
-  const int64_t* cnt = counts + 4 * gi;
-  const int64_t phi0 = offs[gi];
-  if (!FILL) {
-    int c = 0;
-#pragma unroll
-    for (int k = 0; k < W::K; ++k) {
-      if (!inS[k]) continue;
-      c += 1 + (int)(info[k] >> 7);
-      const int* x = xk[k];
-      for (int ax = 0; ax < D; ++ax)
-        for (int s = 0; s < 2; ++s)
-          if (x[ax] == (s ? g.n[ax] - 1 : 0) && ((info[k] >> (1 + 2 * ax + s)) & 1u)) c += 1;   // box face
-    }
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-    if (lane == 0) nrows[F] = c;
-    if (nbmask) {   // leave the rows for the fill pass
-      unsigned long long* mk = nbmask + F * W::K;
-#pragma unroll
-      for (int k = 0; k < W::K; ++k) {
-        const unsigned long long m = __ballot(inS[k]);
-        if (lane == k) mk[k] = m;
-      }
-    }
-    return;
-  }
-  // fill in ascending Phi order: volumes, EB faces, box faces by (d, side)
-  long long pos = row_ptr[F];
-  const unsigned long long below = lanes_below(lane);
-#pragma unroll
-  for (int k = 0; k < W::K; ++k) {
-    bool p = inS[k];
-    unsigned long long m = __ballot(p);
-    if (p) col[pos + __popcll(m & below)] = (int32_t)(phi0 + vid[cell[k]]);
-    pos += __popcll(m);
-  }
-#pragma unroll
-  for (int k = 0; k < W::K; ++k) {
-    bool p = inS[k] && eid[cell[k]] >= 0;
-    unsigned long long m = __ballot(p);
-    if (p) col[pos + __popcll(m & below)] = (int32_t)(phi0 + cnt[0] + eid[cell[k]]);
-    pos += __popcll(m);
-  }
-  for (int ax = 0; ax < D; ++ax)
-    for (int s = 0; s < 2; ++s) {
-#pragma unroll
-      for (int k = 0; k < W::K; ++k) {
-        int32_t b = -1;
-        if (inS[k]) {
-          const int* x = xk[k];
-          if (x[ax] == (s ? g.n[ax] - 1 : 0)) {
-            int j[3] = {x[0], x[1], x[2]};
-            j[ax] += s;
-            b = bid[lattice_index(g, ax, j)];
-          }
-        }
-        bool p = b >= 0;
-        unsigned long long m = __ballot(p);
-        if (p) col[pos + __popcll(m & below)] = (int32_t)(phi0 + cnt[0] + cnt[1] + b);
-        pos += __popcll(m);
-      }
-    }
 }
 
 template <int D, int R>
 static void launch_neighbours(const Work& w, long long n_face, const int64_t* row_ptr, int32_t* col, bool fill,
                               int neumann, hipStream_t st) {
-  // the count pass leaves each searched face's rows (as ballot masks) for the fill pass
-  if (fill)
-    hipLaunchKernelGGL((k_neighbours<D, R, true>), dim3((unsigned)n_face), dim3(64), 0, st, w.dims, w.G, n_face,
-                       w.fcode, w.fref, w.geoms, w.vol_id, w.eb_id, w.face_id, w.box_id, w.counts, w.offs, w.cellinfo,
-                       w.ballreg, w.nrows, row_ptr, col, neumann, w.nbmask);
-  else
-    hipLaunchKernelGGL((k_neighbours<D, R, false>), dim3((unsigned)n_face), dim3(64), 0, st, w.dims, w.G, n_face,
-                       w.fcode, w.fref, w.geoms, w.vol_id, w.eb_id, w.face_id, w.box_id, w.counts, w.offs, w.cellinfo,
-                       w.ballreg, w.nrows, row_ptr, col, neumann, w.nbmask);
+  NeighbourArgs A{w.dims, n_face, 64, w.fcode, w.fref, w.geoms, w.vol_id, w.eb_id, w.box_id, w.counts, w.offs,
+                  w.cellinfo, w.ballreg, w.nrows, row_ptr, col, neumann};
+  // a chunk of 64 faces hides most latency; smaller chunks where that would leave the chip
+  // short of waves (8 per SIMD)
+  while (A.chunk > Win<D, R>::FPW && n_face / A.chunk < 8192) A.chunk /= 2;
+  const dim3 grid((unsigned)((n_face + A.chunk - 1) / A.chunk)), block(64);
+  if (fill) hipLaunchKernelGGL((k_neighbours<D, R, true>), grid, block, 0, st, A);
+  else hipLaunchKernelGGL((k_neighbours<D, R, false>), grid, block, 0, st, A);
 }
 
 int neighbour_rows(const Work& w, const cutcell_opts& o, long long n_face, const int64_t* row_ptr, int32_t* col,

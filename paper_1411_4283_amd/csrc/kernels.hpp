@@ -13,6 +13,7 @@ constexpr int kBinRows = 16;
 constexpr int kMaxRows = kMaxBins * kBinRows;
 constexpr int kNBuckets = kMaxBins + 2;   // then faces with N < M, then template copies
 constexpr int kBinWords = 2 * kNBuckets + 1;       // counts, cursors, max rows
+constexpr int kInfoPad = 32;    // bytes of padding of cellinfo on either side
 constexpr int kXcds = 8;        // MI355X: workgroups are dealt to 8 XCDs (own L2 each) in turn
 constexpr int kQrSlots = 1024;  // workgroups of the QR path, each with a slot of workspace
 
@@ -32,7 +33,8 @@ struct Work {
   int32_t* box_id;      // [G][NF]     local box-face index or -1
   int32_t* box_lf;      // [G][nboxslot] lattice face of each local box face
   int32_t* vol_cell;    // [G][ncell]  cell of each local volume
-  uint8_t* cellinfo;    // [G][ncell]  volume / open-face / EB bits for the neighbour search
+  uint8_t* cellinfo;    // [G][ncell]  volume / open-face / EB bits for the neighbour search, kInfoPad
+                        //             more bytes on either side (its lines are read in eights)
   uint8_t* ballreg;     // [G][ncell]  1: every cell within path radius is a plain interior volume
   uint8_t* ballreg_tmp; // [G][ncell]  erosion ping-pong buffer
   uint8_t* canon;       // [G][ncell]  1: every cell within path radius has the reference moments
@@ -57,7 +59,6 @@ struct Work {
   int32_t* qr_count;    // [1] faces left to the Householder QR path
   int32_t* qr_list;     // [G*maxface] those faces
   double* qr_b;         // [qr_slots][2][kMaxRows * MS] the QR path's exact B per workgroup
-  unsigned long long* nbmask;  // [G*maxface][window words] rows the count pass found (searched faces)
   int qr_slots;         // min(kQrSlots, G*maxface)
   GeomPtrs* geoms;      // [G]
   size_t bytes;
