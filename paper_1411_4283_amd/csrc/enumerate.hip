@@ -583,8 +583,8 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighbourArgs A) {
           });
         }
     __syncthreads();
+    const long long at = __shfl(pos0, src);   // by every lane: one that is off gives nothing away
     if (on) {
-      const long long at = __shfl(pos0, src);
       for (int i = gl; i < n; i += LPF) A.col[at + i] = stage[FILL ? grp : 0][FILL ? i : 0];
     }
     __syncthreads();

@@ -40,3 +40,23 @@ def test_rows_of_every_face(D, R, n, shape, bc):
             ref = np.array([en.n_vol + f - first_eb])
         assert np.array_equal(col[rp[f]:rp[f + 1]], ref), f
     print(f"[gpu] D{D} R{R} n{n}: {en.n_face} faces, {np.diff(rp).min()}..{np.diff(rp).max()} rows")
+
+
+@pytest.mark.parametrize("D,R,n", [(2, 2, 460), (2, 3, 640), (3, 2, 60), (3, 1, 64)])
+def test_rows_where_a_wave_takes_many_faces(D, R, n):
+    """Grids with so many faces that a wave takes chunks of 32 or 64 of them, several at a
+    time: all faces of seeded stretches of 64 and of the last ones, and every face's count
+    through the row pointers of a build (rows ascending, in range)."""
+    g = cg.make_geometry(cg.ball_outside((0.48, 0.53, 0.51)[:D], 0.31), n, 2)
+    st = cc.Builder(cc.DeviceGeometry.from_host(g, "cuda"), R).build()
+    en = oracle.enumerate_geometry(g)
+    rp, col, _, _ = _host(st)
+    assert st.sizes.n_face == en.n_face and en.n_face > 262144
+    inner = np.ones(len(col), bool)
+    inner[rp[:-1]] = False
+    assert col.min() >= 0 and col.max() < st.sizes.n_phi
+    assert np.all(np.diff(col.astype(np.int64))[inner[1:]] > 0)
+    starts = 64 * np.random.default_rng(n).choice(en.n_face // 64, 25, replace=False)
+    eb = np.arange(en.n_face - en.n_eb, en.n_face)
+    for f in np.concatenate([*(np.arange(a, a + 64) for a in starts), eb[:64], eb[-64:]]):
+        assert np.array_equal(col[rp[f]:rp[f + 1]], oracle.neighbours(en, int(f), R)), f
