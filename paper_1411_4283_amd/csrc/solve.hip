@@ -4,9 +4,7 @@
 // L is affine in the volume values x:  L([x | bc]) = A x + L([0 | bc]).  Restarted GMRES(m)
 // solves A x = f - L([0 | bc]) with right Jacobi preconditioning (A D^-1 y = b, x = D^-1 y,
 // D = diag A).  Every vector operation is a kernel here; the host keeps only the small
-// Hessenberg matrix and its Givens rotations.  Orthogonalisation is classical Gram-Schmidt
-// done twice (CGS2): one batched inner-product kernel and one batched update per pass.
-// All reductions sum per-block partials in a fixed order, so a solve is deterministic.
+// Hessenberg matrix and its Givens rotations.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -17,8 +15,7 @@
 
 namespace cutcell {
 
-constexpr int kDotBlock = 256;
-constexpr int kDotBlocks = 512;      // fixed number of partial sums per inner product
+constexpr int kBatch = 8;            // Arnoldi steps launched before the host reads their coefficients
 
 static inline unsigned nb(long long n, int t) { return (unsigned)((n + t - 1) / t); }
 
@@ -53,11 +50,6 @@ __global__ void k_axpby(long long n, double alpha, const double* a, double beta,
   if (i < n) out[i] = alpha * a[i] + beta * b[i];
 }
 
-__global__ void k_mul(long long n, const double* __restrict__ a, const double* __restrict__ b, double* __restrict__ out) {
-  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i < n) out[i] = a[i] * b[i];
-}
-
 // D^-1: A_vv = vol_scale[v] * sum over v's faces of sigma * (the face's coefficient on v)
 template <int D>
 __global__ void k_jacobi(long long n_vol, const int32_t* __restrict__ vol_face, const double* __restrict__ vol_scale,
@@ -85,100 +77,292 @@ __global__ void k_jacobi(long long n_vol, const int32_t* __restrict__ vol_face, 
   dinv[v] = (a != 0.0 && isfinite(a)) ? 1.0 / a : 1.0;
 }
 
-// partial[i][b] = block b's share of V_i . w for i < k, and of w . w as entry k when
-// `self` (V row-major [k][n]).  Eight products per pass over w; each is summed per thread
-// in a fixed order, across the wave by butterfly shuffles, then over the block's waves.
-constexpr int kChunk = 8;
-__global__ __launch_bounds__(kDotBlock) void k_mdot(long long n, int k, int self, const double* __restrict__ V,
-                                                     const double* __restrict__ w, double* __restrict__ partial) {
-  __shared__ double red[kDotBlock / 64][kChunk];
+// ---- Arnoldi step -------------------------------------------------------------------------
+// Classical Gram-Schmidt done twice in three launches: the inner products V^T w (k_dots), the
+// first update of w with the inner products of the result (k_orth), the second update, the
+// norm and the next vector together with the Phi that the next product reads (k_next).  A
+// vector is cut into tiles of 256 E elements, a block takes one (or, past kMaxTiles, every
+// kMaxTiles-th), and leaves a partial sum per inner product; the launch that needs the sums
+// adds the partials itself, block by block alike and in a fixed order, so no launch or copy
+// stands between two of them and a solve is deterministic.  Coefficients stay on the device
+// (a column of H per step); the host reads the columns of several steps at once.  At 30k
+// volumes (32^3, 3D order 4) a step is bound by the latency of its dependent launches and of
+// the loads in each: eleven launches, a copy and a wait took 88 to 100 us, four launches take
+// 41 (15 of them the product).
+constexpr int kTileThreads = 256;
+constexpr int kMaxTiles = 512;
+constexpr int kDotChunk = 8;         // vectors per block of k_dots
+
+// elements per thread: the least that leaves at most 256 tiles (8 at most)
+static inline int tile_elems(long long n) {
+  int e = 1;
+  while (e < 8 && n > 256LL * kTileThreads * e) e *= 2;
+  return e;
+}
+static inline int tile_count(long long n) {
+  const long long t = (long long)kTileThreads * tile_elems(n);
+  return (int)std::max<long long>(1, std::min<long long>(kMaxTiles, (n + t - 1) / t));
+}
+
+// partial[b][i] = block b's share of V_i . w for i < k (V row-major [k][n]; rows of ld partials)
+template <int E>
+__global__ __launch_bounds__(kTileThreads) void k_dots(long long n, int k, const double* __restrict__ V,
+                                                       const double* __restrict__ w, double* __restrict__ partial,
+                                                       int ld) {
+  __shared__ double red[kTileThreads / 64][kDotChunk];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int kk = k + (self ? 1 : 0);
-  for (int i0 = 0; i0 < kk; i0 += kChunk) {
-    double acc[kChunk];
+  const int i0 = blockIdx.y * kDotChunk;
+  double acc[kDotChunk];
 #pragma unroll
-    for (int u = 0; u < kChunk; ++u) acc[u] = 0.0;
-    for (long long t = blockIdx.x * (long long)kDotBlock + threadIdx.x; t < n; t += (long long)kDotBlocks * kDotBlock) {
-      const double wt = w[t];
+  for (int u = 0; u < kDotChunk; ++u) acc[u] = 0.0;
+  for (long long t0 = (long long)blockIdx.x * kTileThreads * E; t0 < n; t0 += (long long)gridDim.x * kTileThreads * E)
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        const int i = i0 + u;
-        if (i < k) acc[u] = fma(V[(long long)i * n + t], wt, acc[u]);
-        else if (i == k && self) acc[u] = fma(wt, wt, acc[u]);
+    for (int e = 0; e < E; ++e) {
+      const long long t = t0 + threadIdx.x + e * kTileThreads;
+      if (t < n) {
+        const double wt = w[t];
+#pragma unroll
+        for (int u = 0; u < kDotChunk; ++u)
+          if (i0 + u < k) acc[u] = fma(V[(long long)(i0 + u) * n + t], wt, acc[u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < kChunk; ++u)
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) acc[u] += __shfl_xor(acc[u], off, 64);
-    if (lane == 0)
-#pragma unroll
-      for (int u = 0; u < kChunk; ++u) red[wv][u] = acc[u];
+  for (int u = 0; u < kDotChunk; ++u) {
+    const double s = wave_sum_f64(acc[u]);
+    if (lane == 0) red[wv][u] = s;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < kDotChunk && i0 + (int)threadIdx.x < k) {
+    double s = 0.0;
+    for (int q = 0; q < kTileThreads / 64; ++q) s += red[q][threadIdx.x];
+    partial[(long long)blockIdx.x * ld + i0 + threadIdx.x] = s;
+  }
+}
+
+// out[i] = sum over the nt blocks of partial[b][i] for i < k, in shared memory: a lane per sum,
+// every fourth block in a wave, eight loads in flight, then the waves' sums in order
+__device__ __forceinline__ void sum_partials(const double* __restrict__ partial, int ld, int nt, int k, double* out) {
+  constexpr int NW = kTileThreads / 64;
+  __shared__ double part[NW][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const int i = i0 + lane;
+    double s = 0.0;
+    if (i < k) {
+#pragma unroll 8
+      for (int b = wv; b < nt; b += NW) s += partial[(long long)b * ld + i];
+    }
+    part[wv][lane] = s;
     __syncthreads();
-    if ((int)threadIdx.x < kChunk) {
-      double sum = 0.0;
-      for (int q = 0; q < kDotBlock / 64; ++q) sum += red[q][threadIdx.x];
-      const int i = i0 + threadIdx.x;
-      if (i < kk) partial[(long long)i * kDotBlocks + blockIdx.x] = sum;
+    if (wv == 0 && i < k) {
+      double t = part[0][lane];
+      for (int q = 1; q < NW; ++q) t += part[q][lane];
+      out[i] = t;
     }
     __syncthreads();
   }
 }
 
-// out[i] = sum of partial[i][0..kDotBlocks) in a fixed order (one block per i)
-__global__ __launch_bounds__(kDotBlock) void k_mdot_final(const double* __restrict__ partial, double* __restrict__ out) {
-  __shared__ double red[kDotBlock];
-  const int i = blockIdx.x;
-  double s = 0.0;
-  for (int b = threadIdx.x; b < kDotBlocks; b += kDotBlock) s += partial[(long long)i * kDotBlocks + b];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = kDotBlock / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-    __syncthreads();
+// c1 = V^T w from its partials; w -= V c1; then the partials of V^T w and, as entry k, w . w
+template <int E>
+__global__ __launch_bounds__(kTileThreads) void k_orth(long long n, int k, const double* __restrict__ V,
+                                                       double* __restrict__ w, const double* __restrict__ partial,
+                                                       int ld, double* __restrict__ c1,
+                                                       double* __restrict__ partial2) {
+  extern __shared__ double sh[];
+  double* cs = sh;                      // [k]
+  double* acc = sh + k;                 // [waves][k + 1]
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  sum_partials(partial, ld, gridDim.x, k, cs);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < k; i += kTileThreads) c1[i] = cs[i];
+  double* mine = acc + wv * (k + 1);
+  bool first = true;
+  for (long long t0 = (long long)blockIdx.x * kTileThreads * E; t0 < n; t0 += (long long)gridDim.x * kTileThreads * E) {
+    double x[E];
+    const double* p = V + t0 + threadIdx.x;
+    bool in[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      in[e] = t0 + threadIdx.x + e * kTileThreads < n;
+      x[e] = in[e] ? w[t0 + threadIdx.x + e * kTileThreads] : 0.0;
+    }
+#pragma unroll 8
+    for (int i = 0; i < k; ++i)
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = fma(-cs[i], in[e] ? p[(long long)i * n + e * kTileThreads] : 0.0, x[e]);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (in[e]) w[t0 + threadIdx.x + e * kTileThreads] = x[e];
+    for (int i0 = 0; i0 <= k; i0 += 8) {
+      double a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int i = i0 + u;
+        a[u] = 0.0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const double v = i < k ? (in[e] ? p[(long long)i * n + e * kTileThreads] : 0.0) : (i == k ? x[e] : 0.0);
+          a[u] = fma(v, x[e], a[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        a[u] = wave_sum_f64(a[u]);
+        if (lane == 0 && i0 + u <= k) mine[i0 + u] = first ? a[u] : mine[i0 + u] + a[u];
+      }
+    }
+    first = false;
   }
-  if (threadIdx.x == 0) out[i] = red[0];
+  if (first && lane == 0)
+    for (int i = 0; i <= k; ++i) mine[i] = 0.0;
+  __syncthreads();
+  for (int i = threadIdx.x; i <= k; i += kTileThreads) {
+    double s = 0.0;
+    for (int q = 0; q < kTileThreads / 64; ++q) s += acc[q * (k + 1) + i];
+    partial2[(long long)blockIdx.x * ld + i] = s;
+  }
 }
 
-// After the second Gram-Schmidt pass: d holds its coefficients c[0..k) and, in d[k], the
-// squared norm of the vector it started from, so the new norm is sqrt(d[k] - |c|^2) (c is
-// at rounding level after the first pass).  hn[0] = norm, hn[1] = 1/norm (0 if the norm
-// vanishes: a lucky breakdown).
-__global__ void k_norm_after(const double* __restrict__ d, int k, double* __restrict__ hn) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// The second pass: d = V^T w and w . w from their partials.  The coefficients are at rounding
+// level after the first pass, so the new norm is sqrt(w . w - |d|^2).  v_next = (w - V d) /
+// norm (0 if the norm vanishes: a lucky breakdown), phi = D^-1 v_next at the volumes (or
+// v_next without dinv), and the column of H: c1 + d, then the norm.
+template <int E>
+__global__ __launch_bounds__(kTileThreads) void k_next(long long n, int k, const double* __restrict__ V,
+                                                       const double* __restrict__ w,
+                                                       const double* __restrict__ partial2, int ld,
+                                                       const double* __restrict__ c1, double* __restrict__ hcol,
+                                                       const double* __restrict__ dinv,
+                                                       const int32_t* __restrict__ vphi, double* __restrict__ vnext,
+                                                       double* __restrict__ phi) {
+  extern __shared__ double sh[];        // [k + 1]
+  sum_partials(partial2, ld, gridDim.x, k + 1, sh);
   double c2 = 0.0;
-  for (int i = 0; i < k; ++i) c2 = fma(d[i], d[i], c2);
-  const double q = d[k] - c2;
-  const double r = q > 0.0 ? sqrt(q) : 0.0;
-  hn[0] = r;
-  hn[1] = r > 0.0 ? 1.0 / r : 0.0;
+  for (int i = 0; i < k; ++i) c2 = fma(sh[i], sh[i], c2);
+  const double q = sh[k] - c2;
+  const double norm = q > 0.0 ? sqrt(q) : 0.0;
+  const double inv = norm > 0.0 ? 1.0 / norm : 0.0;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < k; i += kTileThreads) hcol[i] = c1[i] + sh[i];
+    if (threadIdx.x == 0) hcol[k] = norm;
+  }
+  for (long long t0 = (long long)blockIdx.x * kTileThreads * E; t0 < n; t0 += (long long)gridDim.x * kTileThreads * E) {
+    double x[E];
+    const double* p = V + t0 + threadIdx.x;
+    bool in[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      in[e] = t0 + threadIdx.x + e * kTileThreads < n;
+      x[e] = in[e] ? w[t0 + threadIdx.x + e * kTileThreads] : 0.0;
+    }
+#pragma unroll 8
+    for (int i = 0; i < k; ++i)
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = fma(-sh[i], in[e] ? p[(long long)i * n + e * kTileThreads] : 0.0, x[e]);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (in[e]) {
+        const long long t = t0 + threadIdx.x + e * kTileThreads;
+        const double v = x[e] * inv;
+        vnext[t] = v;
+        phi[vphi[t]] = dinv ? dinv[t] * v : v;
+      }
+  }
 }
 
-// out = s[1] * w (s on the device)
-__global__ void k_scale_dev(long long n, const double* __restrict__ w, const double* __restrict__ sc,
-                            double* __restrict__ out) {
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t < n) out[t] = w[t] * sc[1];
-}
-
-// w -= sum_{i<k} c[i] V_i
-__global__ void k_maxpy(long long n, int k, const double* __restrict__ c, const double* __restrict__ V,
-                        double* __restrict__ w) {
+// v *= s; phi = D^-1 v at the volumes (or v without dinv)
+__global__ void k_first(long long n, double s, double* __restrict__ v, const double* __restrict__ dinv,
+                        const int32_t* __restrict__ vphi, double* __restrict__ phi) {
   const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (t >= n) return;
-  double s = w[t];
-  for (int i = 0; i < k; ++i) s = fma(-c[i], V[i * n + t], s);
-  w[t] = s;
+  const double x = v[t] * s;
+  v[t] = x;
+  phi[vphi[t]] = dinv ? dinv[t] * x : x;
 }
 
-static inline size_t coef_words(int m) { return (size_t)(m + 1) + (m + 2) + 2; }   // pass 1 | pass 2 | norm
+// x += D^-1 sum_{i<k} c[i] V_i
+__global__ void k_update(long long n, int k, const double* __restrict__ c, const double* __restrict__ V,
+                         const double* __restrict__ dinv, double* __restrict__ x) {
+  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  double s = 0.0;
+#pragma unroll 4
+  for (int i = 0; i < k; ++i) s = fma(c[i], V[i * n + t], s);
+  x[t] = fma(dinv[t], s, x[t]);
+}
+
+// The buffers of an Arnoldi process of at most m steps, and its launches.
+struct Arnoldi {
+  long long n;
+  int m, tiles, elems;
+  double* V;          // [m + 1][n]
+  double* w;          // [n]
+  double* partial;    // [tiles][m + 1]
+  double* partial2;   // [tiles][m + 1]
+  double* c1;         // [m]
+  double* H;          // [m][m + 1] columns
+  hipStream_t st;
+
+  static size_t bytes(long long n, int m) {
+    auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+    const size_t nv = std::max<long long>(n, 1), nt = tile_count(n);
+    return al(sizeof(double) * nv * (m + 1)) + al(sizeof(double) * nv) + al(sizeof(double) * nt * (m + 1)) +
+           al(sizeof(double) * nt * (m + 1)) + al(sizeof(double) * m) + al(sizeof(double) * m * (m + 1));
+  }
+  template <class Take>
+  void layout(long long n_, int m_, hipStream_t s, Take&& take) {
+    n = n_;
+    m = m_;
+    st = s;
+    tiles = tile_count(n);
+    elems = tile_elems(n);
+    const size_t nv = std::max<long long>(n, 1);
+    V = (double*)take(sizeof(double) * nv * (m + 1));
+    w = (double*)take(sizeof(double) * nv);
+    partial = (double*)take(sizeof(double) * tiles * (m + 1));
+    partial2 = (double*)take(sizeof(double) * tiles * (m + 1));
+    c1 = (double*)take(sizeof(double) * m);
+    H = (double*)take(sizeof(double) * m * (m + 1));
+  }
+  // w holds A v_j: v_{j+1}, phi and column j of H
+  template <int E>
+  void step_e(int j, const double* dinv, const int32_t* vphi, double* phi) const {
+    const int k = j + 1;
+    const dim3 T(kTileThreads);
+    hipLaunchKernelGGL(k_dots<E>, dim3(tiles, (k + kDotChunk - 1) / kDotChunk), T, 0, st, n, k, V, w, partial, m + 1);
+    hipLaunchKernelGGL(k_orth<E>, dim3(tiles), T, sizeof(double) * (k + (kTileThreads / 64) * (k + 1)), st, n, k, V, w,
+                       partial, m + 1, c1, partial2);
+    hipLaunchKernelGGL(k_next<E>, dim3(tiles), T, sizeof(double) * (k + 1), st, n, k, V, w, partial2, m + 1, c1,
+                       H + (size_t)j * (m + 1), dinv, vphi, V + (long long)k * n, phi);
+  }
+  void step(int j, const double* dinv, const int32_t* vphi, double* phi) const {
+    if (elems == 1) step_e<1>(j, dinv, vphi, phi);
+    else if (elems == 2) step_e<2>(j, dinv, vphi, phi);
+    else if (elems == 4) step_e<4>(j, dinv, vphi, phi);
+    else step_e<8>(j, dinv, vphi, phi);
+  }
+  // |y| to the host
+  int norm(const double* y, double* out) const {
+    if (elems == 1) hipLaunchKernelGGL(k_dots<1>, dim3(tiles), dim3(kTileThreads), 0, st, n, 1, y, y, partial2, 1);
+    else if (elems == 2) hipLaunchKernelGGL(k_dots<2>, dim3(tiles), dim3(kTileThreads), 0, st, n, 1, y, y, partial2, 1);
+    else if (elems == 4) hipLaunchKernelGGL(k_dots<4>, dim3(tiles), dim3(kTileThreads), 0, st, n, 1, y, y, partial2, 1);
+    else hipLaunchKernelGGL(k_dots<8>, dim3(tiles), dim3(kTileThreads), 0, st, n, 1, y, y, partial2, 1);
+    double p[kMaxTiles];
+    CC_HIP(hipMemcpyAsync(p, partial2, sizeof(double) * tiles, hipMemcpyDeviceToHost, st));
+    CC_HIP(hipStreamSynchronize(st));
+    double s = 0.0;
+    for (int b = 0; b < tiles; ++b) s += p[b];
+    *out = std::sqrt(s);
+    return CUTCELL_OK;
+  }
+};
 
 size_t solve_workspace_bytes(long long n_vol, long long n_phi, long long n_face, int m) {
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t nv = std::max<long long>(n_vol, 1);
   return al(sizeof(double) * n_phi) * 2 + al(sizeof(double) * std::max<long long>(n_face, 1)) +
-         al(sizeof(double) * nv) * 5 + al(sizeof(int32_t) * nv) + al(sizeof(double) * nv * (m + 1)) +
-         al(sizeof(double) * kDotBlocks * (m + 2)) + al(sizeof(double) * coef_words(m)) + al(sizeof(double) * (m + 1));
+         al(sizeof(double) * nv) * 3 + al(sizeof(int32_t) * nv) + al(sizeof(double) * m) + Arnoldi::bytes(n_vol, m);
 }
 
 int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_t* vol_off, const double* phi_bc,
@@ -191,24 +375,17 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = ws + off; off += al(bytes); return p; };
   const size_t nv = std::max<long long>(n, 1);
-  double* phi = (double*)take(sizeof(double) * op.n_phi);     // [x | bc]
+  hipStream_t st = op.st;
+  double* phi = (double*)take(sizeof(double) * op.n_phi);     // [0 | bc]
   double* phi0 = (double*)take(sizeof(double) * op.n_phi);    // [v | 0]
   double* flux = (double*)take(sizeof(double) * std::max<long long>(op.n_face, 1));
   double* b = (double*)take(sizeof(double) * nv);
-  double* w = (double*)take(sizeof(double) * nv);
-  double* z = (double*)take(sizeof(double) * nv);
   double* dinv = (double*)take(sizeof(double) * nv);
   double* tmp = (double*)take(sizeof(double) * nv);
   int32_t* vphi = (int32_t*)take(sizeof(int32_t) * nv);
-  double* V = (double*)take(sizeof(double) * nv * (m + 1));
-  double* partial = (double*)take(sizeof(double) * kDotBlocks * (m + 2));
-  double* cbuf = (double*)take(sizeof(double) * coef_words(m));   // pass-1 | pass-2 coefficients | norm
-  double* coef = (double*)take(sizeof(double) * (m + 1));
-  double* c1 = cbuf;
-  double* c2 = cbuf + (m + 1);
-  double* hnb = cbuf + (m + 1) + (m + 2);
-  std::vector<double> hc(coef_words(m));
-  hipStream_t st = op.st;
+  double* coef = (double*)take(sizeof(double) * m);
+  Arnoldi A;
+  A.layout(n, m, st, take);
   const int T = 256;
   const unsigned gv = nb(n, T);
 
@@ -217,30 +394,13 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
     return apply_operator(op.D, op.n_face, n, op.row_ptr, op.col, op.val, op.vol_face, op.vol_scale, p, out, flux,
                           nullptr, st);
   };
-  // A v = L([v | 0])
-  auto matvec = [&](const double* v, double* out) {
-    hipLaunchKernelGGL(k_scatter, dim3(gv), dim3(T), 0, st, n, vphi, v, phi0);
-    return apply(phi0, out);
-  };
-  // V^T y (k vectors) and, with self, y.y as entry k, into out on the device
-  auto mdot = [&](int k, int self, const double* y, double* out) {
-    hipLaunchKernelGGL(k_mdot, dim3(kDotBlocks), dim3(kDotBlock), 0, st, n, k, self, V, y, partial);
-    hipLaunchKernelGGL(k_mdot_final, dim3(k + self), dim3(kDotBlock), 0, st, partial, out);
-  };
-  // ||y||^2 read back to the host
-  auto norm2 = [&](const double* y, double* out) {
-    mdot(0, 1, y, hnb);
-    CC_HIP(hipMemcpyAsync(out, hnb, sizeof(double), hipMemcpyDeviceToHost, st));
-    CC_HIP(hipStreamSynchronize(st));
-    return (int)CUTCELL_OK;
-  };
 
   hipLaunchKernelGGL(k_vol_phi, dim3(gv), dim3(T), 0, st, n, G, phi_off, vol_off, vphi);
   hipLaunchKernelGGL(k_copy, dim3(nb(op.n_phi, T)), dim3(T), 0, st, op.n_phi, phi_bc, phi);
   hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, phi0, op.n_phi, 0.0);
-  hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, z, n, 0.0);
+  hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, tmp, n, 0.0);
   // b = f - L([0 | bc])
-  hipLaunchKernelGGL(k_scatter, dim3(gv), dim3(T), 0, st, n, vphi, z, phi);
+  hipLaunchKernelGGL(k_scatter, dim3(gv), dim3(T), 0, st, n, vphi, tmp, phi);
   int rc = apply(phi, tmp);
   if (rc) return rc;
   hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0, f, -1.0, tmp, b);
@@ -250,10 +410,9 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
   else
     hipLaunchKernelGGL(k_jacobi<2>, dim3(gv), dim3(T), 0, st, n, op.vol_face, op.vol_scale, op.row_ptr, op.col,
                        op.val, vphi, dinv);
-  double nb2 = 0.0;
-  rc = norm2(b, &nb2);
+  double bnorm = 0.0;
+  rc = A.norm(b, &bnorm);
   if (rc) return rc;
-  const double bnorm = std::sqrt(nb2);
   if (!std::isfinite(bnorm)) return fail(CUTCELL_E_INVALID_ARG, "non-finite right-hand side or boundary data");
   if (bnorm == 0.0) {               // the solution is x = 0
     hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, x, n, 0.0);
@@ -264,75 +423,68 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
   }
   int it = 0;
   double res = bnorm;
-  std::vector<double> H((m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
+  std::vector<double> H((size_t)m * m), cs(m), sn(m), g(m + 1), y(m), hc((size_t)kBatch * (m + 1));
   for (;;) {
     // r = b - A x; the exit test always uses this true residual
-    rc = matvec(x, tmp);
+    hipLaunchKernelGGL(k_scatter, dim3(gv), dim3(T), 0, st, n, vphi, x, phi0);
+    rc = apply(phi0, tmp);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0, b, -1.0, tmp, V);
-    double r2 = 0.0;
-    rc = norm2(V, &r2);
+    hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0, b, -1.0, tmp, A.V);
+    double beta = 0.0;
+    rc = A.norm(A.V, &beta);
     if (rc) return rc;
-    const double beta = std::sqrt(r2);
     res = beta;
     if (!(beta > rtol * bnorm) || it >= max_iters) break;
-    hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0 / beta, V, 0.0, V, V);
+    hipLaunchKernelGGL(k_first, dim3(gv), dim3(T), 0, st, n, 1.0 / beta, A.V, dinv, vphi, phi0);
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int j = 0;
-    for (; j < m && it < max_iters; ++j, ++it) {
-      double* vj = V + (long long)j * n;
-      double* vn = V + (long long)(j + 1) * n;
-      hipLaunchKernelGGL(k_mul, dim3(gv), dim3(T), 0, st, n, dinv, vj, z);     // z = D^-1 v_j
-      rc = matvec(z, w);
-      if (rc) return rc;
-      // classical Gram-Schmidt twice; the coefficients stay on the device, the new
-      // vector's norm comes from the second pass, and the host reads all of them once
-      mdot(j + 1, 0, w, c1);
-      hipLaunchKernelGGL(k_maxpy, dim3(gv), dim3(T), 0, st, n, j + 1, c1, V, w);
-      mdot(j + 1, 1, w, c2);
-      hipLaunchKernelGGL(k_maxpy, dim3(gv), dim3(T), 0, st, n, j + 1, c2, V, w);
-      hipLaunchKernelGGL(k_norm_after, dim3(1), dim3(1), 0, st, c2, j + 1, hnb);
-      hipLaunchKernelGGL(k_scale_dev, dim3(gv), dim3(T), 0, st, n, w, hnb, vn);
-      CC_HIP(hipMemcpyAsync(hc.data(), cbuf, sizeof(double) * coef_words(m), hipMemcpyDeviceToHost, st));
+    bool done = false;
+    int ahead = 2;   // steps launched before their columns are read
+    while (!done && j < m && it < max_iters) {
+      const int j0 = j, nj = std::min({ahead, m - j, max_iters - it});
+      for (int q = 0; q < nj; ++q) {
+        rc = apply(phi0, A.w);        // phi0 = [D^-1 v_j | 0]
+        if (rc) return rc;
+        A.step(j0 + q, dinv, vphi, phi0);
+      }
+      CC_HIP(hipMemcpyAsync(hc.data(), A.H + (size_t)j0 * (m + 1), sizeof(double) * nj * (m + 1),
+                            hipMemcpyDeviceToHost, st));
       CC_HIP(hipStreamSynchronize(st));
-      std::vector<double> h(j + 1);
-      for (int i = 0; i <= j; ++i) h[i] = hc[i] + hc[(m + 1) + i];
-      const double hn = hc[(m + 1) + (m + 2)];
-      // Givens rotations on column j of H
-      for (int i = 0; i < j; ++i) {
-        const double t = cs[i] * h[i] + sn[i] * h[i + 1];
-        h[i + 1] = -sn[i] * h[i] + cs[i] * h[i + 1];
-        h[i] = t;
+      const double before = res;
+      for (int q = 0; q < nj && !done; ++q, ++j, ++it) {
+        // Givens rotations on column j of H
+        double* h = hc.data() + (size_t)q * (m + 1);
+        const double hn = h[j + 1];
+        for (int i = 0; i < j; ++i) {
+          const double t = cs[i] * h[i] + sn[i] * h[i + 1];
+          h[i + 1] = -sn[i] * h[i] + cs[i] * h[i + 1];
+          h[i] = t;
+        }
+        const double r = std::hypot(h[j], hn);
+        cs[j] = r > 0.0 ? h[j] / r : 1.0;
+        sn[j] = r > 0.0 ? hn / r : 0.0;
+        h[j] = r;
+        g[j + 1] = -sn[j] * g[j];
+        g[j] = cs[j] * g[j];
+        for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = h[i];
+        res = std::fabs(g[j + 1]);
+        done = res <= rtol * bnorm || hn == 0.0;
       }
-      const double r = std::hypot(h[j], hn);
-      cs[j] = r > 0.0 ? h[j] / r : 1.0;
-      sn[j] = r > 0.0 ? hn / r : 0.0;
-      h[j] = r;
-      g[j + 1] = -sn[j] * g[j];
-      g[j] = cs[j] * g[j];
-      for (int i = 0; i <= j; ++i) H[i * m + j] = h[i];
-      res = std::fabs(g[j + 1]);
-      if (res <= rtol * bnorm || hn == 0.0) {
-        ++j;
-        ++it;
-        break;
-      }
+      // as many steps as the last ones' rate leaves to go, less one, so that few are launched
+      // in vain
+      const double rate = before > 0.0 && res > 0.0 ? std::log(before / res) / nj : 0.0;
+      const double left = rate > 0.0 && rtol > 0.0 ? std::log(res / (rtol * bnorm)) / rate : kBatch;
+      ahead = left < kBatch + 1.0 ? std::max(1, (int)left - 1) : kBatch;
     }
     // y = H^-1 g (upper triangular j x j); x += D^-1 V y
     for (int i = j - 1; i >= 0; --i) {
       double s = g[i];
-      for (int k = i + 1; k < j; ++k) s -= H[i * m + k] * y[k];
-      y[i] = s / H[i * m + i];
+      for (int k = i + 1; k < j; ++k) s -= H[(size_t)i * m + k] * y[k];
+      y[i] = s / H[(size_t)i * m + i];
     }
-    std::vector<double> ny(j);
-    for (int i = 0; i < j; ++i) ny[i] = -y[i];
-    CC_HIP(hipMemcpyAsync(coef, ny.data(), sizeof(double) * j, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, tmp, n, 0.0);
-    hipLaunchKernelGGL(k_maxpy, dim3(gv), dim3(T), 0, st, n, j, coef, V, tmp);   // tmp = V y
-    hipLaunchKernelGGL(k_mul, dim3(gv), dim3(T), 0, st, n, dinv, tmp, tmp);
-    hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0, x, 1.0, tmp, x);
-    CC_HIP(hipStreamSynchronize(st));
+    CC_HIP(hipMemcpyAsync(coef, y.data(), sizeof(double) * j, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_update, dim3(gv), dim3(T), 0, st, n, j, coef, A.V, dinv, x);
   }
   CC_HIP(hipGetLastError());
   if (iters_out) *iters_out = it;
@@ -475,8 +627,7 @@ size_t ritz_workspace_bytes(long long n_vol, long long n_phi, long long n_face, 
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t nv = std::max<long long>(n_vol, 1);
   return al(sizeof(double) * n_phi) * 2 + al(sizeof(double) * std::max<long long>(n_face, 1)) +
-         al(sizeof(double) * nv) + al(sizeof(int32_t) * nv) + al(sizeof(double) * nv * (k + 1)) +
-         al(sizeof(double) * kDotBlocks * (k + 2)) + al(sizeof(double) * coef_words(k)) +
+         al(sizeof(int32_t) * nv) + Arnoldi::bytes(n_vol, k) +
          (inner_m > 0 ? solve_workspace_bytes(n_vol, n_phi, n_face, inner_m) : 0);
 }
 
@@ -490,69 +641,56 @@ int ritz_values(const SolveOp& op, int G, const int64_t* phi_off, const int64_t*
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = ws + off; off += al(bytes); return p; };
   const size_t nv = std::max<long long>(n, 1);
+  hipStream_t st = op.st;
   double* zero_bc = (double*)take(sizeof(double) * op.n_phi);   // Phi = 0 (the inner solves' data)
   double* phi0 = (double*)take(sizeof(double) * op.n_phi);      // [v | 0]
   double* flux = (double*)take(sizeof(double) * std::max<long long>(op.n_face, 1));
-  double* w = (double*)take(sizeof(double) * nv);
   int32_t* vphi = (int32_t*)take(sizeof(int32_t) * nv);
-  double* V = (double*)take(sizeof(double) * nv * (k + 1));
-  double* partial = (double*)take(sizeof(double) * kDotBlocks * (k + 2));
-  double* cbuf = (double*)take(sizeof(double) * coef_words(k));
+  Arnoldi A;
+  A.layout(n, k, st, take);
   char* inner_ws = ws + off;
-  double* c1 = cbuf;
-  double* c2 = cbuf + (k + 1);
-  double* hnb = cbuf + (k + 1) + (k + 2);
-  std::vector<double> hc(coef_words(k));
-  hipStream_t st = op.st;
   const int T = 256;
   const unsigned gv = nb(n, T);
-  auto mdot = [&](int kk, int self, const double* y, double* out) {
-    hipLaunchKernelGGL(k_mdot, dim3(kDotBlocks), dim3(kDotBlock), 0, st, n, kk, self, V, y, partial);
-    hipLaunchKernelGGL(k_mdot_final, dim3(kk + self), dim3(kDotBlock), 0, st, partial, out);
-  };
   hipLaunchKernelGGL(k_vol_phi, dim3(gv), dim3(T), 0, st, n, G, phi_off, vol_off, vphi);
   hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, phi0, op.n_phi, 0.0);
   hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, zero_bc, op.n_phi, 0.0);
-  hipLaunchKernelGGL(k_start_vector, dim3(gv), dim3(T), 0, st, n, V);
-  double n2 = 0.0;
-  mdot(0, 1, V, hnb);
-  CC_HIP(hipMemcpyAsync(&n2, hnb, sizeof(double), hipMemcpyDeviceToHost, st));
-  CC_HIP(hipStreamSynchronize(st));
-  hipLaunchKernelGGL(k_axpby, dim3(gv), dim3(T), 0, st, n, 1.0 / std::sqrt(n2), V, 0.0, V, V);
-  std::vector<double> Hm((size_t)(k + 1) * k, 0.0);
+  hipLaunchKernelGGL(k_start_vector, dim3(gv), dim3(T), 0, st, n, A.V);
+  double nrm = 0.0;
+  int rc = A.norm(A.V, &nrm);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_first, dim3(gv), dim3(T), 0, st, n, 1.0 / nrm, A.V, nullptr, vphi, phi0);
+  std::vector<double> Hm((size_t)(k + 1) * k, 0.0), hc((size_t)k * (k + 1));
   int kk = k, inner_fail = 0;
   for (int j = 0; j < k; ++j) {
-    double* vj = V + (long long)j * n;
-    double* vn = V + (long long)(j + 1) * n;
     if (mode == 0) {
-      hipLaunchKernelGGL(k_scatter, dim3(gv), dim3(T), 0, st, n, vphi, vj, phi0);
-      int rc = op.lap_ptr ? apply_laplacian(op.D, n, op.lap_ptr, op.lap_col, op.lap_val, phi0, w, st)
-                          : apply_operator(op.D, op.n_face, n, op.row_ptr, op.col, op.val, op.vol_face,
-                                           op.vol_scale, phi0, w, flux, nullptr, st);
+      rc = op.lap_ptr ? apply_laplacian(op.D, n, op.lap_ptr, op.lap_col, op.lap_val, phi0, A.w, st)
+                      : apply_operator(op.D, op.n_face, n, op.row_ptr, op.col, op.val, op.vol_face, op.vol_scale, phi0,
+                                       A.w, flux, nullptr, st);
       if (rc) return rc;
     } else {
-      hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, w, n, 0.0);
+      hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, A.w, n, 0.0);
       int it = 0;
       double rr = 0.0;
-      const int rc = solve_poisson(op, G, phi_off, vol_off, zero_bc, vj, w, inner_m, inner_max, inner_rtol, inner_ws,
-                                   solve_workspace_bytes(n, op.n_phi, op.n_face, inner_m), &it, &rr);
+      rc = solve_poisson(op, G, phi_off, vol_off, zero_bc, A.V + (long long)j * n, A.w, inner_m, inner_max, inner_rtol,
+                         inner_ws, solve_workspace_bytes(n, op.n_phi, op.n_face, inner_m), &it, &rr);
       if (rc == CUTCELL_W_NOT_CONVERGED) inner_fail = 1;
       else if (rc) return rc;
     }
-    mdot(j + 1, 0, w, c1);
-    hipLaunchKernelGGL(k_maxpy, dim3(gv), dim3(T), 0, st, n, j + 1, c1, V, w);
-    mdot(j + 1, 1, w, c2);
-    hipLaunchKernelGGL(k_maxpy, dim3(gv), dim3(T), 0, st, n, j + 1, c2, V, w);
-    hipLaunchKernelGGL(k_norm_after, dim3(1), dim3(1), 0, st, c2, j + 1, hnb);
-    hipLaunchKernelGGL(k_scale_dev, dim3(gv), dim3(T), 0, st, n, w, hnb, vn);
-    CC_HIP(hipMemcpyAsync(hc.data(), cbuf, sizeof(double) * coef_words(k), hipMemcpyDeviceToHost, st));
-    CC_HIP(hipStreamSynchronize(st));
-    for (int i = 0; i <= j; ++i) Hm[(size_t)i * k + j] = hc[i] + hc[(k + 1) + i];
-    const double hn = hc[(k + 1) + (k + 2)];
-    Hm[(size_t)(j + 1) * k + j] = hn;
-    if (!(hn > 0.0)) {       // invariant subspace: its eigenvalues are exact
-      kk = j + 1;
-      break;
+    A.step(j, nullptr, vphi, phi0);
+    if (mode == 1 || j + 1 == k) {   // products with A alone run to the end; inner solves stop at once
+      const int j0 = mode == 1 ? j : 0;
+      CC_HIP(hipMemcpyAsync(hc.data() + (size_t)j0 * (k + 1), A.H + (size_t)j0 * (k + 1),
+                            sizeof(double) * (j + 1 - j0) * (k + 1), hipMemcpyDeviceToHost, st));
+      CC_HIP(hipStreamSynchronize(st));
+      bool invariant = false;
+      for (int c = j0; c <= j && !invariant; ++c) {
+        for (int i = 0; i <= c + 1; ++i) Hm[(size_t)i * k + c] = hc[(size_t)c * (k + 1) + i];
+        if (!(hc[(size_t)c * (k + 1) + c + 1] > 0.0)) {   // invariant subspace: its eigenvalues are exact
+          kk = c + 1;
+          invariant = true;
+        }
+      }
+      if (invariant) break;
     }
   }
   CC_HIP(hipGetLastError());
