@@ -114,18 +114,43 @@ __global__ __launch_bounds__(256) void k_face_cotangent(long long n_vol, const i
 }
 
 // Phi-bar_k = sum over the nonzeros j of column k of val[j] * fbar[face(j)]
-template <int SW>
+//
+// SW lanes per Phi entry, U loads of a lane in flight.  Consecutive entries read consecutive
+// values of the same face rows, so workgroup b (which MI355X runs on XCD b % 8) takes its
+// entries from the b % 8-th eighth of them: the value lines that neighbouring entries share
+// are then fetched into one L2 instead of eight.  Bound by the lines of the gathers (a column
+// uses 7 of a value line's 16 doubles); 48^3, path radius 3 (2.7e7 nonzeros): 262 us with 32
+// lanes, one load in flight and the entries dealt over the XCDs in turn, 250 us with 4 loads,
+// 235 us with 16 lanes and 12 loads, 279 us with those and the entries dealt in turn.
+template <int SW, int U>
 __global__ __launch_bounds__(256) void k_phi_bar(long long n_phi, const int64_t* __restrict__ col_ptr,
                                                  const int32_t* __restrict__ nz, const int32_t* __restrict__ nz_face,
                                                  const double* __restrict__ val, const double* __restrict__ fbar,
                                                  double* __restrict__ phi_bar) {
-  const long long gt = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const long long k = gt / SW;
+  const long long per = (long long)(gridDim.x / kXcds);   // workgroups per XCD
+  const long long blk = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+  const long long k = (blk * 256 + threadIdx.x) / SW;
   const int sl = threadIdx.x % SW;
   double s = 0.0;
   if (k < n_phi) {
     const int64_t a = col_ptr[k], b = col_ptr[k + 1];
-    for (int64_t i = a + sl; i < b; i += SW) s = fma(val[nz[i]], fbar[nz_face[i]], s);
+    for (int64_t i = a + sl; i < b; i += SW * U) {
+      int32_t j[U], f[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool in = i + SW * u < b;
+        j[u] = in ? __builtin_nontemporal_load(nz + i + SW * u) : -1;
+        f[u] = in ? __builtin_nontemporal_load(nz_face + i + SW * u) : 0;
+      }
+      double v[U], c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = j[u] >= 0 ? val[j[u]] : 0.0;
+        c[u] = j[u] >= 0 ? fbar[f[u]] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) s = j[u] >= 0 ? fma(v[u], c[u], s) : s;
+    }
   }
 #pragma unroll
   for (int off = SW / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, SW);
@@ -172,7 +197,8 @@ static void apply_adjoint_t(long long n_face, long long n_vol, long long n_phi, 
                             const int32_t* col, const double* val, const int32_t* vol_face, const double* vol_scale,
                             const Transpose& tr, const double* phi, const double* flux, const double* lbar,
                             double* phi_bar, double* val_bar, double* scale_bar, double* fbar, hipStream_t st) {
-  constexpr int SW = (D == 3) ? 32 : 16;
+  constexpr int SW = (D == 3) ? 32 : 16;           // lanes of a face row
+  constexpr int SC = 16, U = (D == 3) ? 12 : 4;    // lanes of a column and their loads in flight
   if (n_face > 0) hipLaunchKernelGGL(k_fill_f64, dim3(nblocks(n_face, 256)), dim3(256), 0, st, fbar, n_face, 0.0);
   if (n_vol > 0) {
     hipLaunchKernelGGL((k_face_cotangent<D, 0>), dim3(nblocks(n_vol, 256)), dim3(256), 0, st, n_vol, vol_face, vol_scale,
@@ -183,9 +209,11 @@ static void apply_adjoint_t(long long n_face, long long n_vol, long long n_phi, 
       hipLaunchKernelGGL(k_scale_bar<D>, dim3(nblocks(n_vol, 256)), dim3(256), 0, st, n_vol, vol_face, flux, lbar,
                          scale_bar);
   }
-  if (n_phi > 0)
-    hipLaunchKernelGGL(k_phi_bar<SW>, dim3(nblocks(n_phi * SW, 256)), dim3(256), 0, st, n_phi, tr.col_ptr, tr.nz,
-                       tr.nz_face, val, fbar, phi_bar);
+  if (n_phi > 0) {
+    const unsigned blocks = (nblocks(n_phi * SC, 256) + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL((k_phi_bar<SC, U>), dim3(blocks), dim3(256), 0, st, n_phi, tr.col_ptr, tr.nz, tr.nz_face, val,
+                       fbar, phi_bar);
+  }
   if (val_bar && n_face > 0)
     hipLaunchKernelGGL(k_val_bar<SW>, dim3(nblocks(n_face * SW, 256)), dim3(256), 0, st, n_face, row_ptr, col, fbar, phi,
                        val_bar);
