@@ -35,19 +35,32 @@ __global__ void k_col_ptr(long long nnz, long long n_phi, const int32_t* __restr
   for (long long k = prev + 1; k <= cur; ++k) col_ptr[k] = i;
 }
 
-// face of each listed CSR position (binary search in row_ptr)
-__global__ void k_nz_face(long long nnz, long long n_face, const int64_t* __restrict__ row_ptr,
-                          const int32_t* __restrict__ nz, int32_t* __restrict__ nz_face) {
-  long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  const int64_t j = nz[i];
-  long long lo = 0, hi = n_face;   // row_ptr[lo] <= j < row_ptr[hi]
-  while (hi - lo > 1) {
-    const long long mid = (lo + hi) >> 1;
-    if (row_ptr[mid] <= j) lo = mid;
-    else hi = mid;
-  }
-  nz_face[i] = (int32_t)lo;
+// The face of every CSR position, then of each listed one.  Bound by the gather's lines;
+// 1.4e7 nonzeros: 235 us as a binary search in row_ptr per nonzero, 21 + 95 us like this.
+__global__ __launch_bounds__(256) void k_row_face(long long n_face, const int64_t* __restrict__ row_ptr,
+                                                  int32_t* __restrict__ face_of) {
+  constexpr int SW = 16;   // lanes per row
+  const long long f = (blockIdx.x * 256LL + threadIdx.x) / SW;
+  if (f >= n_face) return;
+  const int64_t b = row_ptr[f + 1];
+  for (int64_t j = row_ptr[f] + threadIdx.x % SW; j < b; j += SW) face_of[j] = (int32_t)f;
+}
+
+// Workgroup b runs on XCD b % 8 and takes its positions from the b % 8-th eighth: the lines
+// of face_of that neighbouring columns share are then fetched into one L2.
+__global__ __launch_bounds__(256) void k_nz_face(long long nnz, const int32_t* __restrict__ face_of,
+                                                 const int32_t* __restrict__ nz, int32_t* __restrict__ nz_face) {
+  constexpr int U = 4;   // loads of a thread in flight
+  const long long per = (long long)(gridDim.x / kXcds);   // workgroups per XCD
+  const long long i0 = ((blockIdx.x % kXcds) * per + blockIdx.x / kXcds) * (256LL * U) + threadIdx.x;
+  int32_t j[U], f[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) j[u] = i0 + 256 * u < nnz ? nz[i0 + 256 * u] : -1;
+#pragma unroll
+  for (int u = 0; u < U; ++u) f[u] = j[u] >= 0 ? face_of[j[u]] : 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (j[u] >= 0) nz_face[i0 + 256 * u] = f[u];
 }
 
 static int key_bits(long long n_phi) {
@@ -81,7 +94,9 @@ int build_transpose(long long n_face, long long n_phi, long long nnz, const int6
   if (nnz > 0) {
     hipLaunchKernelGGL(k_iota, dim3(nblocks(nnz, 256)), dim3(256), 0, st, vals_in, nnz);
     CC_HIP(hipcub::DeviceRadixSort::SortPairs(ws, temp, col, keys_out, vals_in, nz, (int)nnz, 0, key_bits(n_phi), st));
-    hipLaunchKernelGGL(k_nz_face, dim3(nblocks(nnz, 256)), dim3(256), 0, st, nnz, n_face, row_ptr, nz, nz_face);
+    int32_t* face_of = vals_in;   // the sort has read it
+    hipLaunchKernelGGL(k_row_face, dim3(nblocks(n_face * 16, 256)), dim3(256), 0, st, n_face, row_ptr, face_of);
+    hipLaunchKernelGGL(k_nz_face, dim3(nblocks(nblocks(nnz, 1024), kXcds) * kXcds), dim3(256), 0, st, nnz, face_of, nz, nz_face);
   }
   hipLaunchKernelGGL(k_col_ptr, dim3(nblocks(nnz + 1, 256)), dim3(256), 0, st, nnz, n_phi, keys_out, col_ptr);
   CC_HIP(hipGetLastError());
