@@ -254,17 +254,41 @@ int apply_adjoint(int D, long long n_face, long long n_vol, long long n_phi, con
 //   g = sum_j S(delta_j)^T Abar_j,   dl/dm = g / m_0 - e_0 (g . m) / m_0^2
 // (A~_j = S(delta_j) m / m_0, and the sum of Abar_j . A~_j over j is g . m / m_0).
 // Volumes add the gradient through their EB face's centroid (owner_grad) and through
-// 1/(kappa h^D) in the apply (scale_bar).  One wave per Phi entry, a lane per nonzero; the
-// 64 lane sums are added in lane order.
+// 1/(kappa h^D) in the apply (scale_bar).
+//
+// One wave per Phi entry, a lane per nonzero.  The 2M doubles of a face come in slices: the
+// wave reads a slice of its 64 faces with neighbouring lanes on neighbouring addresses, the
+// next one while it sums this one, and hands each lane its face's part through LDS.  The lane
+// sums meet in registers, two halves of the wave folding two moments into one register.
+// Consecutive entries read the vectors of the same faces, so a workgroup takes four of them
+// and workgroup b, which MI355X runs on XCD b % 8, takes them from the b % 8-th eighth.
+// Bound by what comes through the caches (560 bytes per nonzero, 7 TB/s); 40^3, order 4, path
+// radius 3 (1.4e7 nonzeros): 1450 us with the entries dealt over the XCDs in turn, each lane
+// reading its face's vectors by itself and the lane sums in LDS, 1249 us without the first and
+// the last, 1107 us like this.
+
+// a' = the low halves of a and b, b' = their high halves: a' + b' holds a's sum over l, l ^ 32
+// in the low half of the wave and b's in the high one; with 16: in the even and odd 16 lanes
+__device__ __forceinline__ double fold32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
 
 template <int D, int Q>
-__global__ __launch_bounds__(64) void k_moment_reduce(ReduceArgs R) {
+__global__ __launch_bounds__(256, 2) void k_moment_reduce(ReduceArgs R) {
   constexpr int M = Dims<D, Q>::M, Mf = Dims<D, Q>::Mf;
-  __shared__ double part[64][M + 1];
-  __shared__ double tot[M + 1];
-  const long long k = blockIdx.x;
+  constexpr int NR = (M + 3) / 4;   // registers after both folds
+  const long long per = (long long)(gridDim.x / kXcds);   // workgroups per XCD
+  const long long blk = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+  const long long k = 4 * blk + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (k >= R.n_phi) return;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   int lo = 0, hi = R.G;           // offs[lo] <= k < offs[hi]
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
@@ -272,63 +296,87 @@ __global__ __launch_bounds__(64) void k_moment_reduce(ReduceArgs R) {
     else hi = mid;
   }
   const int gi = lo;
-  const GeomPtrs gp = R.geoms[gi];
+  const GeomPtrs& gp = R.geoms[gi];
   const int64_t loc = k - R.offs[gi];
   const int64_t n_vol = R.counts[4 * gi + 0], n_eb = R.counts[4 * gi + 1];
   const int32_t* vol_cell = R.vol_cell_ws + (long long)gi * R.g.ncell;
   const RowSource rs =
       row_source<D, Q>(R.g, gp, loc, n_vol, n_eb, vol_cell, R.box_lf_ws + (long long)gi * R.g.nboxslot);
-  double g[M];
-  static_for<0, M>([&](auto I) { g[I] = 0.0; });
+  double g[4 * NR];
+  static_for<0, 4 * NR>([&](auto I) { g[I] = 0.0; });
   const int64_t a = R.tr.col_ptr[k], b = R.tr.col_ptr[k + 1];
-  for (int64_t i = a + lane; i < b; i += 64) {
+  constexpr int W = (M % 5 == 0) ? 10 : 12;      // doubles of a slice
+  constexpr int U = W / 2, NS = 2 * M / W;       // 16-byte loads of a lane, slices
+  static_assert(NS * W == 2 * M && W % 2 == 0, "slices");
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  __shared__ dv2 slices[4][64 * U];
+  dv2* const sl2 = slices[threadIdx.x >> 6];
+  for (int64_t i0 = a; i0 < b; i0 += 64) {
+    const int64_t i = i0 + lane < b ? i0 + lane : b - 1;   // past the end: the last one, not summed
     const int64_t j = R.tr.nz[i];
     const int32_t f = R.tr.nz_face[i];
+    const double* at[U];    // the lane's part of a slice: piece (lane + 64 u) % U of face (lane + 64 u) / U
+    static_for<0, U>([&](auto u) {
+      const int t = lane + 64 * u;
+      at[u] = R.face_yw + (long long)__shfl(f, t / U) * 2 * M + 2 * (t % U);
+    });
+    dv2 q[U];
+    static_for<0, U>([&](auto u) { q[u] = *(const dv2*)at[u]; });
     const double wr = R.nz_rz[2 * j], wz = R.nz_rz[2 * j + 1];
-    const double* yw = R.face_yw + (long long)f * 2 * M;
-    double ab[M];
-    static_for<0, M>([&](auto I) { ab[I] = wr * yw[I] - wz * yw[M + I]; });
     double dl[3] = {0, 0, 0};
     for (int ax = 0; ax < D; ++ax) dl[ax] = rs.ctr[ax] - R.face_x0[(long long)f * 4 + ax];
+    double ab[M];
+    static_for<0, NS>([&](auto S) {
+      lds_order();
+      static_for<0, U>([&](auto u) { sl2[lane + 64 * u] = q[u]; });
+      lds_order();
+      if constexpr (S + 1 < NS)
+        static_for<0, U>([&](auto u) { q[u] = *(const dv2*)(at[u] + W * (S + 1)); });
+      static_for<0, U>([&](auto u) {
+        const dv2 v = sl2[lane * U + u];
+        constexpr int e = W * S + 2 * u;   // e, e + 1: y up to M, then w
+        if constexpr (e < M) ab[e] = wr * v.x;
+        else ab[e - M] = fma(-wz, v.x, ab[e - M]);
+        if constexpr (e + 1 < M) ab[e + 1] = wr * v.y;
+        else ab[e + 1 - M] = fma(-wz, v.y, ab[e + 1 - M]);
+      });
+    });
     recentre_T<D, Q>(ab, dl);
-    static_for<0, M>([&](auto I) { g[I] += ab[I]; });
+    if (i0 + lane < b) static_for<0, M>([&](auto I) { g[I] += ab[I]; });
   }
-  static_for<0, M>([&](auto I) { part[lane][I] = g[I]; });
-  __syncthreads();
-  double m[M];
-  load_row_moments<D, Q>(rs, m);
-  if (lane < M) {
-    double s = 0.0;
-    for (int l = 0; l < 64; ++l) s += part[l][lane];
-    tot[lane] = s;
-  }
-  __syncthreads();
-  double gm = 0.0;
-  static_for<0, M>([&](auto I) { gm = fma(tot[I], m[I], gm); });
-  if (lane >= M) return;
-  const double m0 = m[0];
-  double out = tot[lane] / m0;
-  if (lane == 0) out -= gm / (m0 * m0);
-  const GradPtrs gr = R.grads[gi];
+  // lane l keeps moment c = 4 (l % 16) + {0, 2, 1, 3}[l / 16]
+  double s[NR];
+  static_for<0, NR>([&](auto I) {
+    s[I] = sum_in_lane_row(fold16(fold32(g[4 * I], g[4 * I + 1]), fold32(g[4 * I + 2], g[4 * I + 3])));
+  });
+  double tot = s[0];
+  static_for<1, NR>([&](auto I) { tot = (lane & 15) == I ? s[I] : tot; });
+  const int row = lane >> 4, c = 4 * (lane & 15) + ((row & 1) << 1 | row >> 1);
+  const int sl = c >= M ? -1 : rs.dd < 0 ? c : face_slot<D, Q>(c, rs.dd);   // where the moment is stored
+  const double m0 = rs.src[0];
+  const double gm = wave_sum_f64(sl >= 0 ? tot * rs.src[sl] : 0.0);
+  if (sl < 0) return;
+  double out = tot / m0;
+  if (c == 0) out -= gm / (m0 * m0);
+  const GradPtrs& gr = R.grads[gi];
   if (rs.dd < 0 && loc < n_vol) {
     const long long vg = R.offs[(R.G + 1) + gi] + loc;          // global volume index
-    if (lane == 0 && R.scale_bar) out -= R.scale_bar[vg] * R.vol_scale[vg] / m0;   // d(1/(kappa h^D))/d kappa
+    if (c == 0 && R.scale_bar) out -= R.scale_bar[vg] * R.vol_scale[vg] / m0;   // d(1/(kappa h^D))/d kappa
     const int32_t fe = R.vol_face[vg * (2 * D + 1) + 2 * D];
-    if (fe >= 0 && lane <= D) out += R.owner_grad[(long long)fe * 4 + lane];
-    gr.vol_mom[(long long)rs.cell * M + lane] = out;
+    if (fe >= 0 && c <= D) out += R.owner_grad[(long long)fe * 4 + c];
+    gr.vol_mom[(long long)rs.cell * M + c] = out;
   } else if (rs.dd < 0) {
-    gr.eb_mom[(loc - n_vol) * M + lane] = out;
+    gr.eb_mom[(loc - n_vol) * M + c] = out;
   } else {
     // box face: only the transverse moments are stored; the face kernel has already
     // written their flux-vector part
-    const int sl = face_slot<D, Q>(lane, rs.dd);
-    if (sl >= 0) gr.face_mom[rs.dd][rs.loc * Mf + sl] += out;
+    gr.face_mom[rs.dd][rs.loc * Mf + sl] += out;
   }
 }
 
 int reduce_moments(const cutcell_opts& o, const ReduceArgs& R, hipStream_t st) {
   if (R.n_phi <= 0) return CUTCELL_OK;
-  const dim3 grid((unsigned)R.n_phi), block(64);
+  const dim3 grid(nblocks((R.n_phi + 3) / 4, kXcds) * kXcds), block(256);
   if (o.dim == 2 && o.order == 2) hipLaunchKernelGGL((k_moment_reduce<2, 2>), grid, block, 0, st, R);
   else if (o.dim == 2 && o.order == 4) hipLaunchKernelGGL((k_moment_reduce<2, 4>), grid, block, 0, st, R);
   else if (o.dim == 3 && o.order == 2) hipLaunchKernelGGL((k_moment_reduce<3, 2>), grid, block, 0, st, R);

@@ -252,6 +252,10 @@ __device__ __forceinline__ double wave_max_f64(double v) {
   return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
 }
 
+// Orders shared-memory accesses of the wave's lanes with each other, in memory that only
+// this wave uses (its shared-memory instructions complete in order): for the compiler only.
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 __device__ __forceinline__ long long readlane_i64(long long v, int lane) {
   const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, lane);
   const unsigned hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);

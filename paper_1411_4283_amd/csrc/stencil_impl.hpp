@@ -248,10 +248,6 @@ struct FaceSmem {
 // array in memory.
 __device__ __forceinline__ double pick(bool c, double x, double y) { return c ? x : y; }
 
-// Orders shared-memory accesses of the wave's lanes with each other (one wave per
-// workgroup, whose shared-memory instructions complete in order): for the compiler only.
-__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 // Everything about the face that the row and flux computations need.
 struct FaceInfo {
   int32_t F;
