@@ -115,11 +115,7 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.ref_cell = (int32_t*)take(sizeof(int32_t) * G);
   t.tface = (int32_t*)take(sizeof(int32_t) * 3 * G);
   t.tmpl = (int32_t*)take(sizeof(int32_t) * totface);
-  t.okey = (unsigned long long*)take(sizeof(unsigned long long) * totface);
-  t.okey_out = (unsigned long long*)take(sizeof(unsigned long long) * totface);
-  t.oval = (int32_t*)take(sizeof(int32_t) * totface);
-  t.osort_bytes = order_temp_bytes(totface);
-  t.osort_tmp = take(t.osort_bytes);
+  t.order_hist = (int32_t*)take(sizeof(int32_t) * (kNBuckets + 1) * order_tiles(G * g.ncell));
   t.counts = (int64_t*)take(sizeof(int64_t) * 4 * G);
   t.offs = (int64_t*)take(sizeof(int64_t) * 3 * (G + 1));
   t.fcode = (int32_t*)take(sizeof(int32_t) * totface);
@@ -250,13 +246,14 @@ static int prepare(const cutcell_geom* geoms, int G, const cutcell_opts* o, void
   return CUTCELL_OK;
 }
 
-// counts rows per face, scans them into row_ptr (int64); returns nnz and max rows
-static int count_rows(const Prepared& P, const cutcell_opts* o, int64_t* row_ptr, int64_t* nnz, int32_t* maxrows,
-                      hipStream_t st) {
+// counts rows per face, scans them into row_ptr (int64) and counts the buckets of the
+// processing order (`tmpl` as there); returns nnz and the words of w.bins
+static int count_rows(const Prepared& P, const cutcell_opts* o, int64_t* row_ptr, const int32_t* tmpl, int64_t* nnz,
+                      int32_t* bins, hipStream_t st) {
   const Work& w = P.w;
   int rc = neighbour_rows(w, *o, P.n_face, nullptr, nullptr, false, st);
   if (rc) return rc;
-  rc = max_rows(w, P.n_face, st);
+  rc = count_buckets(w, binom(o->order + o->dim, o->dim), tmpl, st);
   if (rc) return rc;
   int64_t total = 0;
   if (P.n_face > 0) {
@@ -264,19 +261,16 @@ static int count_rows(const Prepared& P, const cutcell_opts* o, int64_t* row_ptr
                                           w.scan64, st);
     if (rc) return rc;
   }
-  int32_t mr = 0;
   const int64_t zero = 0;
-  CC_HIP(hipMemcpyAsync(&mr, w.bins + 2 * kNBuckets, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  CC_HIP(hipMemcpyAsync(bins, w.bins, sizeof(int32_t) * kBinWords, hipMemcpyDeviceToHost, st));
   if (row_ptr && P.n_face > 0)
     CC_HIP(hipMemcpyAsync(&total, row_ptr + P.n_face, sizeof(int64_t), hipMemcpyDeviceToHost, st));
   else if (row_ptr)   // no faces: row_ptr = [0]
     CC_HIP(hipMemcpyAsync(row_ptr, &zero, sizeof(int64_t), hipMemcpyHostToDevice, st));
   CC_HIP(hipStreamSynchronize(st));
   *nnz = total;
-  *maxrows = mr;
   return CUTCELL_OK;
 }
-
 
 // Scratch of cutcell_stencils_backward after the forward workspace.
 struct BackWork {
@@ -336,9 +330,10 @@ int cutcell_query(const cutcell_geom* geoms, int32_t n_geom, const cutcell_opts*
   int rc = prepare(geoms, n_geom, opts, workspace, workspace_bytes, st, &P);
   if (rc) return rc;
   int64_t nnz = 0;
-  int32_t mr = 0;
-  rc = count_rows(P, opts, P.w.rp_tmp, &nnz, &mr, st);
+  int32_t bc[kBinWords];
+  rc = count_rows(P, opts, P.w.rp_tmp, nullptr, &nnz, bc, st);
   if (rc) return rc;
+  const int32_t mr = bc[2 * kNBuckets];
   sizes->n_vol = P.n_vol;
   sizes->n_eb = P.n_eb;
   sizes->n_box = P.n_box;
@@ -371,10 +366,16 @@ static int build_common(const cutcell_geom* geoms, int32_t n_geom, const cutcell
   if (sizes->n_geom != n_geom || sizes->n_face != P.n_face || sizes->n_vol != P.n_vol || sizes->n_phi != P.n_phi)
     return fail(CUTCELL_E_CAPACITY, "sizes do not match these inputs (call cutcell_query first)");
   const Work& w = P.w;
+  if (opts->reuse_templates) {
+    rc = find_templates(w, *opts, P.n_face, st);
+    if (rc) return rc;
+  }
+  const int32_t* tmpl = opts->reuse_templates ? w.tmpl : nullptr;
   int64_t nnz = 0;
-  int32_t mr = 0;
-  rc = count_rows(P, opts, out->row_ptr, &nnz, &mr, st);
+  int32_t bc[kBinWords];
+  rc = count_rows(P, opts, out->row_ptr, tmpl, &nnz, bc, st);
   if (rc) return rc;
+  const int32_t mr = bc[2 * kNBuckets];
   timer.mark();
   if (nnz != sizes->nnz) return fail(CUTCELL_E_CAPACITY, "nnz differs from sizes->nnz");
   if (mr > kMaxRows)
@@ -383,17 +384,9 @@ static int build_common(const cutcell_geom* geoms, int32_t n_geom, const cutcell
   rc = neighbour_rows(w, *opts, P.n_face, out->row_ptr, out->col, true, st);
   if (rc) return rc;
   timer.mark();
-  const int M = binom(opts->order + opts->dim, opts->dim);
-  if (opts->reuse_templates) {
-    rc = find_templates(w, *opts, P.n_face, st);
-    if (rc) return rc;
-  }
-  rc = bin_faces(w, P.n_face, M, opts->reuse_templates ? w.tmpl : nullptr, st);
+  rc = order_faces(w, binom(opts->order + opts->dim, opts->dim), tmpl, st);
   if (rc) return rc;
   timer.mark();
-  int32_t bc[kBinWords];
-  CC_HIP(hipMemcpyAsync(bc, w.bins, sizeof(bc), hipMemcpyDeviceToHost, st));
-  CC_HIP(hipStreamSynchronize(st));
   g_last_reused = bc[kMaxBins + 1];
   for (int b = 0; b < kMaxBins; ++b) g_last_bins[b] = bc[b];
   if (tune_out) {
@@ -775,9 +768,9 @@ int cutcell_stencils_backward(const cutcell_geom* geoms, int32_t n_geom, const c
   // bin the faces by their row counts again
   rc = rows_per_face(w, P.n_face, st_->row_ptr, st);
   if (rc) return rc;
-  rc = max_rows(w, P.n_face, st);
+  rc = count_buckets(w, M, nullptr, st);
   if (rc) return rc;
-  rc = bin_faces(w, P.n_face, M, nullptr, st);
+  rc = order_faces(w, M, nullptr, st);
   if (rc) return rc;
   int32_t bc[kBinWords];
   CC_HIP(hipMemcpyAsync(bc, w.bins, sizeof(bc), hipMemcpyDeviceToHost, st));

@@ -1,5 +1,5 @@
 // Enumeration of volumes, boundary faces and flux faces (Sec. 2.1), path-radius
-// neighbour rows (Sec. 2.4) and row-count binning.
+// neighbour rows (Sec. 2.4) and template faces.
 #include "kernels.hpp"
 #include "scan.hpp"
 
@@ -658,67 +658,11 @@ int volume_tables(const Work& w, const cutcell_opts& o, long long n_vol_total, i
   return CUTCELL_OK;
 }
 
-// ---------------------------------------------------------------------------------------
-// binning by row count: buckets of 16 rows (N <= 16, ..., <= 128) and one bucket for
-// faces with fewer rows than monomials; perm lists faces bucket by bucket
-
-// per-block histograms in LDS, one global atomic per bucket per block
-__global__ __launch_bounds__(256) void k_bin_count(long long n_face, int M, const int32_t* __restrict__ nrows,
-                                                   const int32_t* __restrict__ tmpl, int32_t* bins) {
-  __shared__ int32_t h[kNBuckets];
-  if (threadIdx.x < kNBuckets) h[threadIdx.x] = 0;
-  __syncthreads();
-  long long f = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (f < n_face) atomicAdd(&h[face_bucket(f, M, nrows, tmpl)], 1);
-  __syncthreads();
-  if (threadIdx.x < kNBuckets && h[threadIdx.x]) atomicAdd(&bins[threadIdx.x], h[threadIdx.x]);
-}
-
-__global__ void k_bin_starts(int32_t* bins) {
-  if (threadIdx.x != 0) return;
-  int s = 0;
-  for (int b = 0; b < kNBuckets; ++b) {
-    bins[kNBuckets + b] = s;
-    s += bins[b];
-  }
-}
-
-// largest row count (block reduction, one atomic per block)
-__global__ __launch_bounds__(256) void k_max_rows(long long n_face, const int32_t* __restrict__ nrows, int32_t* out) {
-  __shared__ int32_t sm[256];
-  long long f = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  sm[threadIdx.x] = (f < n_face) ? nrows[f] : 0;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) sm[threadIdx.x] = max(sm[threadIdx.x], sm[threadIdx.x + o]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(out, sm[0]);
-}
-
-int max_rows(const Work& w, long long n_face, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.bins + 2 * kNBuckets, 1LL, 0);
-  if (n_face > 0)
-    hipLaunchKernelGGL(k_max_rows, dim3(blocks_for(n_face, 256)), dim3(256), 0, st, n_face, w.nrows,
-                       w.bins + 2 * kNBuckets);
-  CC_HIP(hipGetLastError());
-  return CUTCELL_OK;
-}
-
 int rows_per_face(const Work& w, long long n_face, const int64_t* row_ptr, hipStream_t st) {
   if (n_face > 0)
     hipLaunchKernelGGL(k_rows_per_face, dim3(blocks_for(n_face, 256)), dim3(256), 0, st, n_face, row_ptr, w.nrows);
   CC_HIP(hipGetLastError());
   return CUTCELL_OK;
-}
-
-int bin_faces(const Work& w, long long n_face, int M, const int32_t* tmpl, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.bins, (long long)(2 * kNBuckets), 0);
-  if (n_face <= 0) return CUTCELL_OK;
-  hipLaunchKernelGGL(k_bin_count, dim3(blocks_for(n_face, 256)), dim3(256), 0, st, n_face, M, w.nrows, tmpl, w.bins);
-  hipLaunchKernelGGL(k_bin_starts, dim3(1), dim3(64), 0, st, w.bins);
-  CC_HIP(hipGetLastError());
-  return order_faces(w, n_face, M, tmpl, st);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -12,7 +12,7 @@ constexpr int kMaxBins = 8;     // row-count bins of 16 rows: N <= 16, 32, ..., 
 constexpr int kBinRows = 16;
 constexpr int kMaxRows = kMaxBins * kBinRows;
 constexpr int kNBuckets = kMaxBins + 2;   // then faces with N < M, then template copies
-constexpr int kBinWords = 2 * kNBuckets + 1;       // counts, cursors, max rows
+constexpr int kBinWords = 2 * kNBuckets + 1;       // counts, starts, max rows
 constexpr int kInfoPad = 32;    // bytes of padding of cellinfo on either side
 constexpr int kXcds = 8;        // MI355X: workgroups are dealt to 8 XCDs (own L2 each) in turn
 constexpr int kQrSlots = 1024;  // workgroups of the QR path, each with a slot of workspace
@@ -41,11 +41,7 @@ struct Work {
   int32_t* ref_cell;    // [G]         the reference (ball-regular) cell, or INT32_MAX
   int32_t* tface;       // [G][3]      template face per direction, or INT32_MAX
   int32_t* tmpl;        // [G*maxface] template of each face whose stencil is copied, else -1
-  unsigned long long* okey;      // [G*maxface] processing-order keys (bucket, then cell)
-  unsigned long long* okey_out;  // [G*maxface]
-  int32_t* oval;        // [G*maxface] face ids to sort
-  char* osort_tmp;      // radix-sort scratch
-  size_t osort_bytes;
+  int32_t* order_hist;  // [kNBuckets + 1][order_tiles] faces per bucket and tile of cells, most rows per tile
   int64_t* counts;      // [G][4]      n_vol, n_eb, n_box, n_gface
   int64_t* offs;        // [3][G+1]    phi_off, vol_off, face_off
   int32_t* fcode;       // [G*maxface] per global flux face
@@ -54,7 +50,7 @@ struct Work {
   int64_t* scan64;      // int64 scan tiles over G*maxface
   int64_t* rp_tmp;      // [G*maxface + 1] row offsets when the caller has none (query)
   int32_t* perm;        // [G*maxface]
-  int32_t* bins;        // [kBinWords] bucket counts, bucket cursors, max rows
+  int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows
   int32_t* flagged;     // [2] flagged faces, bad EB input
   int32_t* qr_count;    // [1] faces left to the Householder QR path
   int32_t* qr_list;     // [G*maxface] those faces
@@ -103,12 +99,14 @@ int neighbour_rows(const Work& w, const cutcell_opts& o, long long n_face, const
 // volume -> face table and 1/(kappa h^D)
 int volume_tables(const Work& w, const cutcell_opts& o, long long n_vol_total, int32_t* vol_face,
                   double* vol_scale, hipStream_t st);
-// binning by row count and the stencil solves (Sec. 2.2.1)
-// `tmpl` (or null): faces with tmpl >= 0 go to the template-copy bucket
-int bin_faces(const Work& w, long long n_face, int M, const int32_t* tmpl, hipStream_t st);
-// processing order: faces grouped by bucket, inside a bucket by the cell they sit at
-size_t order_temp_bytes(long long n_items);
-int order_faces(const Work& w, long long n_face, int M, const int32_t* tmpl, hipStream_t st);
+// binning by row count (Sec. 2.2.1)
+// `tmpl` (or null): faces with tmpl >= 0 go to the template-copy bucket.  count_buckets
+// leaves the buckets' counts, their starts and the most rows of a face in w.bins;
+// order_faces then writes w.perm: faces grouped by bucket, inside a bucket by the cell they
+// sit at (same M and tmpl)
+int order_tiles(long long cells);
+int count_buckets(const Work& w, int M, const int32_t* tmpl, hipStream_t st);
+int order_faces(const Work& w, int M, const int32_t* tmpl, hipStream_t st);
 
 // bucket of face f: a 16-row bin, the faces with fewer rows than monomials, or the copies
 __host__ __device__ inline int face_bucket(long long f, int M, const int32_t* nrows, const int32_t* tmpl) {
@@ -118,7 +116,6 @@ __host__ __device__ inline int face_bucket(long long f, int M, const int32_t* nr
 }
 // faces whose systems are bitwise those of one solved face per (geometry, direction)
 int find_templates(const Work& w, const cutcell_opts& o, long long n_face, hipStream_t st);
-int max_rows(const Work& w, long long n_face, hipStream_t st);
 int solve_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count /* host */, long long n_face,
                    const int64_t* row_ptr, const int32_t* col, double* val, int8_t* status, hipStream_t st);
 // Arguments of the per-Phi-entry sum of the rows' moment gradients.

@@ -1,0 +1,49 @@
+"""The buckets of the processing order: counts against the rows' histogram, and every face
+solved exactly where it belongs (no status or value of a prefilled output left over), on
+grids of one cell, of one tile and less, batches whose tiles span geometries, several steps
+per workgroup, and with template copies."""
+
+import ctypes
+
+import numpy as np
+import pytest
+
+import cutgeom as cg
+
+torch = pytest.importorskip("torch")
+import paper_1411_4283_amd as cc  # noqa: E402
+from paper_1411_4283_amd._lib import load  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,n,Q,R,batch,reuse", [
+    (2, 3, 2, 2, 1, False),
+    (2, 1, 2, 1, 1, False),
+    (2, 17, 2, 3, 3, False),
+    (2, 61, 4, 3, 5, True),
+    (2, 760, 2, 2, 1, False),       # 2257 tiles' worth of cells: two steps per workgroup
+    (3, 7, 2, 2, 5, False),
+    (3, 24, 4, 3, 2, True),
+])
+def test_every_face_has_its_place(D, n, Q, R, batch, reuse):
+    geoms = [cg.make_geometry(cg.ball_outside((0.5, 0.47, 0.52)[:D], 0.2 + 0.03 * i), n, Q) for i in range(batch)]
+    b = cc.Builder([cc.DeviceGeometry.from_host(g, "cuda") for g in geoms], R, reuse_templates=reuse)
+    st = b.build()
+    first = st.val[: st.sizes.nnz].clone()
+    st.status.fill_(99)
+    st.val.fill_(float("nan"))
+    b.build(out=st)
+    assert int(st.status[: st.sizes.n_face].max()) < 99
+    assert torch.equal(st.val[: st.sizes.nnz], first) and bool(torch.isfinite(first).all())
+    rows = np.diff(st.row_ptr.cpu().numpy())
+    M = {(2, 2): 6, (2, 4): 15, (3, 2): 10, (3, 4): 35}[D, Q]
+    solved = rows[rows >= M]
+    hist = np.bincount((solved - 1) // 16, minlength=8)
+    counts = (ctypes.c_int64 * 8)()
+    load().cutcell_last_bin_faces(counts, 8)
+    bins, reused = np.array(counts), load().cutcell_last_reused_faces()
+    assert bins.sum() + reused == len(solved) and np.all(bins <= hist)
+    if not reuse:
+        assert reused == 0 and np.array_equal(bins, hist)
+    print(f"[gpu] D{D} n{n} x{batch}: bins {bins.tolist()}, copies {reused}, short {int((rows < M).sum())}")
