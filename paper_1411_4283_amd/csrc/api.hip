@@ -134,6 +134,16 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
     t.qr_b = (double*)take(sizeof(double) * t.qr_slots * 2 * kMaxRows * (M | 1));
   }
   t.geoms = (GeomPtrs*)take(sizeof(GeomPtrs) * G);
+  {
+    // The bytes that a caller has to bring decide which batches a buffer of a given size, and
+    // the static scratch, take.  They stay what they were when the neighbour masks of every
+    // face and the keys and buffers of a radix sort lay here; later arrays come out of this.
+    const long long en = 2 * o.path_radius + 2, et = en - 1, window = o.dim == 3 ? en * et * et : en * et;
+    const size_t per_face = 8 * ((window + 63) / 64) + 20 + (totface > 1024 ? 12 : 0);
+    const size_t kept = per_face * (size_t)totface;
+    const size_t since = align_up(sizeof(int32_t) * (kNBuckets + 1) * order_tiles(G * g.ncell)) + 256;
+    if (kept > since) off += align_up(kept - since);
+  }
   t.bytes = off;
   if (w) *w = t;
   return off;
