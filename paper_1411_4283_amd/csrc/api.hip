@@ -189,20 +189,6 @@ static int validate(const cutcell_geom* geoms, int G, const cutcell_opts* o) {
   return CUTCELL_OK;
 }
 
-// EB cells must be strictly ascending, inside the grid and in volumes (checked on the
-// device before anything indexes with them)
-__global__ void k_check_eb(int G, long long ncell, int M, const GeomPtrs* __restrict__ geoms, int32_t* bad) {
-  const int gi = blockIdx.y;
-  long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  const GeomPtrs gp = geoms[gi];
-  if (e >= gp.n_eb) return;
-  const int32_t c = gp.eb_cell[e];
-  bool ok = c >= 0 && c < ncell;
-  if (ok && e > 0) ok = gp.eb_cell[e - 1] < c;
-  if (ok) ok = gp.vol_mom[(long long)c * M] > 0.0;
-  if (!ok) atomicOr(bad, 1);
-}
-
 struct Prepared {
   Work w;
   std::vector<int64_t> counts, offs;
@@ -229,13 +215,9 @@ static int prepare(const cutcell_geom* geoms, int G, const cutcell_opts* o, void
   }
   CC_HIP(hipMemcpyAsync(w.geoms, gp.data(), sizeof(GeomPtrs) * G, hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 2LL, 0);
-  const int M = binom(o->order + o->dim, o->dim);
   int maxeb = 0;
   for (int i = 0; i < G; ++i) maxeb = std::max(maxeb, geoms[i].n_eb);
-  if (maxeb > 0)
-    hipLaunchKernelGGL(k_check_eb, dim3((unsigned)((maxeb + 255) / 256), G), dim3(256), 0, st, G, w.dims.ncell, M,
-                       w.geoms, w.flagged + 1);
-  rc = enumerate_batch(w, *o, st);
+  rc = enumerate_batch(w, *o, maxeb, st);
   if (rc) return rc;
   P->counts.assign(4 * G, 0);
   P->offs.assign(3 * (G + 1), 0);

@@ -92,7 +92,8 @@ struct Transpose {
 };
 
 // enumeration (Sec. 2.1): flags, maps, global face table, counts and offsets
-int enumerate_batch(const Work& w, const cutcell_opts& o, hipStream_t st);
+// (max_eb: the most EB cells of a geometry; flagged[1] is set where one is not valid)
+int enumerate_batch(const Work& w, const cutcell_opts& o, long long max_eb, hipStream_t st);
 // neighbour rows (Sec. 2.4): count (fill = false) or write col[] (fill = true)
 int neighbour_rows(const Work& w, const cutcell_opts& o, long long n_face, const int64_t* row_ptr, int32_t* col,
                    bool fill, hipStream_t st);

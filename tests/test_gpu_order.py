@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import cutgeom as cg
+import oracle
 
 torch = pytest.importorskip("torch")
 import paper_1411_4283_amd as cc  # noqa: E402
@@ -47,3 +48,17 @@ def test_every_face_has_its_place(D, n, Q, R, batch, reuse):
     if not reuse:
         assert reused == 0 and np.array_equal(bins, hist)
     print(f"[gpu] D{D} n{n} x{batch}: bins {bins.tolist()}, copies {reused}, short {int((rows < M).sum())}")
+
+
+@pytest.mark.parametrize("D,R,n", [(2, 1, 24), (2, 4, 51), (2, 3, 52), (3, 1, 12), (3, 2, 12), (3, 3, 20)])
+def test_regular_cells_and_short_scans(D, R, n):
+    """Rows of every face against the oracle's search on grids whose inner cells are regular
+    out to the path radius, with flag spaces of one to five scan tiles (the one-workgroup
+    scan takes up to four) and more."""
+    g = cg.make_geometry(cg.ball_outside((0.5, 0.47, 0.52)[:D], 0.15), n, 2)
+    st = cc.Builder(cc.DeviceGeometry.from_host(g, "cuda"), R).build()
+    en = oracle.enumerate_geometry(g)
+    rp, col = st.row_ptr.cpu().numpy(), st.col.cpu().numpy()
+    assert st.sizes.n_face == en.n_face
+    for f in range(en.n_face):
+        assert np.array_equal(col[rp[f]:rp[f + 1]], oracle.neighbours(en, f, R)), f
