@@ -82,6 +82,9 @@ static int static_scratch(void** out) {
   return CUTCELL_OK;
 }
 
+// 64-bit words of counts, offs, flagged and qr_count
+static size_t host_words(size_t G) { return 4 * G + 3 * (G + 1) + 2; }
+
 size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   Work t{};
   t.dims = make_dims(o);
@@ -116,8 +119,10 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.tface = (int32_t*)take(sizeof(int32_t) * 3 * G);
   t.tmpl = (int32_t*)take(sizeof(int32_t) * totface);
   t.order_hist = (int32_t*)take(sizeof(int32_t) * (kNBuckets + 1) * order_tiles(G * g.ncell));
-  t.counts = (int64_t*)take(sizeof(int64_t) * 4 * G);
-  t.offs = (int64_t*)take(sizeof(int64_t) * 3 * (G + 1));
+  t.counts = (int64_t*)take(sizeof(int64_t) * host_words(G));
+  t.offs = t.counts + 4 * (size_t)G;
+  t.flagged = (int32_t*)(t.offs + 3 * ((size_t)G + 1));
+  t.qr_count = t.flagged + 2;
   t.fcode = (int32_t*)take(sizeof(int32_t) * totface);
   t.fref = (int32_t*)take(sizeof(int32_t) * totface);
   t.nrows = (int32_t*)take(sizeof(int32_t) * totface);
@@ -125,8 +130,6 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.rp_tmp = (int64_t*)take(sizeof(int64_t) * (totface + 1));
   t.perm = (int32_t*)take(sizeof(int32_t) * totface);
   t.bins = (int32_t*)take(sizeof(int32_t) * kBinWords);
-  t.flagged = (int32_t*)take(sizeof(int32_t) * 2);
-  t.qr_count = (int32_t*)take(sizeof(int32_t));
   t.qr_list = (int32_t*)take(sizeof(int32_t) * totface);
   {
     const int M = binom(o.order + o.dim, o.dim);
@@ -189,6 +192,26 @@ static int validate(const cutcell_geom* geoms, int G, const cutcell_opts* o) {
   return CUTCELL_OK;
 }
 
+// Up to kGeomsByValue geometries travel as an argument of the first launch, which also clears
+// flagged and qr_count: a copy from pageable memory costs the host more
+// (whole build of a 2D 32^2 order-2 geometry: 238 us with it, eight copies to the host and three
+// on the device, 159 us with this, three copies to the host and none on the device).
+constexpr int kGeomsByValue = 32;
+struct GeomsByValue {
+  GeomPtrs g[kGeomsByValue];
+};
+static_assert(sizeof(GeomsByValue) <= 3072, "the geometries must fit among a kernel's arguments");
+
+__global__ __launch_bounds__(64) void k_start(GeomsByValue v, int G, GeomPtrs* geoms, int32_t* flagged) {
+  const int t = threadIdx.x;
+  if (t < 4) flagged[t] = 0;
+  constexpr int W = sizeof(GeomPtrs) / 8;
+  static_assert(sizeof(GeomPtrs) % 8 == 0, "whole words");
+  const unsigned long long* src = (const unsigned long long*)v.g;
+  unsigned long long* dst = (unsigned long long*)geoms;
+  for (int i = t; i < G * W; i += 64) dst[i] = src[i];
+}
+
 struct Prepared {
   Work w;
   std::vector<int64_t> counts, offs;
@@ -213,20 +236,27 @@ static int prepare(const cutcell_geom* geoms, int G, const cutcell_opts* o, void
     gp[i].eb_nmom = geoms[i].eb_nmom;
     gp[i].n_eb = geoms[i].n_eb;
   }
-  CC_HIP(hipMemcpyAsync(w.geoms, gp.data(), sizeof(GeomPtrs) * G, hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 2LL, 0);
+  if (G <= kGeomsByValue) {
+    GeomsByValue v{};
+    std::copy(gp.begin(), gp.end(), v.g);
+    hipLaunchKernelGGL(k_start, dim3(1), dim3(64), 0, st, v, G, w.geoms, w.flagged);
+  } else {
+    CC_HIP(hipMemcpyAsync(w.geoms, gp.data(), sizeof(GeomPtrs) * G, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 4LL, 0);
+  }
   int maxeb = 0;
   for (int i = 0; i < G; ++i) maxeb = std::max(maxeb, geoms[i].n_eb);
   rc = enumerate_batch(w, *o, maxeb, st);
   if (rc) return rc;
-  P->counts.assign(4 * G, 0);
-  P->offs.assign(3 * (G + 1), 0);
-  int32_t bad = 0;
-  CC_HIP(hipMemcpyAsync(P->counts.data(), w.counts, sizeof(int64_t) * 4 * G, hipMemcpyDeviceToHost, st));
-  CC_HIP(hipMemcpyAsync(P->offs.data(), w.offs, sizeof(int64_t) * 3 * (G + 1), hipMemcpyDeviceToHost, st));
-  CC_HIP(hipMemcpyAsync(&bad, w.flagged + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  const size_t words = host_words(G);
+  std::vector<int64_t> back(words);   // counts, offs, flagged
+  CC_HIP(hipMemcpyAsync(back.data(), w.counts, sizeof(int64_t) * words, hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
-  if (bad) return fail(CUTCELL_E_INVALID_ARG, "eb_cell must be strictly ascending cells with kappa > 0");
+  P->counts.assign(back.begin(), back.begin() + 4 * (size_t)G);
+  P->offs.assign(back.begin() + 4 * (size_t)G, back.end() - 2);
+  int32_t flags[4];
+  std::memcpy(flags, &back[words - 2], sizeof(flags));
+  if (flags[1]) return fail(CUTCELL_E_INVALID_ARG, "eb_cell must be strictly ascending cells with kappa > 0");
   for (int i = 0; i < G; ++i) {
     P->n_vol += P->counts[4 * i + 0];
     P->n_eb += P->counts[4 * i + 1];
@@ -245,22 +275,16 @@ static int count_rows(const Prepared& P, const cutcell_opts* o, int64_t* row_ptr
   const Work& w = P.w;
   int rc = neighbour_rows(w, *o, P.n_face, nullptr, nullptr, false, st);
   if (rc) return rc;
-  rc = count_buckets(w, binom(o->order + o->dim, o->dim), tmpl, st);
-  if (rc) return rc;
-  int64_t total = 0;
   if (P.n_face > 0) {
-    rc = exclusive_scan<int32_t, int64_t>(w.nrows, P.n_face, P.n_face, 1, row_ptr, P.n_face, row_ptr ? row_ptr + P.n_face : nullptr,
-                                          w.scan64, st);
+    rc = exclusive_scan<int32_t, int64_t>(w.nrows, P.n_face, P.n_face, 1, row_ptr, P.n_face, row_ptr + P.n_face, w.scan64,
+                                          st);
     if (rc) return rc;
   }
-  const int64_t zero = 0;
+  rc = count_buckets(w, binom(o->order + o->dim, o->dim), tmpl, P.n_face, row_ptr, st);
+  if (rc) return rc;
   CC_HIP(hipMemcpyAsync(bins, w.bins, sizeof(int32_t) * kBinWords, hipMemcpyDeviceToHost, st));
-  if (row_ptr && P.n_face > 0)
-    CC_HIP(hipMemcpyAsync(&total, row_ptr + P.n_face, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  else if (row_ptr)   // no faces: row_ptr = [0]
-    CC_HIP(hipMemcpyAsync(row_ptr, &zero, sizeof(int64_t), hipMemcpyHostToDevice, st));
   CC_HIP(hipStreamSynchronize(st));
-  *nnz = total;
+  std::memcpy(nnz, bins + 2 * kNBuckets + 2, sizeof(int64_t));
   return CUTCELL_OK;
 }
 
@@ -391,7 +415,7 @@ static int build_common(const cutcell_geom* geoms, int32_t n_geom, const cutcell
   }
   if (rc) return rc;
   timer.mark();
-  rc = volume_tables(w, *opts, P.n_vol, out->vol_face, out->vol_scale, st);
+  rc = volume_tables(w, *opts, out->vol_face, out->vol_scale, out->phi_off, out->vol_off, out->face_off, st);
   if (rc) return rc;
   if (out->tmpl && P.n_face > 0) {   // each face's template, -1 where it was solved itself
     if (opts->reuse_templates)
@@ -401,18 +425,13 @@ static int build_common(const cutcell_geom* geoms, int32_t n_geom, const cutcell
                          -1);
   }
   timer.mark();
-  const size_t ob = sizeof(int64_t) * (n_geom + 1);
-  CC_HIP(hipMemcpyAsync(out->phi_off, w.offs, ob, hipMemcpyDeviceToDevice, st));
-  CC_HIP(hipMemcpyAsync(out->vol_off, w.offs + (n_geom + 1), ob, hipMemcpyDeviceToDevice, st));
-  CC_HIP(hipMemcpyAsync(out->face_off, w.offs + 2 * (n_geom + 1), ob, hipMemcpyDeviceToDevice, st));
-  int32_t flagged = 0, nqr = 0;
-  CC_HIP(hipMemcpyAsync(&flagged, w.flagged, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  CC_HIP(hipMemcpyAsync(&nqr, w.qr_count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  int32_t last[4];   // flagged, -, qr_count
+  CC_HIP(hipMemcpyAsync(last, w.flagged, sizeof(last), hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
   CC_HIP(hipGetLastError());
-  g_last_qr = nqr;
+  g_last_qr = last[2];
   timer.finish();
-  return flagged ? CUTCELL_W_FLAGGED_FACES : CUTCELL_OK;
+  return last[0] ? CUTCELL_W_FLAGGED_FACES : CUTCELL_OK;
 }
 
 int cutcell_build_stencils(const cutcell_geom* geoms, int32_t n_geom, const cutcell_opts* opts,
@@ -760,7 +779,7 @@ int cutcell_stencils_backward(const cutcell_geom* geoms, int32_t n_geom, const c
   // bin the faces by their row counts again
   rc = rows_per_face(w, P.n_face, st_->row_ptr, st);
   if (rc) return rc;
-  rc = count_buckets(w, M, nullptr, st);
+  rc = count_buckets(w, M, nullptr, P.n_face, nullptr, st);
   if (rc) return rc;
   rc = order_faces(w, M, nullptr, st);
   if (rc) return rc;

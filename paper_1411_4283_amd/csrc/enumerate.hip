@@ -652,9 +652,16 @@ int neighbour_rows(const Work& w, const cutcell_opts& o, long long n_face, const
 __global__ void k_volume_tables(GridDims g, int G, int M, double hD, const GeomPtrs* __restrict__ geoms,
                                 const int32_t* __restrict__ vol_id, const int32_t* __restrict__ eb_id,
                                 const int32_t* __restrict__ face_id, const int64_t* __restrict__ counts,
-                                const int64_t* __restrict__ offs, int32_t* vol_face, double* vol_scale) {
+                                const int64_t* __restrict__ offs, int32_t* vol_face, double* vol_scale,
+                                int64_t* phi_off, int64_t* vol_off, int64_t* face_off) {
   const int gi = blockIdx.y;
   long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x <= (gi == 0 ? 1 : 0)) {   // offsets of geometry gi + 1, and of geometry 0
+    const int i = threadIdx.x == 0 ? gi + 1 : 0;
+    phi_off[i] = offs[i];
+    vol_off[i] = offs[(G + 1) + i];
+    face_off[i] = offs[2 * (G + 1) + i];
+  }
   if (c >= g.ncell) return;
   const int32_t v = vol_id[gi * g.ncell + c];
   if (v < 0) return;
@@ -675,14 +682,14 @@ __global__ void k_volume_tables(GridDims g, int G, int M, double hD, const GeomP
   vol_scale[V] = 1.0 / (geoms[gi].vol_mom[c * M] * hD);
 }
 
-int volume_tables(const Work& w, const cutcell_opts& o, long long n_vol_total, int32_t* vol_face, double* vol_scale,
-                  hipStream_t st) {
-  if (n_vol_total <= 0) return CUTCELL_OK;
+int volume_tables(const Work& w, const cutcell_opts& o, int32_t* vol_face, double* vol_scale, int64_t* phi_off,
+                  int64_t* vol_off, int64_t* face_off, hipStream_t st) {
   const int M = binom(o.order + o.dim, o.dim);
   double hD = 1.0;
   for (int d = 0; d < o.dim; ++d) hD *= o.h;
   hipLaunchKernelGGL(k_volume_tables, dim3(blocks_for(w.dims.ncell, 256), w.G), dim3(256), 0, st, w.dims, w.G, M, hD,
-                     w.geoms, w.vol_id, w.eb_id, w.face_id, w.counts, w.offs, vol_face, vol_scale);
+                     w.geoms, w.vol_id, w.eb_id, w.face_id, w.counts, w.offs, vol_face, vol_scale, phi_off, vol_off,
+                     face_off);
   CC_HIP(hipGetLastError());
   return CUTCELL_OK;
 }

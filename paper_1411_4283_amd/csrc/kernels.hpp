@@ -12,7 +12,7 @@ constexpr int kMaxBins = 8;     // row-count bins of 16 rows: N <= 16, 32, ..., 
 constexpr int kBinRows = 16;
 constexpr int kMaxRows = kMaxBins * kBinRows;
 constexpr int kNBuckets = kMaxBins + 2;   // then faces with N < M, then template copies
-constexpr int kBinWords = 2 * kNBuckets + 1;       // counts, starts, max rows
+constexpr int kBinWords = 2 * kNBuckets + 4;       // counts, starts, max rows, unused, nonzeros (64 bits)
 constexpr int kInfoPad = 32;    // bytes of padding of cellinfo on either side
 constexpr int kXcds = 8;        // MI355X: workgroups are dealt to 8 XCDs (own L2 each) in turn
 constexpr int kQrSlots = 1024;  // workgroups of the QR path, each with a slot of workspace
@@ -42,17 +42,18 @@ struct Work {
   int32_t* tface;       // [G][3]      template face per direction, or INT32_MAX
   int32_t* tmpl;        // [G*maxface] template of each face whose stencil is copied, else -1
   int32_t* order_hist;  // [kNBuckets + 1][order_tiles] faces per bucket and tile of cells, most rows per tile
+  // counts, offs, flagged and qr_count follow each other: one copy brings them to the host
   int64_t* counts;      // [G][4]      n_vol, n_eb, n_box, n_gface
   int64_t* offs;        // [3][G+1]    phi_off, vol_off, face_off
+  int32_t* flagged;     // [2] flagged faces, bad EB input
+  int32_t* qr_count;    // [1] faces left to the Householder QR path
   int32_t* fcode;       // [G*maxface] per global flux face
   int32_t* fref;        // [G*maxface] lattice face (grid/box) or EB index
   int32_t* nrows;       // [G*maxface]
   int64_t* scan64;      // int64 scan tiles over G*maxface
   int64_t* rp_tmp;      // [G*maxface + 1] row offsets when the caller has none (query)
   int32_t* perm;        // [G*maxface]
-  int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows
-  int32_t* flagged;     // [2] flagged faces, bad EB input
-  int32_t* qr_count;    // [1] faces left to the Householder QR path
+  int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows, nonzeros
   int32_t* qr_list;     // [G*maxface] those faces
   double* qr_b;         // [qr_slots][2][kMaxRows * MS] the QR path's exact B per workgroup
   int qr_slots;         // min(kQrSlots, G*maxface)
@@ -97,16 +98,17 @@ int enumerate_batch(const Work& w, const cutcell_opts& o, long long max_eb, hipS
 // neighbour rows (Sec. 2.4): count (fill = false) or write col[] (fill = true)
 int neighbour_rows(const Work& w, const cutcell_opts& o, long long n_face, const int64_t* row_ptr, int32_t* col,
                    bool fill, hipStream_t st);
-// volume -> face table and 1/(kappa h^D)
-int volume_tables(const Work& w, const cutcell_opts& o, long long n_vol_total, int32_t* vol_face,
-                  double* vol_scale, hipStream_t st);
+// volume -> face table and 1/(kappa h^D), and a copy of the offsets (each [G+1])
+int volume_tables(const Work& w, const cutcell_opts& o, int32_t* vol_face, double* vol_scale, int64_t* phi_off,
+                  int64_t* vol_off, int64_t* face_off, hipStream_t st);
 // binning by row count (Sec. 2.2.1)
 // `tmpl` (or null): faces with tmpl >= 0 go to the template-copy bucket.  count_buckets
-// leaves the buckets' counts, their starts and the most rows of a face in w.bins;
+// leaves the buckets' counts, their starts, the most rows of a face and row_ptr[n_face] in
+// w.bins (and sets row_ptr[0] = 0 where there are no faces; row_ptr may be null);
 // order_faces then writes w.perm: faces grouped by bucket, inside a bucket by the cell they
 // sit at (same M and tmpl)
 int order_tiles(long long cells);
-int count_buckets(const Work& w, int M, const int32_t* tmpl, hipStream_t st);
+int count_buckets(const Work& w, int M, const int32_t* tmpl, long long n_face, int64_t* row_ptr, hipStream_t st);
 int order_faces(const Work& w, int M, const int32_t* tmpl, hipStream_t st);
 
 // bucket of face f: a 16-row bin, the faces with fewer rows than monomials, or the copies

@@ -109,9 +109,11 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_count(OrderArgs A, int3
   }
 }
 
-// hist becomes its exclusive sums; bins: the buckets' counts, their starts, the most rows
+// hist becomes its exclusive sums; bins: the buckets' counts, their starts, the most rows and
+// the nonzeros
 __global__ __launch_bounds__(1024) void k_order_scan(int tiles, int32_t* __restrict__ hist,
-                                                     const int32_t* __restrict__ tile_max, int32_t* __restrict__ bins) {
+                                                     const int32_t* __restrict__ tile_max, int32_t* __restrict__ bins,
+                                                     long long n_face, int64_t* __restrict__ row_ptr) {
   __shared__ int32_t wsum[16], wmax[16], start[kNBuckets + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int n = kNBuckets * tiles, per = (n + 1023) / 1024;
@@ -148,6 +150,10 @@ __global__ __launch_bounds__(1024) void k_order_scan(int tiles, int32_t* __restr
     int m = 0;
     for (int k = 0; k < 16; ++k) m = max(m, wmax[k]);
     bins[2 * kNBuckets] = m;
+    if (row_ptr) {
+      if (n_face == 0) row_ptr[0] = 0;
+      *(int64_t*)(bins + 2 * kNBuckets + 2) = n_face == 0 ? 0 : row_ptr[n_face];
+    }
   }
 }
 
@@ -228,12 +234,12 @@ static OrderArgs order_args(const Work& w, int M, const int32_t* tmpl) {
                    w.eb_id, w.counts, w.offs, w.nrows,            tmpl};
 }
 
-int count_buckets(const Work& w, int M, const int32_t* tmpl, hipStream_t st) {
+int count_buckets(const Work& w, int M, const int32_t* tmpl, long long n_face, int64_t* row_ptr, hipStream_t st) {
   const OrderArgs A = order_args(w, M, tmpl);
   hipLaunchKernelGGL(k_order_count, dim3(A.tiles), dim3(kOrderThreads), 0, st, A, w.order_hist,
                      w.order_hist + kNBuckets * A.tiles);
   hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, st, A.tiles, w.order_hist,
-                     w.order_hist + kNBuckets * A.tiles, w.bins);
+                     w.order_hist + kNBuckets * A.tiles, w.bins, n_face, row_ptr);
   CC_HIP(hipGetLastError());
   return CUTCELL_OK;
 }

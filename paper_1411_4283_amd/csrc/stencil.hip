@@ -81,7 +81,6 @@ static int run_bins(const Work& w, const cutcell_opts& o, const int32_t* bin_cou
     sc[b].route = route;
   }
   int rc = CUTCELL_E_UNSUPPORTED;
-  if (!bw) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.qr_count, 1LL, 0);
   if (qr_all) {
     // every face of the row bins (or of bin only_bin) by Householder QR
     long long first = 0, n = 0;
@@ -182,6 +181,7 @@ int tune_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count
       double tmin = 1e300;
       for (int r = 0; r < reps; ++r) {
         CC_HIP(hipEventRecord(e0, st));
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.qr_count, 1LL, 0);
         int rc = run_bins(w, o, bin_count, row_ptr, col, val, status, st, nullptr, trial, b);
         if (rc) return rc;
         CC_HIP(hipEventRecord(e1, st));
@@ -204,7 +204,7 @@ int tune_stencils(const Work& w, const cutcell_opts& o, const int32_t* bin_count
     out->blocks_per_xcd[b] = sc[b].per_xcd;
     out->split[b] = 0;
   }
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 1LL, 0);
+  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, w.flagged, 4LL, 0);   // and qr_count
   return run_bins(w, o, bin_count, row_ptr, col, val, status, st, nullptr, sc);
 }
 
