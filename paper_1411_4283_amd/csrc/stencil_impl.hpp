@@ -217,6 +217,54 @@ struct WaveMatrix {
 // contents of the slots concerned that are not in place are kept in registers, flat (18 per
 // lane for 32 slots), and exchanged (RowSwap).  Rows held in registers row by row (140 a
 // lane) left too few for the rest of the solve: 104 spilled, 3 of 13 ms.
+// The lines of monomials along each direction: idx[dir][line][p] is the one with exponent p in
+// `dir`, -1 past the order.
+template <int D, int Q>
+struct MonoLines {
+  static constexpr int L = D == 3 ? (Q + 1) * (Q + 2) / 2 : Q + 1;
+  int8_t idx[D][L][Q + 1];
+  constexpr MonoLines() : idx{} {
+    for (int dir = 0; dir < D; ++dir) {
+      int n = 0;
+      for (int i = 0; i < kNMono<D, Q>; ++i) {
+        if (kMono<D, Q>.e[i][dir] != 0) continue;
+        for (int p = 0; p <= Q; ++p) {
+          int at = -1;
+          for (int j = 0; j < kNMono<D, Q>; ++j) {
+            bool same = kMono<D, Q>.e[j][dir] == p;
+            for (int a = 0; a < D; ++a) same = same && (a == dir || kMono<D, Q>.e[j][a] == kMono<D, Q>.e[i][a]);
+            if (same) at = j;
+          }
+          idx[dir][n][p] = (int8_t)at;
+        }
+        ++n;
+      }
+    }
+  }
+};
+template <int D, int Q>
+inline constexpr MonoLines<D, Q> kMonoLines{};
+
+// Rows of small cells by lines of monomials (small_rows) or a lane per row (dd_row).  A row's
+// terms unrolled are 27 kB of code in 3D order 4, but 7 kB and less where a row has at most 15
+// moments, and there the exchanges cost more than they save: 3D order 4, 64^3 solves 9.14 and
+// 1.04 ms (96 and 128 rows) by rows, 8.43 and 0.87 ms by lines; 2D order 4, 256^2 star 329 and
+// 335 us; 3D order 2, 47^3 Neumann 816 and 876 us.  With Neumann EB faces, whose own rows need
+// the code of dd_row in any case, by rows as well: 3D order 4, whole 40^3 builds 3.80 and 4.20 ms.
+template <int D, int Q, bool NEU>
+inline constexpr bool kSmallByLines = !NEU && Dims<D, Q>::M > 16;
+
+// rows of small cells formed at a time
+template <int D, int Q>
+inline constexpr int kSmallBatch = 64 / MonoLines<D, Q>::L < 8 ? 64 / MonoLines<D, Q>::L : 8;
+
+// What the lanes that form a small cell's row have to know of it.
+struct SmallRow {
+  dd delta[3], scale;     // (centre - x0) / h; weight over zeroth moment
+  const double* src;      // as in RowSource
+  int dd_dir, slot;       // direction of a box face, else -1; the row's slot of Bs
+};
+
 template <int D, int Q>
 struct FaceSmem {
   static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
@@ -226,6 +274,10 @@ struct FaceSmem {
     double nus[D][M1];                              // EB normal moments about x0 (flux vector)
     double tr[256];                                 // one tile, for its transpose
     double vec[40];                                 // a vector that every lane reads
+    struct {
+      SmallRow small[kSmallBatch<D, Q>];            // rows of small cells being formed
+      double slo[kSmallBatch<D, Q> * M];            // the low parts of their entries
+    };
     struct {
       double buf[64];                               // the pivot block
       double pv[64];                                // the trailing rows' entries in its columns
@@ -661,6 +713,87 @@ __device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int n, i
   }
 }
 
+// The rows of the lanes in `mask` (this lane's: `rs`) in double-double, rounded into their
+// slots of Bs; sets their weights.  A lane takes a line of monomials of a row, direction after
+// direction -- the shifts of a line by the binomial theorem are the same sums in the same order
+// as in recentre_dd -- and passes the results on through shared memory, so that a few small
+// cells keep all lanes busy and the code is a loop over the directions.  One lane per row and
+// its 105 unrolled terms (27 kB of code, run for every face near a small cell) took 0.92 of
+// 9.14 ms of the 64^3 order-4 solves of up to 96 rows, 0.28 ms like this.
+template <int D, int Q, class SM>
+__device__ __forceinline__ void small_rows(SM& sm, int lane, unsigned long long mask, const RowSource& rs,
+                                           const dd* x0, double wpow, double& w, bool& finite) {
+  constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, LN = MonoLines<D, Q>::L, P = kSmallBatch<D, Q>;
+  const bool mine = (mask >> lane) & 1;
+  const int rank = __popcll(mask & ((1ULL << lane) - 1)), n = __popcll(mask);
+  SmallRow me{};
+  if (mine) {
+    double d2 = 0.0;
+    for (int ax = 0; ax < 3; ++ax) me.delta[ax] = dd_from(0.0);
+    for (int ax = 0; ax < D; ++ax) {
+      me.delta[ax] = dd_sub(dd_from(rs.ctr[ax]), x0[ax]);
+      d2 += me.delta[ax].hi * me.delta[ax].hi;
+    }
+    w = row_weight(d2, wpow);
+    me.scale = dd_div(dd_from(w), dd_from(rs.src[0]));
+    finite = finite && dd_isfinite(me.scale);
+    me.src = rs.src;
+    me.dd_dir = rs.dd;
+    me.slot = lane;
+  }
+  const int k = lane / LN, ln = lane % LN;
+#pragma unroll 1
+  for (int b0 = 0; b0 < n; b0 += P) {
+    lds_order();
+    if (mine && rank >= b0 && rank < b0 + P) sm.small[rank - b0] = me;
+    lds_order();
+    const bool on = k < P && b0 + k < n;
+    const SmallRow& row = sm.small[on ? k : 0];
+    const double* src = row.src;
+    double* hi = sm.Bs + row.slot * MS;
+    double* lo = sm.slo + (on ? k : 0) * M;
+#pragma unroll 1
+    for (int dir = 0; dir < D; ++dir) {
+      int id[Q + 1];
+      dd m[Q + 1], pw[Q + 1];
+      static_for<0, Q + 1>([&](auto I) {
+        id[I] = on ? kMonoLines<D, Q>.idx[dir][ln][I] : -1;
+        m[I] = dd_from(0.0);
+        if (id[I] >= 0) {
+          if (dir > 0) m[I] = dd{hi[id[I]], lo[id[I]]};
+          else {
+            const int sl = row.dd_dir < 0 ? id[I] : face_slot<D, Q>(id[I], row.dd_dir);
+            if (sl >= 0) m[I] = dd_from(src[sl]);
+          }
+        }
+      });
+      const dd delta = row.delta[dir];
+      pw[0] = dd_from(1.0);
+      static_for<1, Q + 1>([&](auto K) { pw[K] = dd_mul(pw[K - 1], delta); });
+      static_for_down<1, Q + 1>([&](auto I) {
+        dd acc = m[I];
+        static_for<0, I>([&](auto C) {
+          acc = dd_add(acc, dd_mul(dd_mul_d(pw[I - C], (double)binom(I, C)), m[C]));
+        });
+        m[I] = acc;
+      });
+      if (dir == D - 1)
+        static_for<0, Q + 1>([&](auto I) {
+          m[I] = dd_mul(m[I], row.scale);
+          finite = finite && (id[I] < 0 || dd_isfinite(m[I]));
+        });
+      lds_order();
+      static_for<0, Q + 1>([&](auto I) {
+        if (id[I] >= 0) {
+          hi[id[I]] = m[I].hi;
+          lo[id[I]] = m[I].lo;
+        }
+      });
+      lds_order();
+    }
+  }
+}
+
 // Rows, Gram matrix, inverse and the refined semi-normal solve of one face with at most
 // NPAD (64, 96 or 128) rows.  Leaves rows 0..63 of B in Bs and the ones past 64 in sw, the
 // inverse in W, weights and z of rows lane and lane + 64 in wreg[], zreg[], and component
@@ -720,7 +853,10 @@ __device__ __forceinline__ int face_forward(const GridDims& g, const GeomPtrs& g
   });
   // row lane + 64 R of a small cell in double-double, into the lane's slot
   auto small_row = [&](auto R) {
-    if (small[R]) {
+    if constexpr (kSmallByLines<D, Q, NEU>) {
+      const unsigned long long mask = __ballot(small[R]);
+      if (mask) small_rows<D, Q>(sm, lane, mask, rsrc[R], x0dd, wpow, wreg[R], finite);
+    } else if (small[R]) {
       dd md[M];
       finite = dd_row<D, Q, NEU>(gp, rsrc[R], x0dd, wpow, md, wreg[R]) && finite;
       static_for<0, M>([&](auto I) { sm.Bs[lane * MS + I] = md[I].hi; });
