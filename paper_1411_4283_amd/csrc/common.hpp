@@ -168,13 +168,37 @@ struct GridDims {
   long long NF;         // total lattice faces
   long long nboxslot;   // cells adjacent to the box boundary, counted per (d, side)
   long long boxoff[7];  // offsets of the (d, side) slabs in the box slot space
+  double inv[2][2];     // 1 / n[d], 1 / (n[d] + 1)
 };
+
+// floor(a / n) for 0 <= a < 2^31, 1 <= n <= 2^14 + 1 and inv = 1 / n rounded: (a + 1/2) / n is
+// at least 1 / (2 n) from a whole number and the rounding below 2^-20 / n.  (Integer division
+// is some 20 instructions, 64-bit division some 100, and every row of every face has three.)
+__device__ __forceinline__ int quotient(int a, double inv) { return (int)((a + 0.5) * inv); }
+
+__device__ __forceinline__ void cell_coords(const GridDims& g, int c, int* x) {
+  const int q = quotient(c, g.inv[0][0]);
+  x[0] = c - q * g.n[0];
+  x[2] = quotient(q, g.inv[0][1]);
+  x[1] = q - x[2] * g.n[1];
+}
+// face `loc` of direction d's lattice
+__device__ __forceinline__ void face_coords(const GridDims& g, int d, int loc, int* j) {
+  const int q = quotient(loc, d == 0 ? g.inv[1][0] : g.inv[0][0]);
+  j[0] = loc - q * (g.n[0] + (d == 0));
+  j[2] = quotient(q, d == 1 ? g.inv[1][1] : g.inv[0][1]);
+  j[1] = q - j[2] * (g.n[1] + (d == 1));
+}
 
 inline GridDims make_dims(const cutcell_opts& o) {
   GridDims g{};
   g.D = o.dim;
   for (int d = 0; d < 3; ++d) g.n[d] = (d < o.dim) ? o.n[d] : 1;
   g.ncell = (long long)g.n[0] * g.n[1] * g.n[2];
+  for (int d = 0; d < 2; ++d) {
+    g.inv[0][d] = 1.0 / g.n[d];
+    g.inv[1][d] = 1.0 / (g.n[d] + 1);
+  }
   g.foff[0] = 0;
   for (int d = 0; d < 3; ++d) {
     long long m = 1;

@@ -33,11 +33,7 @@ __device__ __forceinline__ int lattice_dir(const GridDims& g, long long lf) {
 
 // (32-bit arithmetic: a geometry's lattice has fewer than 2^31 faces, checked on entry)
 __device__ __forceinline__ void lattice_coords(const GridDims& g, int d, long long lf, int* j) {
-  const int loc = (int)(lf - g.foff[d]);
-  const int m0 = g.n[0] + (d == 0), m1 = g.n[1] + (d == 1);
-  j[0] = loc % m0;
-  j[1] = (loc / m0) % m1;
-  j[2] = loc / (m0 * m1);
+  face_coords(g, d, (int)(lf - g.foff[d]), j);
 }
 
 __device__ __forceinline__ long long lattice_index(const GridDims& g, int d, const int* j) {
@@ -179,7 +175,8 @@ __global__ void k_cellinfo(GridDims g, const int32_t* __restrict__ vol_id, const
   const long long o = (long long)gi * g.ncell + c;
   unsigned v = vol_id[o] >= 0 ? 1u : 0u;
   if (v) {
-    int x[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+    int x[3];
+    cell_coords(g, (int)c, x);
     for (int d = 0; d < g.D; ++d)
       for (int s = 0; s < 2; ++s) {
         int j[3] = {x[0], x[1], x[2]};
@@ -204,7 +201,8 @@ __global__ __launch_bounds__(256) void k_ball_regular(GridDims g, const uint8_t*
   const long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (c >= g.ncell) return;
   const long long o = (long long)gi * g.ncell + c;
-  const int x[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+  int x[3];
+  cell_coords(g, (int)c, x);
   bool r = true;
 #pragma unroll
   for (int d = 0; d < D; ++d) r = r && x[d] >= R + 1 && x[d] <= g.n[d] - 2 - R;
@@ -469,10 +467,10 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighbourArgs A) {
 #pragma unroll
       for (int ax = 0; ax < D; ++ax) org[ax] = j[ax] - R - (ax == dn);
     } else {
-      const int c = A.geoms[gi].eb_cell[rf];
-      org[0] = c % g.n[0] - R;
-      org[1] = (c / g.n[0]) % g.n[1] - R;
-      if (D == 3) org[2] = c / (g.n[0] * g.n[1]) - R;
+      int x[3];
+      cell_coords(g, A.geoms[gi].eb_cell[rf], x);
+#pragma unroll
+      for (int ax = 0; ax < D; ++ax) org[ax] = x[ax] - R;
     }
 #pragma unroll
     for (int ax = 0; ax < D; ++ax) ext[ax] = ax == nrm ? W::EN : W::ET;
@@ -668,7 +666,8 @@ __global__ void k_volume_tables(GridDims g, int G, int M, double hD, const GeomP
   const int D = g.D;
   const long long V = offs[(G + 1) + gi] + v;
   const long long F0 = offs[2 * (G + 1) + gi];
-  int x[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+  int x[3];
+  cell_coords(g, (int)c, x);
   const int S = 2 * D + 1;
   for (int d = 0; d < D; ++d)
     for (int s = 0; s < 2; ++s) {
@@ -734,7 +733,8 @@ __global__ void k_canon0(GridDims g, int M, int Mf, const GeomPtrs* __restrict__
   const long long o = (long long)gi * g.ncell + c;
   const unsigned full = (1u << (1 + 2 * g.D)) - 1u;
   bool r = info[o] == full;
-  const int x[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+  int x[3];
+  cell_coords(g, (int)c, x);
   for (int d = 0; d < g.D; ++d) r = r && x[d] >= 1 && x[d] <= g.n[d] - 2;
   const int32_t rc = ref[gi];
   r = r && rc != kNone;

@@ -54,7 +54,8 @@ __device__ __forceinline__ void faces_of_cell(const OrderArgs& A, long long i, F
   if (i >= A.G * g.ncell) return;
   const int gi = (int)(i / g.ncell);
   const int c = (int)(i - gi * g.ncell);
-  const int x[3] = {c % g.n[0], (c / g.n[0]) % g.n[1], c / (g.n[0] * g.n[1])};
+  int x[3];
+  cell_coords(g, c, x);
   const long long F0 = A.offs[2 * (A.G + 1) + gi];
   const int32_t* fid = A.face_id + (long long)gi * g.NF;
 #pragma unroll

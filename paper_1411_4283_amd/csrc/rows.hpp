@@ -61,7 +61,8 @@ __device__ __forceinline__ RowSource row_source(const GridDims& g, const GeomPtr
       rs.src = gp.eb_mom + e * M;
       rs.eb = (int32_t)e;
     }
-    const int ci[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+    int ci[3];
+    cell_coords(g, c, ci);
     for (int ax = 0; ax < D; ++ax) rs.ctr[ax] = ci[ax] + 0.5;
     rs.dd = -1;
     rs.loc = -1;
@@ -70,8 +71,8 @@ __device__ __forceinline__ RowSource row_source(const GridDims& g, const GeomPtr
     const int32_t lf = box_lf[phi_local - n_vol - n_eb];
     const int dd = (lf >= g.foff[1]) + (lf >= g.foff[2]);
     const long long loc = lf - g.foff[dd];
-    const int m0 = g.n[0] + (dd == 0), m1 = g.n[1] + (dd == 1);
-    const int j[3] = {(int)(loc % m0), (int)((loc / m0) % m1), (int)(loc / ((long long)m0 * m1))};
+    int j[3];
+    face_coords(g, dd, (int)loc, j);
     for (int ax = 0; ax < D; ++ax) rs.ctr[ax] = (ax == dd) ? (double)j[ax] : j[ax] + 0.5;
     rs.src = gp.face_mom[dd] + loc * Mf;
     rs.dd = dd;

@@ -321,15 +321,15 @@ __device__ __forceinline__ void face_x0(const GridDims& g, const GeomPtrs& gp, F
   for (int ax = 0; ax < 3; ++ax) { fi.x0h[ax] = 0.0; fi.off[ax] = 0.0; }
   fi.owner_cell = -1;
   if (fi.kind == 0) {
-    const long long loc = fi.ref - g.foff[dn];
-    const int m0 = g.n[0] + (dn == 0), m1 = g.n[1] + (dn == 1);
-    const int j[3] = {(int)(loc % m0), (int)((loc / m0) % m1), (int)(loc / ((long long)m0 * m1))};
+    int j[3];
+    face_coords(g, dn, (int)(fi.ref - g.foff[dn]), j);
     for (int ax = 0; ax < D; ++ax) fi.x0h[ax] = (ax == dn) ? (double)j[ax] : j[ax] + 0.5;
     return;
   }
   const int32_t c = gp.eb_cell[fi.ref];
   fi.owner_cell = c;
-  const int cown[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+  int cown[3];
+  cell_coords(g, c, cown);
   const double* vm = gp.vol_mom + (long long)c * M;
   const double k0 = vm[0];
   for (int ax = 0; ax < D; ++ax) {
@@ -346,7 +346,8 @@ __device__ __forceinline__ void face_x0_dd(const GridDims& g, const GeomPtrs& gp
   for (int ax = 0; ax < 3; ++ax) x0[ax] = dd_from(fi.x0h[ax]);
   if (fi.kind == 0) return;
   const int32_t c = fi.owner_cell;
-  const int cown[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+  int cown[3];
+  cell_coords(g, c, cown);
   const double* vm = gp.vol_mom + (long long)c * M;
   const dd k0 = dd_from(vm[0]);
   for (int ax = 0; ax < D; ++ax) x0[ax] = dd_add(dd_from(cown[ax] + 0.5), dd_div(dd_from(vm[1 + ax]), k0));
@@ -370,7 +371,8 @@ __device__ __forceinline__ void eb_normal_moments(const GridDims& g, const GeomP
     const double* src = gp.eb_nmom + ((long long)fi.ref * D + lane) * M1;
     static_for<0, M1>([&](auto I) { nu[I] = dd_from(src[I]); });
     const int32_t c = fi.owner_cell;
-    const int cown[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((long long)g.n[0] * g.n[1]))};
+    int cown[3];
+    cell_coords(g, c, cown);
     dd dl[3] = {dd_from(0.0), dd_from(0.0), dd_from(0.0)};
     for (int ax = 0; ax < D; ++ax) dl[ax] = dd_sub(dd_from(cown[ax] + 0.5), x0dd[ax]);   // (c - x0)/h
     recentre_dd<D, Q - 1>(nu, dl);
