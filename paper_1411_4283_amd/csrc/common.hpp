@@ -218,12 +218,22 @@ inline GridDims make_dims(const cutcell_opts& o) {
 }
 
 // device copy of the per-geometry input pointers
+// A pointer to HBM that is read from memory: the compiler cannot know its address space and
+// would read through it with flat instructions, which wait for shared memory as well.
+template <class T>
+struct GlobalPtr {
+  typedef const __attribute__((address_space(1))) T* Ptr;
+  Ptr p;
+  __host__ __device__ __forceinline__ void operator=(const T* q) { p = (Ptr)q; }
+  __device__ __forceinline__ operator const T*() const { return (const T*)p; }
+};
+
 struct GeomPtrs {
-  const double* vol_mom;
-  const double* face_mom[3];
-  const int32_t* eb_cell;
-  const double* eb_mom;
-  const double* eb_nmom;
+  GlobalPtr<double> vol_mom;
+  GlobalPtr<double> face_mom[3];
+  GlobalPtr<int32_t> eb_cell;
+  GlobalPtr<double> eb_mom;
+  GlobalPtr<double> eb_nmom;
   int32_t n_eb;
 };
 

@@ -261,7 +261,7 @@ inline constexpr int kSmallBatch = 64 / MonoLines<D, Q>::L < 8 ? 64 / MonoLines<
 // What the lanes that form a small cell's row have to know of it.
 struct SmallRow {
   dd delta[3], scale;     // (centre - x0) / h; weight over zeroth moment
-  const double* src;      // as in RowSource
+  GlobalPtr<double> src;  // as in RowSource
   int dd_dir, slot;       // direction of a box face, else -1; the row's slot of Bs
 };
 
@@ -1141,7 +1141,7 @@ __device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, 
                                              double* __restrict__ val, int8_t* __restrict__ status, int32_t* flagged) {
   constexpr int NR = (NPAD + 63) / 64;
   FaceInfo fi = face_info(A, t);
-  const GeomPtrs gp = A.geoms[fi.gi];
+  const GeomPtrs& gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
   WaveMatrix<D, Q> W;
   RowSwap<D, Q, NPAD - 64> sw;
@@ -1219,7 +1219,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, Q>
   if (t >= A.nbin) return;
   const int lane = threadIdx.x;
   FaceInfo fi = face_info(A, t);
-  const GeomPtrs gp = A.geoms[fi.gi];
+  const GeomPtrs& gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
   const int32_t* vol_cell = A.vol_cell_ws + (long long)fi.gi * A.g.ncell;
   const int32_t* box_lf = A.box_lf_ws + (long long)fi.gi * A.g.nboxslot;

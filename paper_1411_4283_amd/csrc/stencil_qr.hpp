@@ -108,7 +108,7 @@ __device__ void qr_face(const StencilArgs& A, int32_t F, QrSmem<D, Q>& sm, doubl
   using DM = Dims<D, Q>;
   constexpr int M = DM::M, MS = DM::MS, M1 = DM::M1;
   FaceInfo fi = face_info_of(A, F);
-  const GeomPtrs gp = A.geoms[fi.gi];
+  const GeomPtrs& gp = A.geoms[fi.gi];
   face_x0<D, Q>(A.g, gp, fi);
   dd x0[3];
   face_x0_dd<D, Q>(A.g, gp, fi, x0);
