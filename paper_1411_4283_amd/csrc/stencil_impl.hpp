@@ -715,6 +715,49 @@ __device__ __forceinline__ void column_sum_dot2(const SM& sm, int lane, int n, i
   }
 }
 
+// One direction's re-centring of line `ln` of a row (entries hi + lo, read from the row's
+// moments in the first direction), scaled in the last: the same sums in the same order as in
+// dd_row.  Returns false if it left a non-finite value.
+template <int D, int Q>
+__device__ __forceinline__ bool line_shift(int dir, int ln, const dd& delta, const dd& scale, const double* src,
+                                           int dd_dir, double* hi, double* lo) {
+  int id[Q + 1];
+  dd m[Q + 1], pw[Q + 1];
+  static_for<0, Q + 1>([&](auto I) {
+    id[I] = kMonoLines<D, Q>.idx[dir][ln][I];
+    m[I] = dd_from(0.0);
+    if (id[I] >= 0) {
+      if (dir > 0) m[I] = dd{hi[id[I]], lo[id[I]]};
+      else {
+        const int sl = dd_dir < 0 ? id[I] : face_slot<D, Q>(id[I], dd_dir);
+        if (sl >= 0) m[I] = dd_from(src[sl]);
+      }
+    }
+  });
+  pw[0] = dd_from(1.0);
+  static_for<1, Q + 1>([&](auto K) { pw[K] = dd_mul(pw[K - 1], delta); });
+  static_for_down<1, Q + 1>([&](auto I) {
+    dd acc = m[I];
+    static_for<0, I>([&](auto C) {
+      acc = dd_add(acc, dd_mul(dd_mul_d(pw[I - C], (double)binom(I, C)), m[C]));
+    });
+    m[I] = acc;
+  });
+  bool finite = true;
+  if (dir == D - 1)
+    static_for<0, Q + 1>([&](auto I) {
+      m[I] = dd_mul(m[I], scale);
+      finite = finite && (id[I] < 0 || dd_isfinite(m[I]));
+    });
+  static_for<0, Q + 1>([&](auto I) {
+    if (id[I] >= 0) {
+      hi[id[I]] = m[I].hi;
+      lo[id[I]] = m[I].lo;
+    }
+  });
+  return finite;
+}
+
 // The rows of the lanes in `mask` (this lane's: `rs`) in double-double, rounded into their
 // slots of Bs; sets their weights.  A lane takes a line of monomials of a row, direction after
 // direction -- the shifts of a line by the binomial theorem are the same sums in the same order
@@ -751,46 +794,11 @@ __device__ __forceinline__ void small_rows(SM& sm, int lane, unsigned long long 
     lds_order();
     const bool on = k < P && b0 + k < n;
     const SmallRow& row = sm.small[on ? k : 0];
-    const double* src = row.src;
     double* hi = sm.Bs + row.slot * MS;
     double* lo = sm.slo + (on ? k : 0) * M;
 #pragma unroll 1
     for (int dir = 0; dir < D; ++dir) {
-      int id[Q + 1];
-      dd m[Q + 1], pw[Q + 1];
-      static_for<0, Q + 1>([&](auto I) {
-        id[I] = on ? kMonoLines<D, Q>.idx[dir][ln][I] : -1;
-        m[I] = dd_from(0.0);
-        if (id[I] >= 0) {
-          if (dir > 0) m[I] = dd{hi[id[I]], lo[id[I]]};
-          else {
-            const int sl = row.dd_dir < 0 ? id[I] : face_slot<D, Q>(id[I], row.dd_dir);
-            if (sl >= 0) m[I] = dd_from(src[sl]);
-          }
-        }
-      });
-      const dd delta = row.delta[dir];
-      pw[0] = dd_from(1.0);
-      static_for<1, Q + 1>([&](auto K) { pw[K] = dd_mul(pw[K - 1], delta); });
-      static_for_down<1, Q + 1>([&](auto I) {
-        dd acc = m[I];
-        static_for<0, I>([&](auto C) {
-          acc = dd_add(acc, dd_mul(dd_mul_d(pw[I - C], (double)binom(I, C)), m[C]));
-        });
-        m[I] = acc;
-      });
-      if (dir == D - 1)
-        static_for<0, Q + 1>([&](auto I) {
-          m[I] = dd_mul(m[I], row.scale);
-          finite = finite && (id[I] < 0 || dd_isfinite(m[I]));
-        });
-      lds_order();
-      static_for<0, Q + 1>([&](auto I) {
-        if (id[I] >= 0) {
-          hi[id[I]] = m[I].hi;
-          lo[id[I]] = m[I].lo;
-        }
-      });
+      if (on) finite = line_shift<D, Q>(dir, ln, row.delta[dir], row.scale, row.src, row.dd_dir, hi, lo) && finite;
       lds_order();
     }
   }

@@ -1,6 +1,6 @@
 // Launches of the Householder QR path (stencil_qr.hpp): the faces the Gram path leaves to
 // it, or every face when the caller asks for this factorisation.
-#include "stencil_qr.hpp"
+#include "stencil_qr_wide.hpp"
 
 namespace cutcell {
 
@@ -19,19 +19,24 @@ int solve_qr_faces(const Work& w, const cutcell_opts& o, const int32_t* list, co
   A.h = o.h;
   A.wpow = o.weight_custom ? o.weight_power : 5.0;
   const bool neu = o.eb_bc == CUTCELL_BC_NEUMANN;
-  const dim3 g((unsigned)grid), b(64);
-#define CC_QR(DD, QQ)                                                                                           \
-  if (o.dim == DD && o.order == QQ) {                                                                           \
-    if (neu)                                                                                                    \
-      hipLaunchKernelGGL((k_stencil_qr<DD, QQ, true>), g, b, 0, st, A, list, count_dev, count_host, w.qr_b, val, \
-                         status, w.flagged);                                                                            \
-    else                                                                                                        \
-      hipLaunchKernelGGL((k_stencil_qr<DD, QQ, false>), g, b, 0, st, A, list, count_dev, count_host, w.qr_b, val, \
-                         status, w.flagged);                                                                    \
-    CC_HIP(hipGetLastError());                                                                                  \
-    return CUTCELL_OK;                                                                                          \
+  const dim3 g((unsigned)grid);
+#define CC_QR(DD, QQ, KERNEL, THREADS)                                                                                \
+  if (o.dim == DD && o.order == QQ) {                                                                                 \
+    hipLaunchKernelGGL(KERNEL, g, dim3(THREADS), 0, st, A, list, count_dev, count_host, w.qr_b, val, status, w.flagged); \
+    CC_HIP(hipGetLastError());                                                                                        \
+    return CUTCELL_OK;                                                                                                \
   }
-  CC_QR(2, 2) CC_QR(2, 4) CC_QR(3, 2) CC_QR(3, 4)
+  if (neu) {
+    CC_QR(2, 2, (k_stencil_qr<2, 2, true>), 64)
+    CC_QR(2, 4, (k_stencil_qr<2, 4, true>), 64)
+    CC_QR(3, 2, (k_stencil_qr<3, 2, true>), 64)
+    CC_QR(3, 4, (k_stencil_qr<3, 4, true>), 64)
+  } else {
+    CC_QR(2, 2, (k_stencil_qr<2, 2, false>), 64)
+    CC_QR(2, 4, (k_stencil_qr_wide<2, 4>), kWideThreads)
+    CC_QR(3, 2, (k_stencil_qr<3, 2, false>), 64)
+    CC_QR(3, 4, (k_stencil_qr_wide<3, 4>), kWideThreads)
+  }
 #undef CC_QR
   return fail(CUTCELL_E_UNSUPPORTED, "order/dimension");
 }

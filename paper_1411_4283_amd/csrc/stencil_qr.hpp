@@ -4,7 +4,8 @@
 // refinement that has not settled (k_stencil routes them here), and every face when the
 // caller asks for this factorisation.
 //
-// One wavefront owns one face; the factors live in shared memory, the exact B in a slot of
+// One wavefront owns one face (fourth order under Dirichlet conditions has four:
+// stencil_qr_wide.hpp); the factors live in shared memory, the exact B in a slot of
 // the workspace:
 //   1. rows in double-double: the offsets (x_i - x0)/h (exact half-integers for grid and
 //      box faces; for an EB face x0 = cell centre + first moments / zeroth moment), the
@@ -78,8 +79,8 @@ __device__ __forceinline__ void apply_reflector(const QrSmem<D, Q>& sm, int k, i
 }
 
 // x (lane p < M) <- R^-T x  (forward substitution; R^T is lower triangular)
-template <int D, int Q>
-__device__ __forceinline__ double solve_rt(const QrSmem<D, Q>& sm, int lane, double x) {
+template <int D, int Q, class SM>
+__device__ __forceinline__ double solve_rt(const SM& sm, int lane, double x) {
   constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS;
   for (int k = 0; k < M; ++k) {
     const double ak = readlane_f64(x, k) * sm.rdiag[k];
@@ -90,8 +91,8 @@ __device__ __forceinline__ double solve_rt(const QrSmem<D, Q>& sm, int lane, dou
 }
 
 // x (lane p < M) <- R^-1 x  (back substitution)
-template <int D, int Q>
-__device__ __forceinline__ double solve_r(const QrSmem<D, Q>& sm, int lane, double x) {
+template <int D, int Q, class SM>
+__device__ __forceinline__ double solve_r(const SM& sm, int lane, double x) {
   constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS;
   for (int k = M - 1; k >= 0; --k) {
     const double yk = readlane_f64(x, k) * sm.rdiag[k];
