@@ -36,7 +36,7 @@ def log(msg):
 KERNEL_SOURCES = ("paper_1411_4283_amd/csrc/stencil.hip", "paper_1411_4283_amd/csrc/stencil_impl.hpp",
                   "paper_1411_4283_amd/csrc/rows.hpp", "paper_1411_4283_amd/csrc/rows_dd.hpp",
                   "paper_1411_4283_amd/csrc/dd.hpp", "paper_1411_4283_amd/csrc/stencil_qr.hip",
-                  "paper_1411_4283_amd/csrc/stencil_qr.hpp",
+                  "paper_1411_4283_amd/csrc/stencil_qr.hpp", "paper_1411_4283_amd/csrc/stencil_qr_wide.hpp",
                   "paper_1411_4283_amd/csrc/common.hpp", "paper_1411_4283_amd/csrc/kernels.hpp",
                   "paper_1411_4283_amd/csrc/apply.hip", "paper_1411_4283_amd/csrc/gather.hpp")
 TRAFFIC_FILE = "profiles/traffic_3d_order4_sphere64.md"
@@ -646,7 +646,7 @@ def qr_all_timings(torch, cc, dg, R, st_ref, n_face, flops, reps=2):
     torch.cuda.empty_cache()
     return {"ms_per_build": ms, "faces_per_s": n_face / (ms * 1e-3), "tflops_lapack_count": flops / (ms * 1e-3) / 1e12,
             "max_rel_diff_vs_default_build": rel, "same_status": same_status,
-            "note": "every face by the QR path (one wave per face, factors in shared memory, the exact B in a "
+            "note": "every face by the QR path (one workgroup per face, factors in shared memory, the exact B in a "
                     "workspace slot, double-double rows and "
                     "residuals); the default build routes only ill-conditioned faces there"}
 

@@ -472,9 +472,9 @@ int cutcell_ritz(const cutcell_sizes* sizes, int32_t dim, const cutcell_stencils
 
 /* Observability: when enabled (per calling thread), cutcell_build_stencils records HIP
  * events on its stream between its phases, and cutcell_last_profile copies the last
- * build's phase durations in milliseconds into ms[0 .. n-1]: enumeration, row counts and
- * their scan, neighbour fill, binning, stencil solves, volume tables (-1 where a phase did
- * not run).  Returns the number of phases (6), or CUTCELL_E_INVALID_ARG. */
+ * build's phase durations in milliseconds into ms[0 .. n-1]: enumeration, row counts with
+ * their scan, the templates and the bucket counts, neighbour fill, processing order, stencil
+ * solves, volume tables (-1 where a phase did not run).  Returns the number of phases (6), or CUTCELL_E_INVALID_ARG. */
 void cutcell_set_profiling(int enable);
 int cutcell_last_profile(double* ms, int32_t n);
 

@@ -279,7 +279,7 @@ int enumerate_batch(const Work& w, const cutcell_opts& o, long long max_eb, hipS
 // ones between ball-regular cells from the fixed offsets, and searches the others in turn.
 // The fill pass searches again: that is cheaper than keeping the masks.  It is bound by the
 // latency of the search's dependent steps.  64^3, path radius 3 (724k faces, half of them
-// searched): count and fill 0.7 ms; with one cell per lane and step, a wave per face and the
+// searched): count and fill 0.76 ms; with one cell per lane and step, a wave per face and the
 // masks kept for the fill, 1.69 and 0.96 ms.
 
 template <int D, int R>

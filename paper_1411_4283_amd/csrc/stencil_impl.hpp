@@ -23,11 +23,12 @@
 // What bounds it, 64^3 minus a sphere, 3D order 4 (724k faces, 88 rows x 35 columns for most
 // of them): the FP64 pipe, which vector FMAs and matrix instructions share on MI355X (32
 // flop per cycle and SIMD either way), and the latency between dependent steps that two
-// waves per SIMD leave.  10.3 ms; with lane i holding row i of G (29 of 64 lanes idle in the
+// waves per SIMD leave.  8.7 ms; with lane i holding row i of G (29 of 64 lanes idle in the
 // sweep, one exchange through LDS per pivot, a transposition of G by lane permutes) and
-// every row in LDS (three waves on two SIMDs) it was 17.9 ms in six launches.  Of the 10.3,
-// rows of B 3.8 (0.9 for small cells), G 1.5, sweep 1.8, first z 0.5, refinement 1.7, the
-// 97- to 128-row faces 1.0.
+// every row in LDS (three waves on two SIMDs) it was 17.9 ms in six launches.  Of 10.3 ms
+// before the last changes to the rows (lines of small cells' rows -0.9, coordinates without
+// divisions -0.25, no flat loads -0.43), rows of B took 3.8, G 1.5, sweep 1.8, first z 0.5,
+// refinement 1.7, the 97- to 128-row faces 1.0.
 // Under Neumann EB conditions (a separate kernel instance) the EB rows are the
 // normal-derivative rows of eq. 'Neu moment eq for cp' and their values carry h^(D-1);
 // the EB faces themselves have a one-entry stencil (their area) and are written by
