@@ -25,10 +25,10 @@
 // flop per cycle and SIMD either way), and the latency between dependent steps that two
 // waves per SIMD leave.  8.7 ms; with lane i holding row i of G (29 of 64 lanes idle in the
 // sweep, one exchange through LDS per pivot, a transposition of G by lane permutes) and
-// every row in LDS (three waves on two SIMDs) it was 17.9 ms in six launches.  Of 10.3 ms
-// before the last changes to the rows (lines of small cells' rows -0.9, coordinates without
-// divisions -0.25, no flat loads -0.43), rows of B took 3.8, G 1.5, sweep 1.8, first z 0.5,
-// refinement 1.7, the 97- to 128-row faces 1.0.
+// every row in LDS (three waves on two SIMDs) it was 17.9 ms in six launches.  Of the 7.8 of
+// the faces of up to 96 rows: header 0.6, rows of B 2.2 (3.8 before small cells' rows went by
+// lines, coordinates without divisions and loads without flat instructions), G 1.4, sweep 2.0,
+// first z 0.5, refinement 1.1 (0.2 in compensated sums).
 // Under Neumann EB conditions (a separate kernel instance) the EB rows are the
 // normal-derivative rows of eq. 'Neu moment eq for cp' and their values carry h^(D-1);
 // the EB faces themselves have a one-entry stencil (their area) and are written by
