@@ -62,3 +62,21 @@ def test_regular_cells_and_short_scans(D, R, n):
     assert st.sizes.n_face == en.n_face
     for f in range(en.n_face):
         assert np.array_equal(col[rp[f]:rp[f + 1]], oracle.neighbours(en, f, R)), f
+
+
+@pytest.mark.parametrize("batch", [1, 32, 33])
+def test_batches_on_both_sides_of_the_argument_limit(batch):
+    """Geometries reach the device as a kernel argument (up to 32) or by a copy: a batch's
+    stencils are those of its geometries built alone, bit for bit."""
+    geoms = [cg.make_geometry(cg.ball_outside((0.5, 0.48), 0.2 + 0.004 * i), 9, 2) for i in range(batch)]
+    dev = [cc.DeviceGeometry.from_host(g, "cuda") for g in geoms]
+    st = cc.Builder(dev, 2).build()
+    val, rows, phi = [], [], 0
+    for d in dev:
+        s = cc.Builder(d, 2).build()
+        val.append(s.val[: s.sizes.nnz])
+        rows.append(s.col[: s.sizes.nnz] + phi)
+        phi += s.sizes.n_phi
+    assert torch.equal(st.val[: st.sizes.nnz], torch.cat(val))
+    assert torch.equal(st.col[: st.sizes.nnz], torch.cat(rows).to(st.col.dtype))
+    assert int(st.phi_off[-1]) == phi
