@@ -220,7 +220,8 @@ typedef struct {
                            face solved itself -- the input of cutcell_pack_count           */
 } cutcell_stencils;
 
-/* Bytes of device workspace the calls below need for this grid and batch size. */
+/* Bytes of device workspace the calls below need for this grid and batch size (0 without a
+ * dimension of 2 or 3, a grid of at least one cell and a geometry). */
 size_t cutcell_workspace_bytes(const cutcell_opts* opts, int32_t n_geom);
 
 /* Enumerates volumes, boundary faces and flux faces (Sec. 2.1) and counts each face's

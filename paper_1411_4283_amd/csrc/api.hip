@@ -152,6 +152,14 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   return off;
 }
 
+// The size functions are called before anything checks the options, and the layout divides by
+// the grid's extents.
+static bool has_cells(const cutcell_opts& o) {
+  for (int d = 0; d < o.dim; ++d)
+    if (o.n[d] < 1) return false;
+  return true;
+}
+
 static int validate(const cutcell_geom* geoms, int G, const cutcell_opts* o) {
   if (!o) return fail(CUTCELL_E_INVALID_ARG, "opts is NULL");
   if (o->dim != 2 && o->dim != 3) return fail(CUTCELL_E_UNSUPPORTED, "dim must be 2 or 3");
@@ -334,7 +342,7 @@ using namespace cutcell;
 extern "C" {
 
 size_t cutcell_workspace_bytes(const cutcell_opts* opts, int32_t n_geom) {
-  if (!opts || n_geom < 1 || (opts->dim != 2 && opts->dim != 3)) return 0;
+  if (!opts || n_geom < 1 || (opts->dim != 2 && opts->dim != 3) || !has_cells(*opts)) return 0;
   return layout_work(*opts, n_geom, nullptr, nullptr);
 }
 
@@ -722,7 +730,7 @@ int cutcell_apply_adjoint(const cutcell_sizes* sizes, int32_t dim, const cutcell
 
 size_t cutcell_backward_workspace_bytes(const cutcell_opts* opts, const cutcell_sizes* sizes) {
   if (!opts || !sizes || sizes->n_geom < 1 || (opts->dim != 2 && opts->dim != 3) ||
-      (opts->order != 2 && opts->order != 4))
+      (opts->order != 2 && opts->order != 4) || !has_cells(*opts))
     return 0;
   return layout_backward(*opts, sizes->n_geom, sizes->n_face, sizes->nnz, nullptr, nullptr);
 }
