@@ -35,15 +35,18 @@ __global__ void k_col_ptr(long long nnz, long long n_phi, const int32_t* __restr
   for (long long k = prev + 1; k <= cur; ++k) col_ptr[k] = i;
 }
 
-// The face of every CSR position, then of each listed one.  Bound by the gather's lines;
-// 1.4e7 nonzeros: 235 us as a binary search in row_ptr per nonzero, 21 + 95 us like this.
-__global__ __launch_bounds__(256) void k_row_face(long long n_face, const int64_t* __restrict__ row_ptr,
+// The face of every CSR position, then of each listed one.  The first row and the last one
+// reach to the ends of face_of, and no row past them, whatever row_ptr says of nnz.  Bound by
+// the gather's lines; 1.4e7 nonzeros: 235 us as a binary search in row_ptr per nonzero, 21 +
+// 95 us like this.
+__global__ __launch_bounds__(256) void k_row_face(long long n_face, long long nnz, const int64_t* __restrict__ row_ptr,
                                                   int32_t* __restrict__ face_of) {
   constexpr int SW = 16;   // lanes per row
   const long long f = (blockIdx.x * 256LL + threadIdx.x) / SW;
-  if (f >= n_face) return;
-  const int64_t b = row_ptr[f + 1];
-  for (int64_t j = row_ptr[f] + threadIdx.x % SW; j < b; j += SW) face_of[j] = (int32_t)f;
+  if (f > 0 && f >= n_face) return;
+  const int64_t a = f > 0 ? max((int64_t)0, row_ptr[f]) : 0;
+  const int64_t b = f + 1 < n_face ? min((int64_t)nnz, row_ptr[f + 1]) : nnz;
+  for (int64_t j = a + threadIdx.x % SW; j < b; j += SW) face_of[j] = (int32_t)f;
 }
 
 // Workgroup b runs on XCD b % 8 and takes its positions from the b % 8-th eighth: the lines
@@ -95,7 +98,8 @@ int build_transpose(long long n_face, long long n_phi, long long nnz, const int6
     hipLaunchKernelGGL(k_iota, dim3(nblocks(nnz, 256)), dim3(256), 0, st, vals_in, nnz);
     CC_HIP(hipcub::DeviceRadixSort::SortPairs(ws, temp, col, keys_out, vals_in, nz, (int)nnz, 0, key_bits(n_phi), st));
     int32_t* face_of = vals_in;   // the sort has read it
-    hipLaunchKernelGGL(k_row_face, dim3(nblocks(n_face * 16, 256)), dim3(256), 0, st, n_face, row_ptr, face_of);
+    hipLaunchKernelGGL(k_row_face, dim3(nblocks(std::max<long long>(n_face, 1) * 16, 256)), dim3(256), 0, st, n_face,
+                       nnz, row_ptr, face_of);
     hipLaunchKernelGGL(k_nz_face, dim3(nblocks(nblocks(nnz, 1024), kXcds) * kXcds), dim3(256), 0, st, nnz, face_of, nz, nz_face);
   }
   hipLaunchKernelGGL(k_col_ptr, dim3(nblocks(nnz + 1, 256)), dim3(256), 0, st, nnz, n_phi, keys_out, col_ptr);
