@@ -82,8 +82,10 @@ static int static_scratch(void** out) {
   return CUTCELL_OK;
 }
 
-// 64-bit words of counts, offs, flagged and qr_count
-static size_t host_words(size_t G) { return 4 * G + 3 * (G + 1) + 2; }
+// 64-bit words from counts to flagged
+static size_t flag_word(size_t G) {
+  return (align_up(sizeof(int64_t) * (4 * G + 3 * (G + 1))) + sizeof(int32_t) * kBinWords) / sizeof(int64_t);
+}
 
 size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   Work t{};
@@ -119,9 +121,10 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.tface = (int32_t*)take(sizeof(int32_t) * 3 * G);
   t.tmpl = (int32_t*)take(sizeof(int32_t) * totface);
   t.order_hist = (int32_t*)take(sizeof(int32_t) * (kNBuckets + 1) * order_tiles(G * g.ncell));
-  t.counts = (int64_t*)take(sizeof(int64_t) * host_words(G));
+  t.counts = (int64_t*)take(sizeof(int64_t) * (4 * (size_t)G + 3 * ((size_t)G + 1)));
   t.offs = t.counts + 4 * (size_t)G;
-  t.flagged = (int32_t*)(t.offs + 3 * ((size_t)G + 1));
+  t.bins = (int32_t*)take(sizeof(int32_t) * (kBinWords + 4));
+  t.flagged = t.bins + kBinWords;
   t.qr_count = t.flagged + 2;
   t.fcode = (int32_t*)take(sizeof(int32_t) * totface);
   t.fref = (int32_t*)take(sizeof(int32_t) * totface);
@@ -129,7 +132,6 @@ size_t layout_work(const cutcell_opts& o, int G, char* base, Work* w) {
   t.scan64 = (int64_t*)take(sizeof(int64_t) * (scan_tiles(totface) + 1));
   t.rp_tmp = (int64_t*)take(sizeof(int64_t) * (totface + 1));
   t.perm = (int32_t*)take(sizeof(int32_t) * totface);
-  t.bins = (int32_t*)take(sizeof(int32_t) * kBinWords);
   t.qr_list = (int32_t*)take(sizeof(int32_t) * totface);
   {
     const int M = binom(o.order + o.dim, o.dim);
@@ -256,14 +258,14 @@ static int prepare(const cutcell_geom* geoms, int G, const cutcell_opts* o, void
   for (int i = 0; i < G; ++i) maxeb = std::max(maxeb, geoms[i].n_eb);
   rc = enumerate_batch(w, *o, maxeb, st);
   if (rc) return rc;
-  const size_t words = host_words(G);
-  std::vector<int64_t> back(words);   // counts, offs, flagged
+  const size_t words = flag_word(G) + 2;
+  std::vector<int64_t> back(words);   // counts, offs, (bins,) flagged
   CC_HIP(hipMemcpyAsync(back.data(), w.counts, sizeof(int64_t) * words, hipMemcpyDeviceToHost, st));
   CC_HIP(hipStreamSynchronize(st));
   P->counts.assign(back.begin(), back.begin() + 4 * (size_t)G);
-  P->offs.assign(back.begin() + 4 * (size_t)G, back.end() - 2);
-  int32_t flags[4];
-  std::memcpy(flags, &back[words - 2], sizeof(flags));
+  P->offs.assign(back.begin() + 4 * (size_t)G, back.begin() + 4 * (size_t)G + 3 * ((size_t)G + 1));
+  int32_t flags[2];
+  std::memcpy(flags, &back[flag_word(G)], sizeof(flags));
   if (flags[1]) return fail(CUTCELL_E_INVALID_ARG, "eb_cell must be strictly ascending cells with kappa > 0");
   for (int i = 0; i < G; ++i) {
     P->n_vol += P->counts[4 * i + 0];

@@ -42,9 +42,14 @@ struct Work {
   int32_t* tface;       // [G][3]      template face per direction, or INT32_MAX
   int32_t* tmpl;        // [G*maxface] template of each face whose stencil is copied, else -1
   int32_t* order_hist;  // [kNBuckets + 1][order_tiles] faces per bucket and tile of cells, most rows per tile
-  // counts, offs, flagged and qr_count follow each other: one copy brings them to the host
+  // counts, offs, bins, flagged and qr_count follow each other, so that one copy brings them to
+  // the host.  flagged and qr_count share bins' cache line, not the one before: every face reads
+  // counts and offs, and a line that atomics write goes back and forth between the XCDs' L2s
+  // (3D order 2, 32^3, path radius 1, 70k rank-deficient faces: QR kernel 3855 us with all of
+  // them in one line, 901 us with counts and offs apart)
   int64_t* counts;      // [G][4]      n_vol, n_eb, n_box, n_gface
   int64_t* offs;        // [3][G+1]    phi_off, vol_off, face_off
+  int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows, nonzeros
   int32_t* flagged;     // [2] flagged faces, bad EB input
   int32_t* qr_count;    // [1] faces left to the Householder QR path
   int32_t* fcode;       // [G*maxface] per global flux face
@@ -53,7 +58,6 @@ struct Work {
   int64_t* scan64;      // int64 scan tiles over G*maxface
   int64_t* rp_tmp;      // [G*maxface + 1] row offsets when the caller has none (query)
   int32_t* perm;        // [G*maxface]
-  int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows, nonzeros
   int32_t* qr_list;     // [G*maxface] those faces
   double* qr_b;         // [qr_slots][2][kMaxRows * MS] the QR path's exact B per workgroup
   int qr_slots;         // min(kQrSlots, G*maxface)
