@@ -15,6 +15,7 @@
 // with every entry's place found by binary searches in the other rows, in both passes, and
 // the merged rows in 24 KB of shared memory, 2.36 and 2.81 ms.
 #include <algorithm>
+#include <cstddef>
 
 #include "gather.hpp"
 #include "scan.hpp"
@@ -25,9 +26,10 @@ namespace cutcell {
 constexpr int kLapPad = 1024;   // >= (2D+1) rows of <= kMaxRows entries
 constexpr int kLapFast = 512;   // hash table of the fill for rows of at most 7/8 of that
 
-// Hash table of at most CAP columns, and with FILL their sums and the list of them.
+// Hash table of at most CAP columns, and with FILL their sums and the list of them (which is
+// read 16 bytes at a time).
 template <int CAP, bool FILL>
-struct LapTable {
+struct __align__(16) LapTable {
   int32_t key[CAP];
   double sum[FILL ? CAP : 1];
   int32_t list[FILL ? CAP + 8 : 4];   // columns in the order they were added
@@ -60,6 +62,8 @@ __device__ __forceinline__ void merge_row(LapTable<CAP, FILL>& tb, long long v, 
                                           int32_t* __restrict__ lap_col, double* __restrict__ lap_val,
                                           int32_t* too_long) {
   constexpr int S = 2 * D + 1;
+  using Table = LapTable<CAP, FILL>;
+  static_assert(!FILL || (alignof(Table) >= 16 && offsetof(Table, list) % 16 == 0), "the list is read 16 bytes at a time");
   const int lane = threadIdx.x & 63;
   int64_t start[S];
   int len[S];
