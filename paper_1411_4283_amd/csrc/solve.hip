@@ -85,7 +85,7 @@ __global__ void k_jacobi(long long n_vol, const int32_t* __restrict__ vol_face, 
 // kMaxTiles-th), and leaves a partial sum per inner product; the launch that needs the sums
 // adds the partials itself, block by block alike and in a fixed order, so no launch or copy
 // stands between two of them and a solve is deterministic.  Coefficients stay on the device
-// (a column of H per step); the host reads the columns of several steps at once.  At 30k
+// (a column of H for each step of a batch); the host reads the columns of a batch at once.  At 30k
 // volumes (32^3, 3D order 4) a step is bound by the latency of its dependent launches and of
 // the loads in each: eleven launches, a copy and a wait took 88 to 100 us, four launches take
 // 41 (15 of them the product).
@@ -292,28 +292,31 @@ __global__ void k_update(long long n, int k, const double* __restrict__ c, const
   x[t] = fma(dinv[t], s, x[t]);
 }
 
-// The buffers of an Arnoldi process of at most m steps, and its launches.
+// The buffers of an Arnoldi process of at most m steps, and its launches.  The callers' needs
+// must not exceed what a process with 512 partial sums per inner product and one column of
+// coefficients took (a buffer of that size stays enough): hence only `batch` columns of H.
 struct Arnoldi {
   long long n;
-  int m, tiles, elems;
+  int m, batch, tiles, elems;
   double* V;          // [m + 1][n]
   double* w;          // [n]
   double* partial;    // [tiles][m + 1]
   double* partial2;   // [tiles][m + 1]
   double* c1;         // [m]
-  double* H;          // [m][m + 1] columns
+  double* H;          // [batch][m + 1] columns
   hipStream_t st;
 
-  static size_t bytes(long long n, int m) {
+  static size_t bytes(long long n, int m, int batch) {
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t nv = std::max<long long>(n, 1), nt = tile_count(n);
     return al(sizeof(double) * nv * (m + 1)) + al(sizeof(double) * nv) + al(sizeof(double) * nt * (m + 1)) +
-           al(sizeof(double) * nt * (m + 1)) + al(sizeof(double) * m) + al(sizeof(double) * m * (m + 1));
+           al(sizeof(double) * nt * (m + 1)) + al(sizeof(double) * m) + al(sizeof(double) * batch * (m + 1));
   }
   template <class Take>
-  void layout(long long n_, int m_, hipStream_t s, Take&& take) {
+  void layout(long long n_, int m_, int batch_, hipStream_t s, Take&& take) {
     n = n_;
     m = m_;
+    batch = batch_;
     st = s;
     tiles = tile_count(n);
     elems = tile_elems(n);
@@ -323,24 +326,30 @@ struct Arnoldi {
     partial = (double*)take(sizeof(double) * tiles * (m + 1));
     partial2 = (double*)take(sizeof(double) * tiles * (m + 1));
     c1 = (double*)take(sizeof(double) * m);
-    H = (double*)take(sizeof(double) * m * (m + 1));
+    H = (double*)take(sizeof(double) * batch * (m + 1));
   }
-  // w holds A v_j: v_{j+1}, phi and column j of H
+  // w holds A v_j: v_{j+1}, phi and the step's coefficients, into column c of H
   template <int E>
-  void step_e(int j, const double* dinv, const int32_t* vphi, double* phi) const {
+  void step_e(int j, int c, const double* dinv, const int32_t* vphi, double* phi) const {
     const int k = j + 1;
     const dim3 T(kTileThreads);
     hipLaunchKernelGGL(k_dots<E>, dim3(tiles, (k + kDotChunk - 1) / kDotChunk), T, 0, st, n, k, V, w, partial, m + 1);
     hipLaunchKernelGGL(k_orth<E>, dim3(tiles), T, sizeof(double) * (k + (kTileThreads / 64) * (k + 1)), st, n, k, V, w,
                        partial, m + 1, c1, partial2);
     hipLaunchKernelGGL(k_next<E>, dim3(tiles), T, sizeof(double) * (k + 1), st, n, k, V, w, partial2, m + 1, c1,
-                       H + (size_t)j * (m + 1), dinv, vphi, V + (long long)k * n, phi);
+                       H + (size_t)c * (m + 1), dinv, vphi, V + (long long)k * n, phi);
   }
-  void step(int j, const double* dinv, const int32_t* vphi, double* phi) const {
-    if (elems == 1) step_e<1>(j, dinv, vphi, phi);
-    else if (elems == 2) step_e<2>(j, dinv, vphi, phi);
-    else if (elems == 4) step_e<4>(j, dinv, vphi, phi);
-    else step_e<8>(j, dinv, vphi, phi);
+  void step(int j, int c, const double* dinv, const int32_t* vphi, double* phi) const {
+    if (elems == 1) step_e<1>(j, c, dinv, vphi, phi);
+    else if (elems == 2) step_e<2>(j, c, dinv, vphi, phi);
+    else if (elems == 4) step_e<4>(j, c, dinv, vphi, phi);
+    else step_e<8>(j, c, dinv, vphi, phi);
+  }
+  // the first nc columns of H to the host
+  int columns(int nc, double* out) const {
+    CC_HIP(hipMemcpyAsync(out, H, sizeof(double) * nc * (m + 1), hipMemcpyDeviceToHost, st));
+    CC_HIP(hipStreamSynchronize(st));
+    return CUTCELL_OK;
   }
   // |y| to the host
   int norm(const double* y, double* out) const {
@@ -362,7 +371,8 @@ size_t solve_workspace_bytes(long long n_vol, long long n_phi, long long n_face,
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t nv = std::max<long long>(n_vol, 1);
   return al(sizeof(double) * n_phi) * 2 + al(sizeof(double) * std::max<long long>(n_face, 1)) +
-         al(sizeof(double) * nv) * 3 + al(sizeof(int32_t) * nv) + al(sizeof(double) * m) + Arnoldi::bytes(n_vol, m);
+         al(sizeof(double) * nv) * 3 + al(sizeof(int32_t) * nv) + al(sizeof(double) * m) +
+         Arnoldi::bytes(n_vol, m, std::min(m, kBatch));
 }
 
 int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_t* vol_off, const double* phi_bc,
@@ -385,7 +395,7 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
   int32_t* vphi = (int32_t*)take(sizeof(int32_t) * nv);
   double* coef = (double*)take(sizeof(double) * m);
   Arnoldi A;
-  A.layout(n, m, st, take);
+  A.layout(n, m, std::min(m, kBatch), st, take);
   const int T = 256;
   const unsigned gv = nb(n, T);
 
@@ -446,11 +456,10 @@ int solve_poisson(const SolveOp& op, int G, const int64_t* phi_off, const int64_
       for (int q = 0; q < nj; ++q) {
         rc = apply(phi0, A.w);        // phi0 = [D^-1 v_j | 0]
         if (rc) return rc;
-        A.step(j0 + q, dinv, vphi, phi0);
+        A.step(j0 + q, q, dinv, vphi, phi0);
       }
-      CC_HIP(hipMemcpyAsync(hc.data(), A.H + (size_t)j0 * (m + 1), sizeof(double) * nj * (m + 1),
-                            hipMemcpyDeviceToHost, st));
-      CC_HIP(hipStreamSynchronize(st));
+      rc = A.columns(nj, hc.data());
+      if (rc) return rc;
       const double before = res;
       for (int q = 0; q < nj && !done; ++q, ++j, ++it) {
         // Givens rotations on column j of H
@@ -623,12 +632,16 @@ __global__ void k_start_vector(long long n, double* __restrict__ v) {
   v[i] = (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
+// Arnoldi steps between two reads of the coefficients: products with A alone read few times,
+// inner solves after each step
+static int ritz_batch(int k, int inner_m) { return inner_m > 0 ? 1 : std::min(k, 64); }
+
 size_t ritz_workspace_bytes(long long n_vol, long long n_phi, long long n_face, int k, int inner_m) {
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const size_t nv = std::max<long long>(n_vol, 1);
-  return al(sizeof(double) * n_phi) * 2 + al(sizeof(double) * std::max<long long>(n_face, 1)) +
-         al(sizeof(int32_t) * nv) + Arnoldi::bytes(n_vol, k) +
-         (inner_m > 0 ? solve_workspace_bytes(n_vol, n_phi, n_face, inner_m) : 0);
+  return al(sizeof(double) * n_phi) + al(sizeof(int32_t) * nv) + Arnoldi::bytes(n_vol, k, ritz_batch(k, inner_m)) +
+         (inner_m > 0 ? solve_workspace_bytes(n_vol, n_phi, n_face, inner_m)
+                      : al(sizeof(double) * std::max<long long>(n_face, 1)));
 }
 
 int ritz_values(const SolveOp& op, int G, const int64_t* phi_off, const int64_t* vol_off, int mode, int k,
@@ -642,50 +655,51 @@ int ritz_values(const SolveOp& op, int G, const int64_t* phi_off, const int64_t*
   auto take = [&](size_t bytes) { char* p = ws + off; off += al(bytes); return p; };
   const size_t nv = std::max<long long>(n, 1);
   hipStream_t st = op.st;
-  double* zero_bc = (double*)take(sizeof(double) * op.n_phi);   // Phi = 0 (the inner solves' data)
-  double* phi0 = (double*)take(sizeof(double) * op.n_phi);      // [v | 0]
-  double* flux = (double*)take(sizeof(double) * std::max<long long>(op.n_face, 1));
+  double* zeros = (double*)take(sizeof(double) * op.n_phi);   // mode 0: [v | 0]; mode 1: the inner solves' data
   int32_t* vphi = (int32_t*)take(sizeof(int32_t) * nv);
   Arnoldi A;
-  A.layout(n, k, st, take);
-  char* inner_ws = ws + off;
+  const int batch = ritz_batch(k, mode == 1 ? inner_m : 0);
+  A.layout(n, k, batch, st, take);
+  // mode 0: the product's scratch; mode 1: the inner solves', which begin by writing all of
+  // their first n_phi values, so that a step may leave the vector it scatters there
+  char* rest = ws + off;
+  double* phi0 = mode == 0 ? zeros : (double*)rest;
   const int T = 256;
   const unsigned gv = nb(n, T);
   hipLaunchKernelGGL(k_vol_phi, dim3(gv), dim3(T), 0, st, n, G, phi_off, vol_off, vphi);
-  hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, phi0, op.n_phi, 0.0);
-  hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, zero_bc, op.n_phi, 0.0);
+  hipLaunchKernelGGL(k_fill_f64, dim3(nb(op.n_phi, T)), dim3(T), 0, st, zeros, op.n_phi, 0.0);
   hipLaunchKernelGGL(k_start_vector, dim3(gv), dim3(T), 0, st, n, A.V);
   double nrm = 0.0;
   int rc = A.norm(A.V, &nrm);
   if (rc) return rc;
   hipLaunchKernelGGL(k_first, dim3(gv), dim3(T), 0, st, n, 1.0 / nrm, A.V, nullptr, vphi, phi0);
-  std::vector<double> Hm((size_t)(k + 1) * k, 0.0), hc((size_t)k * (k + 1));
+  std::vector<double> Hm((size_t)(k + 1) * k, 0.0), hc((size_t)batch * (k + 1));
   int kk = k, inner_fail = 0;
   for (int j = 0; j < k; ++j) {
     if (mode == 0) {
       rc = op.lap_ptr ? apply_laplacian(op.D, n, op.lap_ptr, op.lap_col, op.lap_val, phi0, A.w, st)
                       : apply_operator(op.D, op.n_face, n, op.row_ptr, op.col, op.val, op.vol_face, op.vol_scale, phi0,
-                                       A.w, flux, nullptr, st);
+                                       A.w, (double*)rest, nullptr, st);
       if (rc) return rc;
     } else {
       hipLaunchKernelGGL(k_fill_f64, dim3(gv), dim3(T), 0, st, A.w, n, 0.0);
       int it = 0;
       double rr = 0.0;
-      rc = solve_poisson(op, G, phi_off, vol_off, zero_bc, A.V + (long long)j * n, A.w, inner_m, inner_max, inner_rtol,
-                         inner_ws, solve_workspace_bytes(n, op.n_phi, op.n_face, inner_m), &it, &rr);
+      rc = solve_poisson(op, G, phi_off, vol_off, zeros, A.V + (long long)j * n, A.w, inner_m, inner_max, inner_rtol,
+                         rest, solve_workspace_bytes(n, op.n_phi, op.n_face, inner_m), &it, &rr);
       if (rc == CUTCELL_W_NOT_CONVERGED) inner_fail = 1;
       else if (rc) return rc;
     }
-    A.step(j, nullptr, vphi, phi0);
-    if (mode == 1 || j + 1 == k) {   // products with A alone run to the end; inner solves stop at once
-      const int j0 = mode == 1 ? j : 0;
-      CC_HIP(hipMemcpyAsync(hc.data() + (size_t)j0 * (k + 1), A.H + (size_t)j0 * (k + 1),
-                            sizeof(double) * (j + 1 - j0) * (k + 1), hipMemcpyDeviceToHost, st));
-      CC_HIP(hipStreamSynchronize(st));
+    A.step(j, j % batch, nullptr, vphi, phi0);
+    if ((j + 1) % batch == 0 || j + 1 == k) {
+      const int j0 = j - j % batch;
+      rc = A.columns(j + 1 - j0, hc.data());
+      if (rc) return rc;
       bool invariant = false;
       for (int c = j0; c <= j && !invariant; ++c) {
-        for (int i = 0; i <= c + 1; ++i) Hm[(size_t)i * k + c] = hc[(size_t)c * (k + 1) + i];
-        if (!(hc[(size_t)c * (k + 1) + c + 1] > 0.0)) {   // invariant subspace: its eigenvalues are exact
+        const double* h = hc.data() + (size_t)(c - j0) * (k + 1);
+        for (int i = 0; i <= c + 1; ++i) Hm[(size_t)i * k + c] = h[i];
+        if (!(h[c + 1] > 0.0)) {   // invariant subspace: its eigenvalues are exact
           kk = c + 1;
           invariant = true;
         }
