@@ -128,7 +128,7 @@ def c4_shapes(w):
 
 
 SCHEDULE_NOTE = ("per row-count bin (16 rows each): (XCD chunks, persistent workgroups per XCD or 0 for one per "
-                 "face, 0), chosen by timing on the workload")
+                 "face, 0), one for all bins of a launch, chosen by timing on the workload")
 
 
 def batched_comparison(steps):

@@ -255,9 +255,11 @@ int cutcell_build_stencils_noalloc(const cutcell_geom* geoms, int32_t n_geom, co
                                    const cutcell_sizes* sizes, cutcell_stencils* out, cutcell_stream_t stream);
 
 /* Builds the stencils like cutcell_build_stencils and, on the way, times every candidate
- * schedule of each row-count bin (best of `reps` runs, HIP events on `stream`), writing the
- * fastest to *tuning and each bin's best time in milliseconds to best_ms[8] (-1 for empty
- * bins; may be NULL).  opts->tuning is ignored.  Synchronises `stream`. */
+ * schedule (best of `reps` runs, HIP events on `stream`) of each launch -- the bins of up to
+ * 64, 96 and 128 rows -- and writes one schedule for the bins of a launch to *tuning: the
+ * fastest, or the default where no other is faster by a margin, both alone and in the whole
+ * solve.  best_ms[8] (may be NULL) gets the best time in milliseconds of the launch that takes
+ * the bin's faces (-1 for empty bins).  opts->tuning is ignored.  Synchronises `stream`. */
 int cutcell_autotune(const cutcell_geom* geoms, int32_t n_geom, const cutcell_opts* opts,
                      const cutcell_sizes* sizes, cutcell_stencils* out, void* workspace, size_t workspace_bytes,
                      int32_t reps, cutcell_tuning* tuning, double* best_ms, cutcell_stream_t stream);

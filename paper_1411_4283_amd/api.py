@@ -235,9 +235,10 @@ class Builder:
         self.opts.tuning = ctypes.pointer(tuning) if tuning is not None else None
 
     def autotune(self, out: "Stencils | None" = None, reps: int = 2, stream=None, cache: str | None = None):
-        """Time the candidate launch schedules and kernel widths of every row-count bin on
-        these geometries, keep the fastest (set_tuning) and return (tuning, best ms per bin).
-        `out` receives the stencils, as from build().
+        """Time the candidate launch schedules on these geometries, launch by launch (the bins
+        of up to 64, 96 and 128 rows), keep the fastest or, where none beats it by a margin,
+        the default (set_tuning) and return (tuning, best ms of each bin's launch).  `out`
+        receives the stencils, as from build().
 
         With `cache` (a JSON file), each bin's choice is kept under the key (GPU
         architecture, D, Q, path radius, bin): when every bin this workload fills has an

@@ -1505,27 +1505,28 @@ void launch_rows(const Work& w, double hscale, const int32_t* perm, long long nb
 #define CC_ROWS_ALL(DD, QQ) CC_ROWS(DD, QQ, 64, extern) CC_ROWS(DD, QQ, 96, extern) CC_ROWS(DD, QQ, 128, extern)
 CC_ROWS_ALL(2, 2) CC_ROWS_ALL(2, 4) CC_ROWS_ALL(3, 2) CC_ROWS_ALL(3, 4)
 
-// The row bins of one (dimension, order): bins that run on the same kernel with the same
-// schedule share a launch (their faces follow each other in the order), so that a small
-// build pays for two launches and no bin ends with a nearly empty chip.
+// Rows of the kernel that takes bin b.
+constexpr int bin_width(int b) { return kBinRows * (b + 1) <= 64 ? 64 : (kBinRows * (b + 1) <= 96 ? 96 : 128); }
+
+// The row bins of one (dimension, order), or those of one kernel width: bins that run on the
+// same kernel with the same schedule share a launch (their faces follow each other in the
+// order), so that a small build pays for two launches and no bin ends with a nearly empty chip.
 template <int D, int Q>
 int dispatch_row_bins(const Work& w, double hscale, const int32_t* bin_count, const int64_t* row_ptr,
                       const int32_t* col, double* val, int8_t* status, hipStream_t st, const BackwardArgs* bw,
-                      const BinSchedule* sched, int only_bin, bool neu, double h, double wpow) {
+                      const BinSchedule* sched, int only_width, bool neu, double h, double wpow) {
   constexpr int M = binom(Q + D, D);
-  auto width = [](int b) { return kBinRows * (b + 1) <= 64 ? 64 : (kBinRows * (b + 1) <= 96 ? 96 : 128); };
   long long start = 0;
   for (int b = 0; b < kMaxBins;) {
     long long nb = bin_count[b];
-    const bool skip = only_bin >= 0 && b != only_bin;
+    const bool skip = only_width > 0 && bin_width(b) != only_width;
     if (nb > 0 && kBinRows * (b + 1) < M && !skip)
       return fail(CUTCELL_E_INVALID_ARG, "internal: face with N >= M in a bin narrower than M");
     int e = b + 1;
-    if (only_bin < 0)
-      for (; e < kMaxBins && width(e) == width(b) && (bw || sched[e].same(sched[b])); ++e) nb += bin_count[e];
+    for (; e < kMaxBins && bin_width(e) == bin_width(b) && (bw || sched[e].same(sched[b])); ++e) nb += bin_count[e];
     if (!skip) {
-      const auto launch = width(b) == 64 ? launch_rows<D, Q, 64> : (width(b) == 96 ? launch_rows<D, Q, 96>
-                                                                                   : launch_rows<D, Q, 128>);
+      const auto launch = bin_width(b) == 64 ? launch_rows<D, Q, 64>
+                                             : (bin_width(b) == 96 ? launch_rows<D, Q, 96> : launch_rows<D, Q, 128>);
       launch(w, hscale, w.perm + start, nb, row_ptr, col, val, status, st, bw, sched[b], neu, h, wpow);
     }
     start += nb;
