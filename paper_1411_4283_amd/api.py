@@ -240,8 +240,8 @@ class Builder:
         the default (set_tuning) and return (tuning, best ms of each bin's launch).  `out`
         receives the stencils, as from build().
 
-        With `cache` (a JSON file), each bin's choice is kept under the key (GPU
-        architecture, D, Q, path radius, bin): when every bin this workload fills has an
+        With `cache` (a JSON file), each bin's choice is kept under the key (GPU architecture,
+        version of the launches, D, Q, path radius, bin): when every bin this workload fills has an
         entry, those are used without timing (best ms then -1, and self.tuned_from_cache is
         True); otherwise every bin is timed and the file gets the new entries."""
         if self.sizes is None:
@@ -270,7 +270,7 @@ class Builder:
 
     def _cache_prefix(self) -> str:
         arch = torch.cuda.get_device_properties(self.device).gcnArchName.split(":")[0]
-        return f"{arch}/D{self.dim}/Q{self.opts.order}/R{self.opts.path_radius}"
+        return f"{arch}/{CACHE_VERSION}/D{self.dim}/Q{self.opts.order}/R{self.opts.path_radius}"
 
     def _tuning_from_cache(self, path: str, out: "Stencils", stream) -> "Tuning | None":
         entries = _cache_load(path)
@@ -362,6 +362,11 @@ class Builder:
                                            garr, _ptr(wb), _ptr(ws), ws.numel(), _stream(stream))
         check(rc, "cutcell_stencils_backward", allow_flagged=False)
         return out, (None if wb is None else wb[: s.nnz])
+
+
+# Raised when the kernels' widths or the grouping of their launches change: times of other
+# launches choose schedules that may be slower than the default.
+CACHE_VERSION = "v2"
 
 
 def _cache_load(path: str) -> dict:
