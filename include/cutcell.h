@@ -244,7 +244,7 @@ int cutcell_build_stencils(const cutcell_geom* geoms, int32_t n_geom, const cutc
  * device array of CUTCELL_STATIC_SCRATCH_BYTES per GPU, held from the library's loading to
  * the end of the process; a batch whose workspace (cutcell_workspace_bytes) is larger is
  * refused with CUTCELL_E_WORKSPACE before any work (256 MiB holds one geometry up to 64^3 at
- * order 4, which needs about 198 MiB).  The call allocates nothing and records no profiling events.  Every call on one
+ * order 4, which needs about 210 MiB).  The call allocates nothing and records no profiling events.  Every call on one
  * GPU uses that GPU's array, which keeps the last call's contents (the build clears what it
  * needs), so calls that overlap on one GPU -- other threads, other streams -- race and must
  * be serialised by the caller.  `sizes` comes from cutcell_query (with a workspace of the

@@ -191,8 +191,8 @@ __global__ __launch_bounds__(64) void k_lap_count(long long n_vol, const int32_t
                                nullptr, too_long);
 }
 
-// Volumes whose merged rows fit the small table, one wave each: 9 KB of shared memory leave
-// 17 waves to a CU, the large table's 18 KB nine.
+// Volumes whose merged rows fit the small table, one wave each: 9,264 bytes of shared memory
+// leave 17 waves to a CU, the large table's 18,480 eight.
 constexpr int kLapFastRows = kLapFast / 8 * 7;
 template <int D>
 __global__ __launch_bounds__(64) void k_lap_fill(long long n_vol, const int32_t* __restrict__ vol_face,

@@ -210,14 +210,6 @@ struct WaveMatrix {
   double sd;            // of component `lane`
 };
 
-// Shared memory of one face (one wave): 64 rows of B and one buffer used in turn for the EB
-// normal moments, the tile transposition, the pivot blocks and z.  20.3 KB in 3D order 4, so
-// that eight waves share the 160 KB of a CU, two on each SIMD; with every row in shared
-// memory it was 26 KB at 88 rows and six waves.  The slots hold rows 0..63 (state 0), or
-// rows 64 and up in the first slots instead of the ones that belong there (state 1); the
-// contents of the slots concerned that are not in place are kept in registers, flat (18 per
-// lane for 32 slots), and exchanged (RowSwap).  Rows held in registers row by row (140 a
-// lane) left too few for the rest of the solve: 104 spilled, 3 of 13 ms.
 // The lines of monomials along each direction: idx[dir][line][p] is the one with exponent p in
 // `dir`, -1 past the order.
 template <int D, int Q>
@@ -266,6 +258,14 @@ struct SmallRow {
   int dd_dir, slot;       // direction of a box face, else -1; the row's slot of Bs
 };
 
+// Shared memory of one face (one wave): 64 rows of B and one buffer used in turn for the EB
+// normal moments, the tile transposition, the pivot blocks and z.  20.3 KB in 3D order 4, so
+// that eight waves share the 160 KB of a CU, two on each SIMD; with every row in shared
+// memory it was 26 KB at 88 rows and six waves.  The slots hold rows 0..63 (state 0), or
+// rows 64 and up in the first slots instead of the ones that belong there (state 1); the
+// contents of the slots concerned that are not in place are kept in registers, flat (18 per
+// lane for 32 slots), and exchanged (RowSwap).  Rows held in registers row by row (140 a
+// lane) left too few for the rest of the solve: 104 spilled, 3 of 13 ms.
 template <int D, int Q>
 struct FaceSmem {
   static constexpr int M = Dims<D, Q>::M, MS = Dims<D, Q>::MS, M1 = Dims<D, Q>::M1;
@@ -1183,8 +1183,14 @@ __device__ __forceinline__ void stencil_face(const StencilArgs& A, long long t, 
   }
 }
 
-// Waves per SIMD that the kernels are built for: two where the rows of B fill the
-// registers (3D order 4), four otherwise (shared memory allows no more).
+// Waves per SIMD that the kernels are built for: two where the rows of B fill the registers
+// (3D order 4, 200 to 256 of them, where 20.3 KB of shared memory allow no more), and at least
+// four otherwise.  With one workgroup per face that is four in 2D order 4 (108 registers and
+// 10.0 KB, which allow no more), four to five in 3D order 2 (92 to 116, 8.0 KB) and six in 2D
+// order 2 (76, 6.0 KB), without spills.  What spills: persistent instances (WALK), 12 to 90
+// registers, and Neumann instances in fourth order (3D: 20, 220 and 329 at 64, 96 and 128
+// rows), which still take half the time that they took with every row in shared memory (3D,
+// 40^3, whole build 6.5 and 3.6 ms).
 template <int D, int Q>
 constexpr int kWaves = Dims<D, Q>::M > 16 ? 2 : 4;
 

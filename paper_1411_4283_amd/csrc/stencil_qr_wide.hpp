@@ -2,7 +2,8 @@
 // under Dirichlet EB conditions: the same steps, the work of each spread over the workgroup.
 //   * rows: a thread per line of a row's monomials, direction after direction;
 //   * factors: four lanes hold a column in registers, only the reflectors pass through shared
-//     memory;
+//     memory (four waves per SIMD leave 128 registers: 48 to 53 are spilled, in the parts in
+//     double-double too; three waves: 447 us where four take 303, 64^3);
 //   * refinement: the residuals by all waves, the triangular solves and reflectors by the
 //     first.
 //
