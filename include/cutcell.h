@@ -119,8 +119,8 @@ typedef void* cutcell_stream_t; /* hipStream_t */
 
 /* Launch schedule of the stencil solves, per row-count bin b (faces with
  * 16 b < N <= 16 (b + 1) rows).  Results do not depend on it (every face is solved the same
- * way); only the order in which workgroups take faces does.  Bins of at most 64 rows share
- * a launch where their entries agree, and so do the others.
+ * way); only the order in which workgroups take faces does.  Bins of one kernel width (up to
+ * 64, 96 and 128 rows) share a launch where their entries agree.
  *   xcd_chunks[b]     1: faces in bin order over the workgroups; 8: the bin is cut into
  *                     8 contiguous chunks, one per XCD (MI355X deals workgroups to its 8
  *                     XCDs in turn, each with its own L2), so faces that share rows share

@@ -45,8 +45,8 @@ struct Work {
   // counts, offs, bins, flagged and qr_count follow each other, so that one copy brings them to
   // the host.  flagged and qr_count share bins' cache line, not the one before: every face reads
   // counts and offs, and a line that atomics write goes back and forth between the XCDs' L2s
-  // (3D order 2, 32^3, path radius 1, 70k rank-deficient faces: QR kernel 3855 us with all of
-  // them in one line, 901 us with counts and offs apart)
+  // (3D order 2, 32^3, path radius 1, 70k rank-deficient faces: whole build 5.0 ms with all of
+  // them in one line, 2.0 ms with counts and offs apart)
   int64_t* counts;      // [G][4]      n_vol, n_eb, n_box, n_gface
   int64_t* offs;        // [3][G+1]    phi_off, vol_off, face_off
   int32_t* bins;        // [kBinWords] bucket counts, bucket starts, max rows, nonzeros

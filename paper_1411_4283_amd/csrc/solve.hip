@@ -88,7 +88,7 @@ __global__ void k_jacobi(long long n_vol, const int32_t* __restrict__ vol_face, 
 // (a column of H for each step of a batch); the host reads the columns of a batch at once.  At 30k
 // volumes (32^3, 3D order 4) a step is bound by the latency of its dependent launches and of
 // the loads in each: eleven launches, a copy and a wait took 88 to 100 us, four launches take
-// 41 (15 of them the product).
+// 42 (37 in the kernels, 15 of them the product).
 constexpr int kTileThreads = 256;
 constexpr int kMaxTiles = 512;
 constexpr int kDotChunk = 8;         // vectors per block of k_dots
